@@ -142,7 +142,9 @@ typedef enum {
                                    (default), 1, 2 or 4 */
     PASE_OPT_C_SPLITS = 10,     /* same kernel: workgroups sharing one tile's c range (partial
                                    keys reduced by a second launch), 0 = chosen (default), else
-                                   min(value, K_v) for every vertex */
+                                   min(value, K_v) for every vertex.  Any of these four knobs set,
+                                   or PASE_OPT_HOIST_ELEMS below its default, also keeps every
+                                   vertex off the class form (which has no tiles and no prep) */
     PASE_OPT_CONFIG_SET = 12,   /* configuration set of the next pase_enumerate_configs: 0
                                    (default) power-of-two split factors, p = 2^L <= 65536; 1
                                    every tuple of positive integer factors (Sec. II's C(v)),
@@ -182,10 +184,10 @@ typedef enum {
                                    use the direct fill: every term of recurrence (4) summed per
                                    cell from its source arrays in one launch, no prep blocks --
                                    for the long chains of small dependent vertices, where launch
-                                   count dominates.  A level uses it only when all its vertices
-                                   qualify (so that it saves launches; any vertex under the
-                                   sequential schedule).  Default 2^18; 0 = never.  Not used with
-                                   PASE_OPT_KERNEL = 1 */
+                                   count dominates.  With caller-given costs or the volume model a
+                                   level uses it only when all its vertices qualify (so that it
+                                   saves launches; any vertex under the sequential schedule).
+                                   Default 2^18; 0 = never.  Not used with PASE_OPT_KERNEL = 1 */
     PASE_OPT_BULK_US = 17,      /* schedules 4 and 5: planned fill time (microseconds) from which a
                                    row-kernel vertex runs on the bulk stream (default 100) */
     PASE_OPT_FUSED_MIN = 20,    /* 1 (default): a row-kernel vertex without a column digit whose one
@@ -225,7 +227,7 @@ typedef struct {
     uint32_t max_dep;          /* max |D(i)| */
     uint32_t key_type;         /* 0 = fp64 exact-integer keys, 1 = uint64 keys */
     uint32_t launches;         /* kernels launched by the search */
-    uint32_t rows_vertices;    /* vertices filled by the row/column-chunk kernel */
+    uint32_t rows_vertices;    /* vertices filled by the row/column-chunk kernel (not its class form) */
     uint64_t rows_cells;       /* cells filled by that kernel */
     double host_plan_ms;       /* pase_enumerate_configs (host): seq_ms + plan_ms */
     double wall_ms;            /* pase_find_best_strategy, host wall clock */
@@ -376,13 +378,14 @@ pase_status pase_stats(pase_graph_t g, pase_run_stats *out);
  * PASE_OPT_PROFILE=1, its fill time. */
 typedef struct {
     uint32_t position;   /* index in the GenerateSeq order */
-    uint32_t kernel;     /* 0 = generic fill, 1 = row/column-chunk fill, 2 = direct fill */
+    uint32_t kernel;     /* 0 = generic fill, 1 = row/column-chunk fill (tile_cols 0: its class form, which
+                            evaluates the column digit's transfer cost per split class), 2 = direct fill */
     uint32_t num_configs, dep_count;
     uint64_t entries;    /* |table| = product of K over D(v) */
     uint64_t cells;      /* K_v * entries */
     int32_t column;      /* row kernel: column digit (vertex id), -1 for none or the generic kernel */
     uint32_t outer, rows, tile_cols;
-    uint32_t tile_rows;  /* rows per lane (1 or 2) */
+    uint32_t tile_rows;  /* rows per lane (1 or 2); class form: rows per workgroup */
     uint32_t splits, row_terms, lookups;
     uint32_t parts;      /* row kernel: waves sharing one tile's c range (1, 2 or 4) */
     double fill_ms;      /* PASE_OPT_PROFILE: event time of this vertex's fill kernel */

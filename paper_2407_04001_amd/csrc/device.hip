@@ -42,12 +42,38 @@ constexpr uint32_t kSidePrepBlocks = 256;   // grid of a hoisted prep: one workg
 // signatures and two device bytes (edge_cost_sig).  The same launch sets the
 // nF keys of the fused minima to the sentinel `fill` (with caller-given costs
 // it runs for that alone, nL = nS = 0).
-__global__ void k_cost_tables(const DevVertex *__restrict__ V, uint32_t nv, const DevEdge *__restrict__ E,
+//
+// For class fills (ct.Lk non-null) it also writes the key-space forms they
+// read -- (layer cost << bits) + c, and each edge end's
+// f = r * ceil(elems / P) << bits -- and, in the workgroups past nbase, the
+// class tables.
+struct ClassOut {
+    void *Lk, *fk;            // KeyT arrays, parallel to L and sig; null: no class fill
+    uint32_t fp64, ntabs;
+    const DevClassTab *tabs;
+    char *ws;
+};
+
+__global__ __launch_bounds__(256) void k_cost_tables(const DevVertex *__restrict__ V, uint32_t nv,
+                              const DevEdge *__restrict__ E,
                               uint32_t ne, const uint8_t *__restrict__ ex, uint64_t *__restrict__ L,
                               uint8_t *__restrict__ lsum, uint64_t *__restrict__ sig, uint64_t nL,
-                              uint64_t nS, uint64_t r, uint64_t *__restrict__ fkeys, uint64_t nF, uint64_t fill) {
+                              uint64_t nS, uint64_t r, uint64_t *__restrict__ fkeys, uint64_t nF, uint64_t fill,
+                              ClassOut ct, uint32_t nbase) {
+    __shared__ uint64_t buf[kClassTabTile];
+    if (blockIdx.x >= nbase) {
+        const uint32_t b = blockIdx.x - nbase;
+        uint32_t lo = 0;
+        while (lo + 1 < ct.ntabs && ct.tabs[lo + 1].blk0 <= b) lo++;
+        class_table_item(ct.tabs[lo], b - ct.tabs[lo].blk0, ex, ct.ws, buf);
+        return;
+    }
+    auto put_key = [&](void *at, uint64_t i, uint64_t key) {
+        if (ct.fp64) ((double *)at)[i] = (double)key;
+        else ((uint64_t *)at)[i] = key;
+    };
     for (uint64_t t = blockIdx.x * (uint64_t)blockDim.x + threadIdx.x; t < nL + nS + nF;
-         t += (uint64_t)gridDim.x * blockDim.x) {
+         t += (uint64_t)nbase * blockDim.x) {
         if (t >= nL + nS) {
             fkeys[t - nL - nS] = fill;
         } else if (t < nL) {
@@ -58,8 +84,10 @@ __global__ void k_cost_tables(const DevVertex *__restrict__ V, uint32_t nv, cons
             }
             const DevVertex dv = V[lo];
             const uint8_t *e = ex + dv.ex_off + (t - dv.L_off) * dv.ndims;
-            L[t] = layer_cost(dv, e, r);
+            const uint64_t cost = layer_cost(dv, e, r);
+            L[t] = cost;
             lsum[t] = (uint8_t)device_byte(dv, e);
+            if (ct.Lk) put_key(ct.Lk, t, (cost << dv.bits) + (t - dv.L_off));
         } else {
             uint64_t u = t - nL;
             uint32_t lo = 0, hi = ne;   // last edge with sig_off <= u
@@ -69,13 +97,16 @@ __global__ void k_cost_tables(const DevVertex *__restrict__ V, uint32_t nv, cons
             }
             const DevEdge de = E[lo];
             uint64_t c = u - de.sig_off;
-            const DevVertex vs = V[de.src];
-            if (c < vs.K) {
-                sig[u] = split_signature(de.sdim, de.rank, ex + vs.ex_off + c * vs.ndims, de.factors);
-            } else {
-                const DevVertex vd = V[de.dst];
-                c -= vs.K;
-                sig[u] = split_signature(de.ddim, de.rank, ex + vd.ex_off + c * vd.ndims, de.factors);
+            const uint32_t Ks = V[de.src].K;
+            const bool src = c < Ks;
+            const DevVertex ve = V[src ? de.src : de.dst];
+            if (!src) c -= Ks;
+            const uint8_t *e = ex + ve.ex_off + c * ve.ndims;
+            sig[u] = split_signature(src ? de.sdim : de.ddim, de.rank, e, de.factors);
+            if (ct.Lk) {
+                const uint32_t P = device_byte(ve, e);
+                const uint64_t f = de.factors ? ceil_div_u64(de.elems, P) : (de.elems + ((1ull << P) - 1)) >> P;
+                put_key(ct.fk, u, (r * f) << de.bits);
             }
         }
     }
@@ -277,6 +308,32 @@ __global__ __launch_bounds__(256) void k_fill_direct(const DirectArgs *__restric
     const uint32_t kb = batch_find(be, nbe, blockIdx.x);
     set_priority(be[kb]);
     direct_item<KeyT>(descs[be[kb].pos], blockIdx.x - be[kb].first, V, E, L, lsum, sig, cb, r, xch);
+}
+
+// Class fill of the vertices of one level; `one` names the vertex of a
+// one-vertex launch (the chains of small vertices: its descriptor is then the
+// first load, without a search through the batch), ~0 otherwise.
+template <typename KeyT>
+__global__ __launch_bounds__(512) void k_fill_class(const ClassArgs *__restrict__ descs,
+                                                              const BatchEntry *__restrict__ be, uint32_t nbe,
+                                                              uint32_t one, uint32_t prio) {
+    extern __shared__ __align__(16) char lds[];
+    if (prio) __builtin_amdgcn_s_setprio(3);
+    uint32_t pos = one, lb = blockIdx.x;
+    if (one == ~0u) {
+        const uint32_t kb = batch_find(be, nbe, blockIdx.x);
+        pos = be[kb].pos;
+        lb -= be[kb].first;
+    }
+    const ClassArgs &a = descs[pos];
+    switch (a.ne * 8 + a.nt) {
+#define PASE_CLASS(ne, nt) case ne * 8 + nt: class_item<KeyT, ne, nt>(a, lb, lds); break;
+#define PASE_CLASS_E(ne) PASE_CLASS(ne, 0) PASE_CLASS(ne, 1) PASE_CLASS(ne, 2) PASE_CLASS(ne, 3) PASE_CLASS(ne, 4)
+        PASE_CLASS_E(0) PASE_CLASS_E(1) PASE_CLASS_E(2) PASE_CLASS_E(3) PASE_CLASS_E(4)
+#undef PASE_CLASS_E
+#undef PASE_CLASS
+    default: break;
+    }
 }
 
 // ------------------------------------------------------------------ back-substitution
@@ -564,6 +621,7 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
     const GenericArgs *dg = (const GenericArgs *)(dr + n);
     const ReduceArgs *dd = (const ReduceArgs *)(dg + n);
     const DirectArgs *dx = (const DirectArgs *)(dd + n);
+    const ClassArgs *dcl = (const ClassArgs *)(dx + n);
     const BatchEntry *dbe = (const BatchEntry *)(ws + P.off_batch);
     uint32_t *dcfg = (uint32_t *)(ws + P.off_cfg);
     SearchOut *dout = (SearchOut *)(ws + P.off_out);
@@ -572,7 +630,7 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
     // the row kernel with a column chunk per lane (profile 2)
     const int profile = noalloc ? 0 : g->profile;
     auto timed = [&](const Batch &b) {
-        if (profile == 1) return b.kind == Batch::kRows || b.kind == Batch::kGeneric || b.kind == Batch::kDirect;
+        if (profile == 1) return b.kind != Batch::kPrep && b.kind != Batch::kReduce;
         return profile == 2 && b.kind == Batch::kRows && b.variant / 32 != 1;
     };
     uint32_t nfill = 0;
@@ -603,13 +661,23 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
     uint64_t *dfk = (uint64_t *)(ws + P.off_fused);
     if (g->overridden && nF) {
         hipLaunchKernelGGL(k_cost_tables, dim3(grid_for(nF)), dim3(256), 0, s, dV, (uint32_t)nv, dE, (uint32_t)ne, dex,
-                           dL, dls, dsig, (uint64_t)0, (uint64_t)0, g->r, dfk, nF, fsent);
+                           dL, dls, dsig, (uint64_t)0, (uint64_t)0, g->r, dfk, nF, fsent, ClassOut{}, grid_for(nF));
         launches_n++;
     }
     if (!g->overridden) {
-        hipLaunchKernelGGL(k_cost_tables, dim3(grid_for(si.nL + P.sig_count + nF)), dim3(256), 0, s, dV,
+        ClassOut ct{};
+        if (P.class_fills) {
+            ct.Lk = ws + P.off_Lk;
+            ct.fk = ws + P.off_fk;
+            ct.fp64 = std::is_same<KeyT, double>::value;
+            ct.ntabs = (uint32_t)P.ctabs.size();
+            ct.tabs = (const DevClassTab *)(ws + P.off_ctdesc);
+            ct.ws = ws;
+        }
+        const uint32_t nbase = grid_for(si.nL + P.sig_count + nF);
+        hipLaunchKernelGGL(k_cost_tables, dim3(nbase + P.ctab_blocks), dim3(256), 0, s, dV,
                            (uint32_t)nv, dE, (uint32_t)ne, dex, dL, dls, dsig, si.nL, P.sig_count, g->r, dfk, nF,
-                           fsent);
+                           fsent, ct, nbase);
         launches_n++;
         if (g->volume && g->mat_total) {
             hipLaunchKernelGGL(g->factors ? k_edge_volume : k_edge_volume_pow2, dim3(grid_for(g->mat_rows, 1, 65535)),
@@ -729,6 +797,7 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
         case Batch::kRows:
         case Batch::kGeneric:
         case Batch::kDirect:
+        case Batch::kClass:
         {
             // with profiling, the launch itself records its start and end
             // (events attached to the dispatch, no extra packets in the stream)
@@ -739,7 +808,10 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
             if (b.kind == Batch::kGeneric) {
                 launch_generic<KeyT>(dg, e, b, bs, e0, e1);
             } else if constexpr (kWide) {
-                return fail(g, PASE_ERR_INTERNAL, "a 128-bit key plan holds a row or direct fill");
+                return fail(g, PASE_ERR_INTERNAL, "a 128-bit key plan holds a row, direct or class fill");
+            } else if (b.kind == Batch::kClass) {
+                hipExtLaunchKernelGGL((k_fill_class<KeyT>), dim3(b.blocks), dim3(b.variant), b.lds, bs, e0, e1, 0,
+                                      dcl, e, b.nentries, b.nentries == 1 ? b.pos0 : ~0u, (uint32_t)(si.lanes && b.lane == 0));
             } else if (b.kind == Batch::kRows) {
                 if (!launch_rows<KeyT>(dr, dg, e, b, bs, e0, e1)) return fail(g, PASE_ERR_INTERNAL, "no kernel for TZ");
             } else {

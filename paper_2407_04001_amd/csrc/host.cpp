@@ -397,11 +397,11 @@ static void fuse_minima(pase_graph_t g, Plan &P) {
     const int n = (int)P.v.size();
     for (int i2 = 0; i2 < n; i2++) {
         VPlan &b = P.v[i2];
-        if (b.kernel != kRows || b.z >= 0 || b.nsplit != 1 || b.terms.size() != 1 || b.terms[0].dig.size() < 2)
+        if (b.kernel != kRows || b.classes || b.z >= 0 || b.nsplit != 1 || b.terms.size() != 1 || b.terms[0].dig.size() < 2)
             continue;
         const int i1 = b.terms[0].j;
         VPlan &a = P.v[i1];
-        if (a.kernel != kRows || a.z != b.vi || !a.O.empty() || a.R != b.R || a.nsplit != 1 || a.consumer != i2 ||
+        if (a.kernel != kRows || a.classes || a.z != b.vi || !a.O.empty() || a.R != b.R || a.nsplit != 1 || a.consumer != i2 ||
             a.lane != b.lane || a.fuse_into >= 0 || a.fused_from >= 0)
             continue;
         a.fuse_into = i2;
@@ -423,7 +423,7 @@ static void fuse_minima(pase_graph_t g, Plan &P) {
 // more than it saves).
 static void hoist_preps(pase_graph_t g, Plan &P, bool lanes) {
     for (auto &vp : P.v) {
-        if ((vp.kernel != kRows && vp.kernel != kGeneric) || vp.fused_from >= 0 || vp.fuse_into >= 0) continue;
+        if ((vp.kernel != kRows && vp.kernel != kGeneric) || vp.classes || vp.fused_from >= 0 || vp.fuse_into >= 0) continue;
         uint64_t elems = 0;
         int ready = -1;
         int lane = -1;            // lane of the tables the blocks read (-2: more than one)
@@ -474,9 +474,15 @@ static void hoist_preps(pase_graph_t g, Plan &P, bool lanes) {
 // waits for a large fill, so a chain of small dependent vertices runs beside
 // the large fills instead of after them.  Producers precede their reader in
 // the sequence, so one pass suffices.
+// (A class fill counts from a quarter of the threshold: it is bound by the
+// stores of its table, which hold up the other lane's loads as well.)
+static bool bulk_fill(const VPlan &vp, double bulk_us) {
+    return vp.kernel == kRows && vp.est_us * (vp.classes ? 4.0 : 1.0) >= bulk_us;
+}
+
 static void assign_bulk_lanes(Plan &P, double bulk_us) {
     for (auto &vp : P.v) {
-        bool bulk = vp.kernel == kRows && vp.est_us >= bulk_us;
+        bool bulk = bulk_fill(vp, bulk_us);
         for (const auto &t : vp.terms) bulk |= P.v[t.j].lane == 1;
         vp.lane = bulk ? 1 : 0;
     }
@@ -493,7 +499,7 @@ static void assign_bulk_lanes(Plan &P, double bulk_us) {
 // for each other level by level.
 static void assign_split_lanes(Plan &P, double bulk_us) {
     for (auto &vp : P.v) {
-        bool one = vp.level < kSplitBatchedLevels || (vp.kernel == kRows && vp.est_us >= bulk_us);
+        bool one = vp.level < kSplitBatchedLevels || bulk_fill(vp, bulk_us);
         for (const auto &t : vp.terms) one |= P.v[t.j].lane == 1 && P.v[t.j].level >= kSplitBatchedLevels;
         vp.lane = one ? 1 : 0;
     }
@@ -628,13 +634,94 @@ static pase_status build_plan(pase_graph_t g) {
     // split
     // 128-bit keys: every vertex on prep + the generic kernel
     const int kernel_mode = g->plan_wide ? 1 : g->kernel_mode;
+    // Class fill: with the split match model and no tile knob set, a digit z
+    // that meets v_i in one edge and in no lookup.  The digit with the most
+    // configurations leaves the fewest rows.  Always better than the dense
+    // fills where it applies (K * rest instead of K * rest * Kz cells, no prep
+    // launch: 2.05 -> 0.24 ms on the Transformer's largest level at p = 64, 17
+    // -> 6 us on its small chain vertices); a direct vertex without such a
+    // digit takes the same kernel's plain minimum (8.2 -> 5.5 us per launch on
+    // the residual CNN at p = 8).  The tile knobs and a hoisting threshold below its default
+    // ask for the dense fills and their preps, which they then get.
+    const bool class_ok = kernel_mode == 0 && !g->volume && !g->overridden && !g->tile_cols && !g->tile_rows &&
+                          !g->tile_parts && !g->c_splits && (!g->hoist_elems || g->hoist_elems >= kHoistElems);
+    auto plan_class = [&](int i, bool direct) {
+        VPlan &vp = P.v[i];
+        if (!class_ok || vp.K > kClassMaxK || vp.terms.size() > (size_t)kMaxClassTerms) return false;
+        auto edges_to = [&](int w) {
+            int k = 0;
+            for (int e : vp.edges) k += (int)g->E[e].src == w || (int)g->E[e].dst == w;
+            return k;
+        };
+        int z = -1;
+        for (int w : vp.D) {
+            bool looked = g->K[w] > kClassMaxK || edges_to(w) != 1;
+            for (const auto &t : vp.terms) looked |= std::count(t.dig.begin(), t.dig.end(), w) > 0;
+            if (!looked && (z < 0 || g->K[w] > g->K[z])) z = w;
+        }
+        if ((z < 0 && !direct) || vp.edges.size() - (z >= 0) > (size_t)kMaxClassEdges) return false;
+        const std::vector<int> order = gather_layout(vp);
+        std::vector<int> R;
+        for (int u : order)
+            if (u != z) R.push_back(u);
+        uint64_t rows = 1;
+        for (int u : R) rows *= g->K[u];
+        const uint32_t Kz = z >= 0 ? g->K[z] : 1;
+        const uint32_t ne = (uint32_t)vp.edges.size() - (z >= 0), nt = (uint32_t)vp.terms.size();
+        auto fits = [&](uint32_t lr, bool keep) {
+            return class_lds(vp.K, Kz, ne, nt, lr, z >= 0, keep, 512) <= kClassMaxLds;
+        };
+        // rows per workgroup.  Few rows: so many that there is about one
+        // workgroup per CU and every lane group has a configuration (X in
+        // LDS).  Many rows: 64, a whole wave's, so that the table is stored in
+        // full lines; X then fits up to K of about 100, else it is formed
+        // twice -- unless that would read a large lookup twice, where fewer
+        // rows with X in LDS are better.
+        uint64_t looked = 0;
+        for (const auto &t : vp.terms) looked += P.v[t.j].N * 8;
+        uint32_t lr = 0, threads = 256;
+        bool keep = z >= 0;
+        const uint32_t most = std::max(vp.K, Kz);
+        while (lr < 6 && ((rows >> lr) > 256 || (threads >> lr) > 2 * most) && fits(lr + 1, keep)) lr++;
+        if (z >= 0 && lr < 6 && (rows >> 6) > 256 && fits(6, false) && (looked <= (32ull << 20) || lr < kClassStagedRows)) {
+            lr = 6;
+            keep = false;
+        }
+        if (!fits(lr, keep)) return false;
+        if (lr == 6 && (rows >> 6) > 256) threads = 512;
+        vp.keep = keep;
+        vp.threads = threads;
+        vp.classes = true;
+        vp.lr = lr;
+        vp.z = z;
+        vp.O.clear();
+        vp.R = R;
+        vp.MO = 1;
+        vp.MR = rows;
+        vp.TZ = 0;
+        vp.TM = 1u << lr;
+        vp.nsplit = 1;
+        vp.cper = vp.K;
+        vp.parts = 0;
+        vp.layout.clear();
+        if (z >= 0) vp.layout.push_back(z);
+        vp.layout.insert(vp.layout.end(), R.begin(), R.end());
+        vp.stride.assign(vp.layout.size(), 1);
+        for (int k = (int)vp.layout.size() - 2; k >= 0; k--) vp.stride[k] = vp.stride[k + 1] * g->K[vp.layout[k + 1]];
+        // the table's stores, or the X evaluations
+        vp.est_us = 5.0 + std::max((double)vp.N * 10 / 3.5e6,
+                                   (double)rows * vp.K * (4.0 + 6.0 * (double)(vp.edges.size() + vp.terms.size())) / 1e7);
+        return true;
+    };
     auto plan_one = [&](int i, uint32_t ftz, uint32_t ftm, bool no_split) {
         VPlan &vp = P.v[i];
+        vp.classes = false;
         const uint32_t tile_cols = ftz ? ftz : g->tile_cols, tile_rows = ftm ? ftm : g->tile_rows;
         // small vertices: the direct fill (one launch, no prep blocks), whose
         // time is a launch plus the gather of every term of every cell
         if (!ftz && g->direct_cells && kernel_mode == 0 && vp.N * vp.K <= g->direct_cells && (g->schedule == kSchedSeq || level_small[vp.level])) {
             vp.kernel = kDirect;
+            if (plan_class(i, true)) return;
             vp.est_us = 4.0 + (double)vp.N * vp.K * (1.0 + vp.edges.size() + vp.terms.size()) / 4e5;
             vp.layout = gather_layout(vp);
             vp.nsplit = 1;
@@ -642,6 +729,13 @@ static pase_status build_plan(pase_graph_t g) {
             vp.stride.assign(vp.layout.size(), 1);
             for (int k = (int)vp.layout.size() - 2; k >= 0; k--)
                 vp.stride[k] = vp.stride[k + 1] * g->K[vp.layout[k + 1]];
+            return;
+        }
+        // (a small vertex of a level that is not all small: the class kernel
+        // still needs no prep launch)
+        const bool small = g->direct_cells && vp.N * vp.K <= g->direct_cells;
+        if (!ftz && kernel_mode == 0 && plan_class(i, small)) {
+            vp.kernel = small ? kDirect : kRows;
             return;
         }
         RowsChoice best;
@@ -776,6 +870,19 @@ static pase_status build_plan(pase_graph_t g) {
             // (split chains: only the batched levels share launches level-wide)
             if (g->schedule == kSchedSplit && P.v[i].level >= kSplitBatchedLevels) continue;
             const VPlan &dv = P.v[d];
+            if (P.v[i].classes || dv.classes) {
+                // class fills of a batched level share one launch, and with it
+                // the largest one's rows per workgroup and use of LDS
+                VPlan &ci = P.v[i];
+                if (ci.classes && dv.classes && ci.z >= 0 &&
+                    class_lds(ci.K, g->K[ci.z], (uint32_t)ci.edges.size() - 1, (uint32_t)ci.terms.size(), dv.lr, true,
+                              dv.keep, 512) <= kClassMaxLds) {
+                    ci.lr = dv.lr;
+                    ci.keep = dv.keep;
+                    ci.TM = dv.TM;
+                }
+                continue;
+            }
             const bool unsplit = dv.nsplit == 1 && !g->c_splits;
             if (P.v[i].TZ == dv.TZ && P.v[i].TM == dv.TM && (!unsplit || P.v[i].nsplit == 1)) continue;
             const VPlan saved = P.v[i];
@@ -787,7 +894,7 @@ static pase_status build_plan(pase_graph_t g) {
         }
     }
     for (const auto &vp : P.v) {
-        if (vp.kernel != kRows) continue;
+        if (vp.kernel != kRows || vp.classes) continue;
         P.rows_vertices++;
         P.rows_cells += vp.N * vp.K;
         if (vp.z < 0) P.stream_cells += vp.N * vp.K;
@@ -796,6 +903,42 @@ static pase_status build_plan(pase_graph_t g) {
     if (g->schedule == kSchedBulk) assign_bulk_lanes(P, (double)g->bulk_us);
     if (g->schedule == kSchedSplit) assign_split_lanes(P, (double)g->bulk_us);
     if (g->fuse_min && kernel_mode == 0) fuse_minima(g, P);
+    // class tables, one per distinct edge shape (v_i's end, the other end)
+    P.overridden = g->overridden;
+    for (auto &vp : P.v) {
+        if (!vp.classes) continue;
+        P.class_fills++;
+        if (vp.z < 0) continue;
+        for (int e : vp.edges) {
+            const auto &d = g->E[e];
+            const bool is_src = (int)d.src == vp.vi;
+            if ((is_src ? (int)d.dst : (int)d.src) != vp.z) continue;
+            DevClassTab t;
+            std::memset(&t, 0, sizeof t);
+            t.K = vp.K;
+            t.Kz = g->K[vp.z];
+            t.ndu = g->V[vp.vi].ndims;
+            t.ndz = g->V[vp.z].ndims;
+            t.rank = d.rank;
+            t.factors = g->factors ? 1 : 0;
+            for (uint32_t k = 0; k < kMaxDims; k++) {
+                t.udim[k] = (int8_t)(k < d.rank ? (is_src ? d.src_dim[k] : d.dst_dim[k]) : -1);
+                t.zdim[k] = (int8_t)(k < d.rank ? (is_src ? d.dst_dim[k] : d.src_dim[k]) : -1);
+            }
+            for (size_t k = 0; k < P.ctabs.size() && vp.ctab < 0; k++) {
+                const DevClassTab &o = P.ctabs[k];
+                if (o.ndu == t.ndu && o.ndz == t.ndz && o.rank == t.rank &&
+                    !std::memcmp(o.udim, t.udim, sizeof t.udim) && !std::memcmp(o.zdim, t.zdim, sizeof t.zdim))
+                    vp.ctab = (int)k;
+            }
+            if (vp.ctab < 0) {
+                t.blk0 = P.ctab_blocks;
+                P.ctab_blocks += (t.K + t.Kz + 256 / kClassTabLanes - 1) / (256 / kClassTabLanes);
+                vp.ctab = (int)P.ctabs.size();
+                P.ctabs.push_back(t);
+            }
+        }
+    }
     g->stats.plan_ms = ms_since(t1);
     return PASE_OK;
 }
@@ -873,9 +1016,11 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
     off = align_up(off + n * sizeof(BacktrackDesc), A);
     P.off_desc = off;
     off = align_up(off + n * (sizeof(PrepArgs) + sizeof(RowsArgs) + sizeof(GenericArgs) + sizeof(ReduceArgs) +
-                              sizeof(DirectArgs)), A);
+                              sizeof(DirectArgs) + sizeof(ClassArgs)), A);
     P.off_batch = off;
     off = align_up(off + 3 * (uint64_t)n * sizeof(BatchEntry), A);
+    P.off_ctdesc = off;
+    off = align_up(off + P.ctabs.size() * sizeof(DevClassTab), A);
     // one zero key: the row term that pads a row-kernel vertex up to the
     // row-term count of the launch it shares (uploaded zeroed with the rest)
     P.off_zero = off;
@@ -888,6 +1033,20 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
     // they sit past the uploaded constant region
     P.off_vmat = off;
     if (g->volume && !g->overridden) off = align_up(off + g->mat_total * 8, A);
+
+    // class fills: key-space costs and class tables, written on the device
+    P.off_Lk = P.off_fk = P.off_ctab = off;
+    if (P.class_fills) {
+        P.off_fk = off = align_up(off + sumK * 8, A);
+        P.off_ctab = off = align_up(off + P.sig_count * 8, A);
+        for (auto &t : P.ctabs) {
+            t.inv_off = off;
+            off = align_up(off + t.K * 2, 16);
+            t.zs_off = off;
+            off = align_up(off + t.Kz * sizeof(ClassEntry), 16);
+        }
+        off = align_up(off, A);
+    }
 
     // T arena: interval packing over launch slots -- a table is written in the
     // slot of its vertex and last read in the slot of its reader
@@ -933,7 +1092,9 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
     std::vector<VPlan *> hoisted;
     for (auto &vp : P.v) {
         uint64_t e = 0, pb = 0;
-        if (vp.kernel == kRows) {
+        if (vp.classes) {
+            // no blocks
+        } else if (vp.kernel == kRows) {
             e += align_up(vp.MO * vp.K * vp.ldz, 32);
             for (int u : vp.R) e += align_up((uint64_t)vp.K * g->K[u], 32);
             if (vp.nsplit > 1) pb = align_up((uint64_t)vp.nsplit * vp.N * kb, A);
@@ -990,7 +1151,9 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
 // passes 64 bits.
 static pase_status plan_search(pase_graph_t g, bool replan) {
     pase_status st;
-    if (replan && (st = build_plan(g)) != PASE_OK) return st;
+    // (a plan with class fills reads the model's own costs: caller-given ones
+    // need the dense fills, and the other way round)
+    if ((replan || g->plan.overridden != g->overridden) && (st = build_plan(g)) != PASE_OK) return st;
     const uint32_t kt = choose_key_type(g, &st);
     if (st != PASE_OK) return fail(g, st, "a cost bound of the recurrence exceeds 64 bits");
     if ((kt == 2) != g->plan_wide) {

@@ -24,6 +24,9 @@ constexpr int kMaxDep = PASE_MAX_DEP;
 constexpr int kMaxATerms = 4;      // per-lane row terms of the row kernel
 constexpr int kMaxGTerms = 24;     // terms of the generic kernel
 constexpr int kMaxContrib = 64;    // contributions to one precomputed block
+constexpr uint64_t kHoistElems = 1ull << 20;   // PASE_OPT_HOIST_ELEMS default
+constexpr int kMaxClassEdges = 4;  // rest-digit edges of the class fill
+constexpr int kMaxClassTerms = 4;  // lookups of the class fill
 constexpr int kMaxBlocks = kMaxDep + 1;
 constexpr uint64_t kMaxTableEntries = (1ull << 31) - 1;
 constexpr uint32_t kAssignMaxDevices = 1024;   // p bound of the device assignment
@@ -44,6 +47,7 @@ struct DevVertex {            // configuration data of one vertex (uploaded once
     uint32_t input_mask;      // halo term: loop dims indexing the input tensor
     uint32_t halo_w[kMaxDims];   // halo width per loop dim
     uint64_t halo_n[kMaxDims];   // halo term: prod of the input dims' sizes other than this one
+    uint32_t bits, pad;       // argmin bits of its keys (cost << bits | configuration)
 };
 
 struct DevEdge {
@@ -54,6 +58,23 @@ struct DevEdge {
     uint64_t sig_off;         // element offset of its split signatures: K_src, then K_dst
     uint64_t mat_off;         // volume transfer model: element offset of its K_src x K_dst matrix
     uint64_t row0;            // volume transfer model: its first matrix row among all edges' rows
+    uint32_t bits, pad;       // argmin bits of the end that is eliminated first: the keys its cost enters
+};
+
+// Class table of an edge shape (the class fill below): the configurations of
+// the eliminated end u (K of them) and of the other end z (Kz), grouped by
+// equal split signatures.  Written on the device by k_cost_tables.
+struct DevClassTab {
+    uint64_t ex_u, ex_z;      // byte offsets of the two ends' split rows
+    uint64_t inv_off;         // byte offset of inv: uint16[K], configuration c's place when sorted by class
+    uint64_t zs_off;          // byte offset of zs: ClassEntry[Kz], the other end's configurations sorted by class
+    uint32_t K, Kz, ndu, ndz, rank, factors, blk0, pad;
+    int8_t udim[kMaxDims], zdim[kMaxDims];
+};
+
+struct ClassEntry {           // one configuration z of the other end
+    uint16_t first, count;    // its class's configurations of u: places [first, first + count) of the sorted order
+    uint32_t z;
 };
 
 // One contribution to a precomputed block element (see Prep below).
@@ -184,6 +205,61 @@ struct DirectArgs {
     uint16_t *A;
 };
 
+// Class fill.  With the split match model an edge's cost is
+//     r * t_x(c, z) = 0 if c and z split the tensor alike (one class), else min(f(c), f(z)),
+//     f(x) = r * ceil(elems / P_x)
+// (the larger device count gives the smaller cost), and 0 <= f, so for a digit
+// z that meets v_i in this one edge and in no lookup, with X[c][rest] the sum
+// of all other terms,
+//     min_c X[c] + t_x(c, z) = min( min_{c in class of z} X[c],  f(z) + min_c X[c],  min_c (X[c] + f(c)) ):
+// K * rest evaluations of X and about two minima per table entry instead of K
+// adds and minima per entry.  Every term on the right is a key of a
+// configuration or an upper bound of one, so minimum and argmin are those of
+// the left.  Without such a digit (has_z = 0) the fill is the minimum over c
+// of X itself.
+struct ClassEdge {            // an edge to a rest digit
+    const uint64_t *sig_c, *sig_o;   // split signatures by c, by the other end's configuration
+    const void *f_c, *f_o;           // f of the two ends, key space
+    uint32_t dig, pad;               // rest digit of the other end
+};
+
+struct ClassTerm {            // a lookup T_j (key space)
+    const void *ptr;
+    uint32_t sc, pad;         // element stride of c
+    uint32_t sd[kMaxDep];     // element strides of the rest digits
+};
+
+struct ClassArgs {
+    const void *Lk;           // key-space layer costs: (cost << bits) + c
+    const uint16_t *inv;      // class table of the edge to z
+    const ClassEntry *zs;
+    const void *fzc, *fzo;    // f of that edge by c, by z
+    void *T;                  // index z * rows + row (without z: row)
+    uint16_t *A;
+    uint32_t K, Kz, bits, out_shift;
+    uint32_t rows, nR;        // rows = product of the rest radices (slowest first)
+    uint32_t rad[kMaxDep];
+    uint32_t lr, has_z;       // a workgroup takes 2^lr rows
+    uint32_t staged;          // many rows: per-configuration data staged through LDS
+    uint32_t keep;            // staged: 1: X of all K configurations and rows in LDS; 0: lr = 6 and X formed twice
+    uint32_t ne, nt, nblk, lds;   // lds: bytes of dynamic LDS
+    ClassEdge e[kMaxClassEdges];
+    ClassTerm t[kMaxClassTerms];
+};
+
+constexpr uint32_t kClassMaxK = 4096;         // configurations of either end of the class edge
+constexpr uint32_t kClassMaxLds = 64 << 10;   // two workgroups per CU (160 KB) with room beside them
+constexpr uint32_t kClassTabLanes = 16;       // threads per configuration of the class tables' counting
+constexpr uint32_t kClassStagedRows = 4;      // log2 of the rows per workgroup from which data is staged
+// dynamic LDS of one workgroup: per-wave minima and X; staged: also the per-configuration records, the
+// class entries and the configurations of the lookups
+inline uint64_t class_lds(uint64_t K, uint64_t Kz, uint32_t ne, uint32_t nt, uint32_t lr, bool has_z, bool keep,
+                          uint32_t threads) {
+    const uint64_t red = (threads / 64) * (16ull << (lr < 6 ? lr : 6)), x = keep ? (K << lr) * 8 : 0;
+    if (lr < kClassStagedRows) return red + x;
+    return red + x + K * (16 + 16 * ne + (nt ? 4 : 0)) + (has_z ? Kz * 16 : 0);
+}
+
 struct ReduceArgs {
     const void *partial;
     void *T;
@@ -235,6 +311,13 @@ struct VPlan {
     KernelKind kernel = kGeneric;
     // row kernel shape
     int z = -1;                     // column digit (vertex id)
+    // class fill (kernel kRows or kDirect): z is then the class digit (-1: none), R the rest
+    // digits, and every term is read from its source array (no prep blocks)
+    bool classes = false;
+    uint32_t lr = 0;                // log2 of the rows per workgroup
+    bool keep = false;              // X kept in LDS
+    uint32_t threads = 256;         // workgroup size
+    int ctab = -1;                  // its class table
     std::vector<int> O, R;          // outer / row digits (vertex ids), slowest first
     uint32_t TZ = 0, TM = 1, ldz = 0, nchunks = 0, nsplit = 1, cper = 0, parts = 1;
     uint64_t MO = 1, MR = 1;
@@ -283,6 +366,12 @@ struct Plan {
     bool by_level = false;          // the vertices of one dependency level share launches
     bool resident = false;          // every table and scratch buffer resident at once (no reuse)
     uint64_t off_desc = 0, off_batch = 0;   // per-vertex launch descriptors, batch tables
+    // class fills: tables per edge shape (byte offsets relative to off_ctab until layout) and the
+    // key-space layer costs and edge f values, all written by k_cost_tables
+    std::vector<DevClassTab> ctabs;
+    uint32_t class_fills = 0, ctab_blocks = 0;
+    uint64_t off_ctdesc = 0, off_ctab = 0, off_Lk = 0, off_fk = 0;
+    bool overridden = false;        // planned for caller-given costs
 };
 
 struct DeviceState;   // defined by the device runtime
@@ -317,7 +406,7 @@ struct pase_graph_s {
     uint64_t direct_cells = 1ull << 18;  // pase_option PASE_OPT_DIRECT_CELLS
     uint32_t bulk_us = 100;         // pase_option PASE_OPT_BULK_US
     bool fuse_min = true;           // pase_option PASE_OPT_FUSED_MIN
-    uint64_t hoist_elems = 1ull << 20;   // pase_option PASE_OPT_HOIST_ELEMS (0 = never)
+    uint64_t hoist_elems = pase::kHoistElems;   // pase_option PASE_OPT_HOIST_ELEMS (0 = never)
     std::vector<uint64_t> weight_n; // gradient term of the enumeration: weight words per vertex (0 = none)
     bool volume = false;            // the enumerated transfer model is the volume intersection
     std::vector<uint64_t> mat_off;  // volume model: element offset of each edge's cost matrix

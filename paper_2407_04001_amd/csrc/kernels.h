@@ -823,4 +823,404 @@ __device__ __forceinline__ void direct_item(const DirectArgs &a, uint32_t lb, co
     }
 }
 
+// ------------------------------------------------------------------ class fill
+// Pointers read from a descriptor are generic to the compiler, which then
+// issues flat loads (they also count as LDS operations and wait for them);
+// these name global memory.
+template <typename T> using Glb = __attribute__((address_space(1))) T *;
+template <typename T> __device__ __forceinline__ Glb<const T> glb(const void *p) { return (Glb<const T>)(uintptr_t)p; }
+
+// Class table of one edge shape: every configuration's place in the order of
+// (signature, index) and, per configuration of the other end, the range of
+// u's configurations with its signature, by counting: kClassTabLanes threads
+// per configuration, each against its share of all signatures (staged through
+// LDS).  A share of 1/16 keeps the loop at 58 of the Transformer's 924
+// signatures per edge (one thread per configuration took 53 us).
+constexpr uint32_t kClassTabTile = 1024;
+__device__ __forceinline__ void class_table_item(const DevClassTab &t, uint32_t lb, const uint8_t *__restrict__ ex,
+                                                 char *__restrict__ ws, uint64_t (&buf)[kClassTabTile]) {
+    const uint32_t n = t.K + t.Kz, sub = threadIdx.x % kClassTabLanes;
+    const uint32_t e = lb * (256 / kClassTabLanes) + threadIdx.x / kClassTabLanes;
+    auto sig_of = [&](uint32_t i) {
+        return i < t.K ? split_signature(t.udim, t.rank, ex + t.ex_u + (uint64_t)i * t.ndu, t.factors)
+                       : split_signature(t.zdim, t.rank, ex + t.ex_z + (uint64_t)(i - t.K) * t.ndz, t.factors);
+    };
+    const uint64_t me = e < n ? sig_of(e) : 0;
+    uint32_t ulow = 0, ueq = 0, ueqb = 0, zlow = 0, zeqb = 0;   // smaller, equal, equal and before, per end
+    for (uint32_t base = 0; base < n; base += kClassTabTile) {
+        __syncthreads();
+        for (uint32_t i = threadIdx.x; i < kClassTabTile && base + i < n; i += 256) buf[i] = sig_of(base + i);
+        __syncthreads();
+        for (uint32_t j = sub; j < kClassTabTile && base + j < n; j += kClassTabLanes) {
+            const uint64_t s = buf[j];
+            const bool lt = s < me, eq = s == me, before = eq && base + j < e, u = base + j < t.K;
+            ulow += lt && u;
+            ueq += eq && u;
+            ueqb += before && u;
+            zlow += lt && !u;
+            zeqb += before && !u;
+        }
+    }
+    for (uint32_t m = kClassTabLanes / 2; m > 0; m >>= 1) {
+        ulow += __shfl_xor(ulow, m, 64);
+        ueq += __shfl_xor(ueq, m, 64);
+        ueqb += __shfl_xor(ueqb, m, 64);
+        zlow += __shfl_xor(zlow, m, 64);
+        zeqb += __shfl_xor(zeqb, m, 64);
+    }
+    if (sub) return;
+    if (e < t.K) ((uint16_t *)(ws + t.inv_off))[e] = (uint16_t)(ulow + ueqb);
+    else if (e < n)
+        ((ClassEntry *)(ws + t.zs_off))[zlow + zeqb] = ClassEntry{(uint16_t)ulow, (uint16_t)ueq, e - t.K};
+}
+
+// Workgroup lb of one vertex's class fill: 2^lr rows (the fastest bits of the
+// thread index) x blockDim >> lr groups of lanes.
+//
+// Few rows (class_item_small): every configuration's data is read by one group
+// only, so each thread loads it where it needs it; LDS holds X alone (a few
+// KB, so the workgroup fits beside those of a large fill on another stream).
+// All loads of a thread are independent (U configurations and entries in
+// flight): about three memory round trips in all.
+template <typename KeyT, int NE, int NT>
+__device__ __forceinline__ void class_item_small(const ClassArgs &a, uint32_t lb, char *lds) {
+    using Ops = KeyOps<KeyT>;
+    using Val = typename Ops::Val;
+    constexpr int ME = NE > 0 ? NE : 1, MT = NT > 0 ? NT : 1;
+    constexpr int U = 4;
+    const uint32_t threads = blockDim.x, lr = a.lr, R = 1u << lr, G = threads >> lr, K = a.K, Kz = a.Kz;
+    const bool has_z = a.has_z;
+    const uint32_t rl = threadIdx.x & (R - 1), g = threadIdx.x >> lr;
+    const uint32_t row = lb * R + rl, rows = a.rows, bits = a.bits, out_shift = a.out_shift;
+    const bool live = row < rows;
+    KeyT *red = (KeyT *)lds;                            // [waves][R][2]
+    KeyT *X = red + (threads / 64) * R * 2;             // [K][R]
+    const Glb<Val> T = (Glb<Val>)(uintptr_t)a.T;
+    const Glb<uint16_t> A = (Glb<uint16_t>)(uintptr_t)a.A;
+    const Glb<const KeyT> Lk = glb<KeyT>(a.Lk), fzc = glb<KeyT>(a.fzc), fzo = glb<KeyT>(a.fzo);
+    const Glb<const uint16_t> inv = glb<uint16_t>(a.inv);
+    const Glb<const uint64_t> zs = glb<uint64_t>(a.zs);   // ClassEntry: first, count, z
+
+    uint32_t d[kMaxDep];
+    {
+        uint32_t x = live ? row : rows - 1;
+        for (int k = kMaxDep - 1; k >= 0; k--)
+            if (k < (int)a.nR) {
+                d[k] = k ? x % a.rad[k] : x;
+                if (k) x /= a.rad[k];
+            } else d[k] = 0;
+    }
+    uint64_t so[ME];
+    KeyT fo[ME];
+    Glb<const uint64_t> sc[ME];
+    Glb<const KeyT> fc[ME];
+    Glb<const Val> tp[MT];
+    uint32_t tsc[MT];
+#pragma unroll
+    for (int t = 0; t < NE; t++) {
+        uint32_t w = 0;
+        for (int k = 0; k < kMaxDep; k++) w = k == (int)a.e[t].dig ? d[k] : w;
+        so[t] = glb<uint64_t>(a.e[t].sig_o)[w];
+        fo[t] = glb<KeyT>(a.e[t].f_o)[w];
+        sc[t] = glb<uint64_t>(a.e[t].sig_c);
+        fc[t] = glb<KeyT>(a.e[t].f_c);
+    }
+#pragma unroll
+    for (int t = 0; t < NT; t++) {
+        uint32_t o = 0;
+        for (int k = 0; k < kMaxDep; k++)
+            if (k < (int)a.nR) o += d[k] * a.t[t].sd[k];
+        tp[t] = glb<Val>(a.t[t].ptr) + o;
+        tsc[t] = a.t[t].sc;
+    }
+    // the first entries of z of this group, requested ahead of the barrier
+    uint64_t w[U];
+    KeyT fz[U];
+    if (has_z) {
+#pragma unroll
+        for (int u = 0; u < U; u++) w[u] = zs[min(g + u * G, Kz - 1)];
+    }
+    KeyT m0 = Ops::sentinel(), m1 = Ops::sentinel();
+    for (uint32_t c0 = g; c0 < K; c0 += U * G) {
+        KeyT x[U], f[U], ef[U][ME], tv[U][MT];
+        uint64_t es[U][ME];
+        uint32_t at[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            // (past the end: the last configuration once more, the same minima and store)
+            const uint32_t c = min(c0 + u * G, K - 1);
+            x[u] = Lk[c];
+            if (has_z) {
+                at[u] = inv[c];
+                f[u] = fzc[c];
+            }
+#pragma unroll
+            for (int t = 0; t < NE; t++) {
+                es[u][t] = sc[t][c];
+                ef[u][t] = fc[t][c];
+            }
+#pragma unroll
+            for (int t = 0; t < NT; t++) tv[u][t] = __builtin_bit_cast(KeyT, tp[t][(uint64_t)c * tsc[t]]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+#pragma unroll
+            for (int t = 0; t < NE; t++)
+                x[u] = Ops::add(x[u], es[u][t] == so[t] ? (KeyT)0 : Ops::min(ef[u][t], fo[t]));
+#pragma unroll
+            for (int t = 0; t < NT; t++) x[u] = Ops::add(x[u], tv[u][t]);
+            m0 = Ops::min(m0, x[u]);
+            if (has_z) {
+                m1 = Ops::min(m1, Ops::add(x[u], f[u]));
+                X[(at[u] << lr) + rl] = x[u];
+            }
+        }
+    }
+    if (has_z) {
+#pragma unroll
+        for (int u = 0; u < U; u++) fz[u] = fzo[w[u] >> 32];
+    }
+    for (uint32_t m = R; m < 64; m <<= 1) {
+        m0 = Ops::min(m0, shfl_xor_key(m0, (int)m));
+        m1 = Ops::min(m1, shfl_xor_key(m1, (int)m));
+    }
+    const uint32_t RW = min(R, 64u), wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (lane < RW) {
+        red[(wave * RW + lane) * 2] = m0;
+        red[(wave * RW + lane) * 2 + 1] = m1;
+    }
+    __syncthreads();
+    for (uint32_t v = 0; v < threads / 64; v++) {
+        m0 = Ops::min(m0, red[(v * RW + rl) * 2]);
+        m1 = Ops::min(m1, red[(v * RW + rl) * 2 + 1]);
+    }
+    if (!live) return;
+    auto put = [&](uint64_t idx, KeyT key) {
+        Val v;
+        uint32_t cc;
+        Ops::split(key, bits, out_shift, v, cc);
+        T[idx] = v;
+        A[idx] = (uint16_t)cc;
+    };
+    if (!has_z) {
+        if (g == 0) put(row, m0);
+        return;
+    }
+    for (uint32_t q0 = g; q0 < Kz; q0 += U * G) {
+        if (q0 != g) {
+#pragma unroll
+            for (int u = 0; u < U; u++) w[u] = zs[min(q0 + u * G, Kz - 1)];
+#pragma unroll
+            for (int u = 0; u < U; u++) fz[u] = fzo[w[u] >> 32];
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            if (q0 + u * G >= Kz) break;
+            const uint32_t first = (uint32_t)w[u] & 0xffff, count = (uint32_t)w[u] >> 16;
+            KeyT best = Ops::min(m1, Ops::add(m0, fz[u]));
+            for (uint32_t k = 0; k < count; k++) best = Ops::min(best, X[((first + k) << lr) + rl]);
+            put((w[u] >> 32) * rows + row, best);
+        }
+    }
+}
+
+// Many rows (class_item_staged): first the workgroup brings the per-configuration data (layer cost, f, the
+// rest edges' signatures and f) into LDS in class order, and the class entries
+// of z: both are read many times, by all rows, and the class order makes every
+// later index a sequential one.  Then the groups share the configurations c:
+// X[c][row] is formed for its two minima, min X and min (X + f(c)), and kept
+// in LDS when `keep`.  After these are combined (lane swaps, LDS) the groups
+// share the configurations z in class order: a table entry is the minimum of
+// its class's X values and of the two minima.  When X of all K configurations
+// does not fit (keep = 0; 64 rows, one wave per group) each class's X values are
+// formed again: one more evaluation per (c, row), against Kz / K table entries.
+// Bound by the stores of its table (10 bytes per entry).
+//
+// Measured on the Transformer at p = 64: its 36 leaves, four of them 8.3e9
+// cells, 2.05 ms dense (94% of the fp64 issue rate) and 0.24 ms here (3 TB/s of
+// stores); one level of its encoder chain 20 us (prep, row fill, split
+// reduction) and 6 us.  With the data read from global memory by every group
+// instead of staged, the leaves took 0.57 ms (vector loads of data that whole
+// waves share).
+template <typename KeyT, int NE, int NT>
+__device__ __forceinline__ void class_item_staged(const ClassArgs &a, uint32_t lb, char *lds) {
+    using Ops = KeyOps<KeyT>;
+    using Val = typename Ops::Val;
+    constexpr int ME = NE > 0 ? NE : 1, MT = NT > 0 ? NT : 1;
+    constexpr int U = 4;
+    struct alignas(16) Rec { KeyT x, f; };              // layer cost and f of a configuration (edge: signature and f)
+    struct alignas(16) EdgeRec { uint64_t sig; KeyT f; };
+    struct alignas(16) ZRec { uint32_t place, z; KeyT f; };   // place: first | count << 16
+    const uint32_t threads = blockDim.x, lr = a.lr, R = 1u << lr, G = threads >> lr, K = a.K, Kz = a.Kz;
+    const bool has_z = a.has_z, keep = a.keep;
+    const uint32_t rl = threadIdx.x & (R - 1);
+    uint32_t g = threadIdx.x >> lr;
+    const uint32_t row = lb * R + rl;
+    const bool live = row < a.rows;
+    Rec *rec = (Rec *)lds;                              // [K]
+    EdgeRec *erec = (EdgeRec *)(rec + K);               // [NE][K]
+    ZRec *zs = (ZRec *)(erec + NE * K);                 // [Kz]
+    KeyT *red = (KeyT *)(zs + (has_z ? Kz : 0));        // [waves][min(R, 64)][2]
+    const uint32_t RW = min(R, 64u);
+    KeyT *X = red + (threads / 64) * RW * 2;            // [K][R] when keep
+    uint32_t *cs = (uint32_t *)(X + (keep ? K << lr : 0));   // [K] configurations in class order (lookups)
+
+    for (uint32_t c = threadIdx.x; c < K; c += threads) {
+        const uint32_t at = has_z ? glb<uint16_t>(a.inv)[c] : c;
+        Rec r;
+        r.x = glb<KeyT>(a.Lk)[c];
+        r.f = has_z ? glb<KeyT>(a.fzc)[c] : (KeyT)0;
+        EdgeRec er[ME];
+#pragma unroll
+        for (int t = 0; t < NE; t++) {
+            er[t].sig = glb<uint64_t>(a.e[t].sig_c)[c];
+            er[t].f = glb<KeyT>(a.e[t].f_c)[c];
+        }
+        rec[at] = r;
+#pragma unroll
+        for (int t = 0; t < NE; t++) erec[t * K + at] = er[t];
+        if (NT > 0) cs[at] = c;
+    }
+    if (has_z)
+        for (uint32_t q = threadIdx.x; q < Kz; q += threads) {
+            const uint64_t w = glb<uint64_t>(a.zs)[q];   // ClassEntry: first, count, z
+            ZRec r;
+            r.place = (uint32_t)w;
+            r.z = (uint32_t)(w >> 32);
+            r.f = glb<KeyT>(a.fzo)[r.z];
+            zs[q] = r;
+        }
+    uint32_t d[kMaxDep];
+    {
+        uint32_t x = live ? row : a.rows - 1;
+        for (int k = kMaxDep - 1; k >= 0; k--)
+            if (k < (int)a.nR) {
+                d[k] = k ? x % a.rad[k] : x;
+                if (k) x /= a.rad[k];
+            } else d[k] = 0;
+    }
+    uint64_t so[ME];
+    KeyT fo[ME];
+    Glb<const Val> tp[MT];
+    uint32_t tsc[MT];
+#pragma unroll
+    for (int t = 0; t < NE; t++) {
+        uint32_t w = 0;
+        for (int k = 0; k < kMaxDep; k++) w = k == (int)a.e[t].dig ? d[k] : w;
+        so[t] = glb<uint64_t>(a.e[t].sig_o)[w];
+        fo[t] = glb<KeyT>(a.e[t].f_o)[w];
+    }
+#pragma unroll
+    for (int t = 0; t < NT; t++) {
+        uint32_t o = 0;
+        for (int k = 0; k < kMaxDep; k++)
+            if (k < (int)a.nR) o += d[k] * a.t[t].sd[k];
+        tp[t] = glb<Val>(a.t[t].ptr) + o;
+        tsc[t] = a.t[t].sc;
+    }
+    const uint32_t bits = a.bits, out_shift = a.out_shift, rows = a.rows;
+    const Glb<Val> T = (Glb<Val>)(uintptr_t)a.T;
+    const Glb<uint16_t> A = (Glb<uint16_t>)(uintptr_t)a.A;
+    __syncthreads();
+    if (!keep && has_z) g = __builtin_amdgcn_readfirstlane(g);   // (64 rows: a group is a wave)
+
+    // X of the configuration at place p: its terms, then their sum
+    struct Terms { Rec r; EdgeRec e[ME]; KeyT t[MT]; };
+    auto fetch = [&](uint32_t p) {
+        Terms v;
+        if (NT > 0) {
+            const uint32_t c = cs[p];
+#pragma unroll
+            for (int t = 0; t < NT; t++) v.t[t] = __builtin_bit_cast(KeyT, tp[t][(uint64_t)c * tsc[t]]);
+        }
+        v.r = rec[p];
+#pragma unroll
+        for (int t = 0; t < NE; t++) v.e[t] = erec[t * K + p];
+        return v;
+    };
+    auto sum = [&](const Terms &v) {
+        KeyT x = v.r.x;
+#pragma unroll
+        for (int t = 0; t < NE; t++) x = Ops::add(x, v.e[t].sig == so[t] ? (KeyT)0 : Ops::min(v.e[t].f, fo[t]));
+#pragma unroll
+        for (int t = 0; t < NT; t++) x = Ops::add(x, v.t[t]);
+        return x;
+    };
+    KeyT m0 = Ops::sentinel(), m1 = Ops::sentinel();
+    for (uint32_t p0 = g; p0 < K; p0 += U * G) {
+        Terms v[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) v[u] = fetch(min(p0 + u * G, K - 1));
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            // (past the end: the last configuration once more, the same minima and store)
+            const uint32_t p = min(p0 + u * G, K - 1);
+            const KeyT x = sum(v[u]);
+            m0 = Ops::min(m0, x);
+            m1 = Ops::min(m1, Ops::add(x, v[u].r.f));
+            if (keep) X[(p << lr) + rl] = x;
+        }
+    }
+    for (uint32_t m = R; m < 64; m <<= 1) {
+        m0 = Ops::min(m0, shfl_xor_key(m0, (int)m));
+        m1 = Ops::min(m1, shfl_xor_key(m1, (int)m));
+    }
+    const uint32_t wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    if (lane < RW) {
+        red[(wave * RW + lane) * 2] = m0;
+        red[(wave * RW + lane) * 2 + 1] = m1;
+    }
+    __syncthreads();
+    for (uint32_t w = 0; w < threads / 64; w++) {
+        m0 = Ops::min(m0, red[(w * RW + rl) * 2]);
+        m1 = Ops::min(m1, red[(w * RW + rl) * 2 + 1]);
+    }
+    if (!live) return;
+    auto put = [&](uint64_t idx, KeyT key) {
+        Val v;
+        uint32_t cc;
+        Ops::split(key, bits, out_shift, v, cc);
+        T[idx] = v;
+        A[idx] = (uint16_t)cc;
+    };
+    if (!has_z) {
+        if (g == 0) put(row, m0);
+        return;
+    }
+    if (keep) {
+        for (uint32_t q = g; q < Kz; q += G) {
+            const ZRec r = zs[q];
+            const uint32_t first = r.place & 0xffff, count = r.place >> 16;
+            KeyT best = Ops::min(m1, Ops::add(m0, r.f));
+            for (uint32_t k = 0; k < count; k++) best = Ops::min(best, X[((first + k) << lr) + rl]);
+            put((uint64_t)r.z * rows + row, best);
+        }
+    } else {
+        const uint32_t per = (Kz + G - 1) / G, q1 = min(Kz, (g + 1) * per);
+        uint32_t last = ~0u;
+        KeyT s = Ops::sentinel();
+        for (uint32_t q = min(Kz, g * per); q < q1; q++) {
+            const ZRec r = zs[q];
+            const uint32_t place = __builtin_amdgcn_readfirstlane(r.place);
+            if (place != last) {
+                last = place;
+                s = Ops::sentinel();
+                for (uint32_t k = 0; k < place >> 16; k++) s = Ops::min(s, sum(fetch((place & 0xffff) + k)));
+            }
+            put((uint64_t)r.z * rows + row, Ops::min(s, Ops::min(m1, Ops::add(m0, r.f))));
+        }
+    }
+}
+
+template <typename KeyT, int NE, int NT>
+__device__ __forceinline__ void class_item(const ClassArgs &a, uint32_t b, char *lds) {
+    // blocks are dealt round-robin to the 8 XCDs (block counts and first blocks
+    // are multiples of 8): a contiguous range of rows per XCD, so that the
+    // lines two neighbouring workgroups share are completed in one L2
+    const uint32_t lb = (b % 8) * (a.nblk / 8) + b / 8;
+    if (lb >= (a.rows + (1u << a.lr) - 1) >> a.lr) return;   // the whole workgroup leaves together
+    if (a.staged) class_item_staged<KeyT, NE, NT>(a, lb, lds);
+    else class_item_small<KeyT, NE, NT>(a, lb, lds);
+}
+
 }  // namespace pase

@@ -50,6 +50,10 @@ pase_status build_launches(pase_graph_t g, char *ws, std::vector<Launch<KeyT>> &
     out.assign(n, Launch<KeyT>());
     contrib.clear();
     const uint64_t *ovedge = (const uint64_t *)(ws + P.off_ovedge);
+    // element offsets of every vertex's layer costs and every edge's signatures
+    std::vector<uint64_t> koff(g->V.size() + 1, 0), soff(g->E.size() + 1, 0);
+    for (size_t v = 0; v < g->V.size(); v++) koff[v + 1] = koff[v] + g->K[v];
+    for (size_t e = 0; e < g->E.size(); e++) soff[e + 1] = soff[e] + g->K[g->E[e].src] + g->K[g->E[e].dst];
     for (int i = 0; i < n; i++) {
         const VPlan &vp = P.v[i];
         Launch<KeyT> &L = out[i];
@@ -135,7 +139,77 @@ pase_status build_launches(pase_graph_t g, char *ws, std::vector<Launch<KeyT>> &
             L.prep.total += bk.elems;
             return (int)L.prep.nblocks++;
         };
-        if (vp.kernel == kDirect) {
+        if (vp.classes) {
+            if constexpr (sizeof(KeyT) != 8) {
+                return fail(g, PASE_ERR_INTERNAL, "class fill with 128-bit keys");
+            } else {
+                ClassArgs &ca = L.ca;
+                std::memset(&ca, 0, sizeof ca);
+                ca.Lk = (const KeyT *)(ws + P.off_Lk) + koff[vp.vi];
+                ca.K = vp.K;
+                ca.Kz = vp.z >= 0 ? g->K[vp.z] : 1;
+                ca.has_z = vp.z >= 0;
+                ca.bits = vp.bits;
+                ca.out_shift = vp.out_shift;
+                ca.rows = (uint32_t)vp.MR;
+                ca.nR = (uint32_t)vp.R.size();
+                for (size_t k = 0; k < vp.R.size(); k++) ca.rad[k] = g->K[vp.R[k]];
+                ca.lr = vp.lr;
+                ca.keep = vp.keep;
+                ca.staged = vp.lr >= kClassStagedRows;
+                ca.nblk = (uint32_t)((((vp.MR + (1u << vp.lr) - 1) >> vp.lr) + 7) / 8 * 8);
+                // the two ends' signatures and f arrays of an edge: v_i's, the other's
+                auto ends = [&](int e, uint64_t &oc, uint64_t &oo) {
+                    const bool is_src = (int)g->E[e].src == vp.vi;
+                    const uint64_t s0 = soff[e], d0 = s0 + g->K[g->E[e].src];
+                    oc = is_src ? s0 : d0;
+                    oo = is_src ? d0 : s0;
+                };
+                const uint64_t *sig = (const uint64_t *)(ws + P.off_sig);
+                const KeyT *fk = (const KeyT *)(ws + P.off_fk);
+                bool zdone = vp.z < 0;
+                for (int e : vp.edges) {
+                    uint64_t oc, oo;
+                    ends(e, oc, oo);
+                    if (other_of(e) == vp.z) {
+                        if (zdone || vp.ctab < 0) return fail(g, PASE_ERR_INTERNAL, "class edge");
+                        zdone = true;
+                        ca.fzc = fk + oc;
+                        ca.fzo = fk + oo;
+                        ca.inv = (const uint16_t *)(ws + P.ctabs[vp.ctab].inv_off);
+                        ca.zs = (const ClassEntry *)(ws + P.ctabs[vp.ctab].zs_off);
+                        continue;
+                    }
+                    if (ca.ne >= (uint32_t)kMaxClassEdges) return fail(g, PASE_ERR_INTERNAL, "class edges");
+                    ClassEdge &ce = ca.e[ca.ne++];
+                    ce.sig_c = sig + oc;
+                    ce.sig_o = sig + oo;
+                    ce.f_c = fk + oc;
+                    ce.f_o = fk + oo;
+                    ce.dig = (uint32_t)(std::find(vp.R.begin(), vp.R.end(), other_of(e)) - vp.R.begin());
+                    if (ce.dig >= ca.nR) return fail(g, PASE_ERR_INTERNAL, "class edge digit");
+                }
+                if (!zdone) return fail(g, PASE_ERR_INTERNAL, "class edge");
+                for (const auto &t : vp.terms) {
+                    if (ca.nt >= (uint32_t)kMaxClassTerms) return fail(g, PASE_ERR_INTERNAL, "class lookups");
+                    ClassTerm &ct = ca.t[ca.nt++];
+                    uint32_t sd[kMaxDep];
+                    lookup_strides(P, i, t.j, ct.sc, sd);
+                    if (max_index(vp.K, ct.sc, sd, rad, m) >= P.v[t.j].N) bounds_ok = false;
+                    if (vp.z >= 0 && sd[0]) return fail(g, PASE_ERR_INTERNAL, "class digit in a lookup");
+                    ct.ptr = ws + P.off_T + P.v[t.j].T_off;
+                    for (size_t k = 0; k < vp.R.size(); k++) ct.sd[k] = sd[(vp.z >= 0 ? 1 : 0) + k];
+                }
+                ca.T = ws + P.off_T + vp.T_off;
+                ca.A = (uint16_t *)(ws + P.off_A + vp.A_off);
+                // (the launch's workgroups may be larger than planned: at most 512 threads)
+                const uint64_t lds = class_lds(ca.K, ca.Kz, ca.ne, ca.nt, ca.lr, ca.has_z, ca.keep, 512);
+                if (lds > kClassMaxLds || (ca.has_z && !ca.keep && ca.lr != 6))
+                    return fail(g, PASE_ERR_INTERNAL, "class fill LDS");
+                ca.lds = (uint32_t)lds;
+                L.cls = true;
+            }
+        } else if (vp.kernel == kDirect) {
             // every term over all plan digits; no blocks
             DirectArgs &da = L.da;
             std::memset(&da, 0, sizeof da);
@@ -417,6 +491,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         x.ndims = g->V[v].ndims;
         x.reduce_mask = g->V[v].reduce_mask;
         x.factors = g->factors ? 1 : 0;
+        x.bits = P.v[P.pos[v]].bits;
         x.weight_n = g->weight_n[v];
         x.weight_mask = g->V[v].weight_mask;
         if (g->halo) {
@@ -446,6 +521,8 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
             x.ddim[k] = (int8_t)(k < x.rank ? g->E[e].dst_dim[k] : -1);
         }
         x.elems = g->E[e].elems;
+        // its cost enters the keys of the end that comes first in the sequence
+        x.bits = P.v[std::min(P.pos[x.src], P.pos[x.dst])].bits;
         x.sig_off = sig_off;
         x.mat_off = g->volume ? g->mat_off[e] : 0;
         x.row0 = g->volume ? g->mat_row0[e] : 0;
@@ -489,25 +566,37 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
 
     // ---- kernel descriptors: per position, one of each kind
     const uint64_t desc_bytes =
-        (uint64_t)n * (sizeof(PrepArgs) + sizeof(RowsArgs) + sizeof(GenericArgs) + sizeof(ReduceArgs) + sizeof(DirectArgs));
+        (uint64_t)n * (sizeof(PrepArgs) + sizeof(RowsArgs) + sizeof(GenericArgs) + sizeof(ReduceArgs) + sizeof(DirectArgs) +
+                      sizeof(ClassArgs));
     if ((st = region(P.off_desc, desc_bytes, P.off_batch, "descriptors")) != PASE_OK) return st;
     PrepArgs *hp = (PrepArgs *)(img + P.off_desc);
     RowsArgs *hr = (RowsArgs *)(hp + n);
     GenericArgs *hg = (GenericArgs *)(hr + n);
     ReduceArgs *hd = (ReduceArgs *)(hg + n);
     DirectArgs *hx = (DirectArgs *)(hd + n);
+    ClassArgs *hc = (ClassArgs *)(hx + n);
     for (int i = 0; i < n; i++) {
         hp[i] = launches[i].prep;
         hr[i] = launches[i].ra;
         hg[i] = launches[i].ga;
         hd[i] = launches[i].red;
         hx[i] = launches[i].da;
+        hc[i] = launches[i].ca;
+    }
+    if (!P.ctabs.empty()) {
+        if ((st = region(P.off_ctdesc, P.ctabs.size() * sizeof(DevClassTab), P.off_zero, "class tables")) != PASE_OK) return st;
+        DevClassTab *ht = (DevClassTab *)(img + P.off_ctdesc);
+        for (size_t k = 0; k < P.ctabs.size(); k++) {
+            ht[k] = P.ctabs[k];
+            ht[k].ex_u = row_off[ht[k].ndu];
+            ht[k].ex_z = row_off[ht[k].ndz];
+        }
     }
 
     // ---- batches: per launch group, one prep launch, one fill launch per
     // kernel variant and one split-reduction launch
     BatchEntry *hbe = (BatchEntry *)(img + P.off_batch);
-    const uint64_t be_cap = (P.off_zero - P.off_batch) / sizeof(BatchEntry);
+    const uint64_t be_cap = (P.off_ctdesc - P.off_batch) / sizeof(BatchEntry);
     uint32_t nbe = 0;
     // launch groups in enqueue order: the slots (levels, or positions); with
     // lanes, each slot's vertices of lane 0, then those of lane 1
@@ -521,8 +610,10 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
     auto add_batch = [&](Batch::Kind kind, uint32_t variant, const std::vector<int> &members,
                          uint32_t (*nblk)(const Launch<KeyT> &)) {
         if (members.empty()) return;
-        Batch b{kind, cur_lane, cur_group, variant, nbe, 0, 0, false};
+        Batch b{kind, cur_lane, cur_group, variant, nbe, 0, 0};
+        b.pos0 = (uint32_t)members[0];
         for (int i : members) {
+            if (kind == Batch::kClass) b.lds = std::max(b.lds, launches[i].ca.lds);
             if (nbe >= be_cap) { be_overflow = true; return; }
             hbe[nbe].pos = (uint32_t)i;
             hbe[nbe].first = b.blocks;
@@ -535,7 +626,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         si.batches.push_back(b);
     };
     // per-group scratch, reused across groups (cleared, capacity kept)
-    std::vector<int> prepped, direct, grp;
+    std::vector<int> prepped, direct, cls, grp;
     std::vector<std::pair<uint32_t, int>> rows, gens, reds;
     std::map<uint32_t, int> shape_dom;   // TZ * 4 + TM -> largest vertex of the group
     constexpr bool kF64 = std::is_same<KeyT, double>::value;
@@ -569,15 +660,20 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         cur_group = (int)sl;
         prepped.clear();
         direct.clear();
+        cls.clear();
         // a fused minimum's blocks are built with its producer's, before the
         // producer's fill reads them; its own fill is a reduction (below)
         std::vector<int> fills;   // members with a prep here or hoisted: rows / generic fills
         for (int i : mem) {
-            if (launches[i].direct) direct.push_back(i);
+            if (launches[i].cls) cls.push_back(i);
+            else if (launches[i].direct) direct.push_back(i);
             else if (!launches[i].fused) (hoisting && P.v[i].prep_after >= -1 ? fills : prepped).push_back(i);
             if (P.v[i].fuse_into >= 0) prepped.push_back(P.v[i].fuse_into);
         }
         add_batch(Batch::kDirect, 0, direct, [](const Launch<KeyT> &L) { return L.da.nblk; });
+        uint32_t cls_threads = 256;
+        for (int i : cls) cls_threads = std::max(cls_threads, P.v[i].threads);
+        add_batch(Batch::kClass, cls_threads, cls, [](const Launch<KeyT> &L) { return L.ca.nblk; });
         add_batch(Batch::kPrep, 0, prepped, [](const Launch<KeyT> &L) { return L.prep.nwg; });
         prepped.insert(prepped.end(), fills.begin(), fills.end());
         rows.clear();
@@ -714,6 +810,7 @@ pase_status plan_check(pase_graph_t g, uint64_t *image_bytes) {
             if (pos >= fills.size()) return fail(g, PASE_ERR_INTERNAL, "batch entry out of range");
             const bool fused = g->plan.v[pos].fused_from >= 0;
             if (b.kind == Batch::kRows || b.kind == Batch::kGeneric || b.kind == Batch::kDirect ||
+                b.kind == Batch::kClass ||
                 (b.kind == Batch::kReduce && fused)) {
                 fills[pos]++;
                 fill_batch[pos] = (int)bi;
@@ -726,7 +823,7 @@ pase_status plan_check(pase_graph_t g, uint64_t *image_bytes) {
     // waited for by the vertex's group
     for (size_t i = 0; i < g->plan.v.size(); i++) {
         const VPlan &vp = g->plan.v[i];
-        if (vp.kernel == kDirect || vp.fused_from >= 0) continue;
+        if (vp.kernel == kDirect || vp.classes || vp.fused_from >= 0) continue;
         if (prep_batch[i] < 0 || prep_batch[i] > fill_batch[i])
             return fail(g, PASE_ERR_INTERNAL, "a prep does not precede its fill");
         if (si.hoist && vp.prep_after >= -1) {
