@@ -112,6 +112,14 @@ __global__ __launch_bounds__(256) void k_cost_tables(const DevVertex *__restrict
     }
 }
 
+// Class ids of the joint fills' shapes, one workgroup each, after the class
+// tables.
+__global__ __launch_bounds__(kJointMaxK) void k_joint_tables(const DevJointTab *__restrict__ jt,
+                                                             const DevClassTab *__restrict__ tabs, char *ws) {
+    __shared__ JointTabLds lds;
+    joint_table_item(jt[blockIdx.x], tabs, ws, lds);
+}
+
 // Volume-intersection model: every entry of every edge's K_src x K_dst cost
 // matrix, into the matrix region the prep kernel then reads like caller-given
 // matrices, for every-integer splits (the device walk of volume_cost).  One
@@ -312,11 +320,13 @@ __global__ __launch_bounds__(256) void k_fill_direct(const DirectArgs *__restric
 
 // Class fill of the vertices of one level; `one` names the vertex of a
 // one-vertex launch (the chains of small vertices: its descriptor is then the
-// first load, without a search through the batch), ~0 otherwise.
-template <typename KeyT>
-__global__ __launch_bounds__(512) void k_fill_class(const ClassArgs *__restrict__ descs,
-                                                              const BatchEntry *__restrict__ be, uint32_t nbe,
-                                                              uint32_t one, uint32_t prio) {
+// first load, without a search through the batch), ~0 otherwise.  MANY: the
+// vertices with three or four edges or lookups, whose registers (160) would
+// cost all others half of their waves (6 per SIMD with 84 registers).
+template <typename KeyT, bool MANY>
+__global__ __launch_bounds__(512, MANY ? 3 : 6) void k_fill_class(const ClassArgs *__restrict__ descs,
+                                                                  const BatchEntry *__restrict__ be, uint32_t nbe,
+                                                                  uint32_t one, uint32_t prio) {
     extern __shared__ __align__(16) char lds[];
     if (prio) __builtin_amdgcn_s_setprio(3);
     uint32_t pos = one, lb = blockIdx.x;
@@ -326,14 +336,53 @@ __global__ __launch_bounds__(512) void k_fill_class(const ClassArgs *__restrict_
         lb -= be[kb].first;
     }
     const ClassArgs &a = descs[pos];
-    switch (a.ne * 8 + a.nt) {
 #define PASE_CLASS(ne, nt) case ne * 8 + nt: class_item<KeyT, ne, nt>(a, lb, lds); break;
-#define PASE_CLASS_E(ne) PASE_CLASS(ne, 0) PASE_CLASS(ne, 1) PASE_CLASS(ne, 2) PASE_CLASS(ne, 3) PASE_CLASS(ne, 4)
-        PASE_CLASS_E(0) PASE_CLASS_E(1) PASE_CLASS_E(2) PASE_CLASS_E(3) PASE_CLASS_E(4)
-#undef PASE_CLASS_E
-#undef PASE_CLASS
-    default: break;
+    if constexpr (MANY) {
+        switch (a.ne * 8 + a.nt) {
+            PASE_CLASS(0, 3) PASE_CLASS(0, 4) PASE_CLASS(1, 3) PASE_CLASS(1, 4) PASE_CLASS(2, 3) PASE_CLASS(2, 4)
+            PASE_CLASS(3, 0) PASE_CLASS(3, 1) PASE_CLASS(3, 2) PASE_CLASS(3, 3) PASE_CLASS(3, 4)
+            PASE_CLASS(4, 0) PASE_CLASS(4, 1) PASE_CLASS(4, 2) PASE_CLASS(4, 3) PASE_CLASS(4, 4)
+        default: break;
+        }
+    } else {
+        switch (a.ne * 8 + a.nt) {
+            PASE_CLASS(0, 0) PASE_CLASS(0, 1) PASE_CLASS(0, 2) PASE_CLASS(1, 0) PASE_CLASS(1, 1) PASE_CLASS(1, 2)
+            PASE_CLASS(2, 0) PASE_CLASS(2, 1) PASE_CLASS(2, 2)
+        default: break;
+        }
     }
+#undef PASE_CLASS
+}
+
+// U: configurations per thread (2 when one of the three counts is past the
+// workgroup's 512 threads; its registers would halve the waves of the others).
+template <typename KeyT, int U>
+__global__ __launch_bounds__(512, U == 1 ? 6 : 4) void k_fill_joint(const JointArgs *__restrict__ descs,
+                                                                    const BatchEntry *__restrict__ be, uint32_t nbe,
+                                                                    uint32_t one, uint32_t prio) {
+    extern __shared__ __align__(16) char lds[];
+    if (prio) __builtin_amdgcn_s_setprio(3);
+    uint32_t pos = one, lb = blockIdx.x;
+    if (one == ~0u) {
+        const uint32_t kb = batch_find(be, nbe, blockIdx.x);
+        pos = be[kb].pos;
+        lb -= be[kb].first;
+    }
+    const JointArgs &a = descs[pos];
+    if (a.has_e) joint_item<KeyT, U, true>(a, lb, lds);
+    else joint_item<KeyT, U, false>(a, lb, lds);
+}
+
+template <typename KeyT>
+__global__ __launch_bounds__(512) void k_fill_half(const JointArgs *__restrict__ descs,
+                                                   const BatchEntry *__restrict__ be, uint32_t nbe, uint32_t prio) {
+    extern __shared__ __align__(16) char lds[];
+    if (prio) __builtin_amdgcn_s_setprio(3);
+    const uint32_t kb = batch_find(be, nbe, blockIdx.x);
+    const JointArgs &a = descs[be[kb].pos];
+    const uint32_t most = max(max(a.s[0].K, a.s[1].K), a.Ky);
+    if (most <= blockDim.x) half_item<KeyT, 1>(a, blockIdx.x - be[kb].first, lds);
+    else half_item<KeyT, 2>(a, blockIdx.x - be[kb].first, lds);
 }
 
 // ------------------------------------------------------------------ back-substitution
@@ -361,7 +410,12 @@ __global__ void k_backtrack(const BacktrackDesc *__restrict__ bt, uint32_t n, co
 // Back-substitution by backward levels: one thread per position; the
 // configurations of one level depend only on those of lower levels, so a level
 // costs one dependent argmin read instead of one per vertex.  Configurations
-// live in LDS until the end.
+// live in LDS until the end, a position's digits and strides in registers
+// (indexed by unrolled constants; in scratch memory they cost every level a
+// second round trip).  A position without a table (part of a joint fill) has
+// its argmin evaluated by a wave, whose descriptor is in LDS (the first
+// kLazyLds of them): the level's such positions over the waves.
+constexpr uint32_t kLazyLds = 32;
 template <typename KeyT>
 __global__ __launch_bounds__(kMaxBacktrackThreads) void k_backtrack_levels(const BacktrackDesc *__restrict__ bt,
                                                                           uint32_t n, uint32_t nlev,
@@ -369,21 +423,83 @@ __global__ __launch_bounds__(kMaxBacktrackThreads) void k_backtrack_levels(const
                                                                           uint32_t *__restrict__ cfg,
                                                                           SearchOut *out) {
     __shared__ uint32_t scfg[kMaxBacktrackThreads];
-    __shared__ uint32_t sbad;
+    __shared__ uint16_t slazy[kMaxBacktrackThreads];   // positions without a table, any order
+    __shared__ uint16_t slevel[kMaxBacktrackThreads];  // their levels
+    __shared__ ClassArgs sargs[kLazyLds];
+    __shared__ uint32_t sdig[kLazyLds][kMaxDep + 2];   // digits, vertex, configurations
+    __shared__ uint32_t sbad, nlazy;
     const uint32_t t = threadIdx.x;
     const bool mine = t < n;
-    if (t == 0) sbad = 0;
-    BacktrackDesc d;
-    if (mine) d = bt[t];
+    if (t == 0) sbad = nlazy = 0;
+    scfg[t] = 0;
+    __syncthreads();
+    uint32_t dig[kMaxDep], m = 0, level = ~0u, vi = 0, K = 0;
+    uint64_t stride[kMaxDep];
+    const uint16_t *A = nullptr;
+    if (mine) {
+        const BacktrackDesc &d = bt[t];
+        m = d.m;
+        vi = d.vi;
+        K = d.K;
+        A = d.A;
+#pragma unroll
+        for (int k = 0; k < kMaxDep; k++) {
+            dig[k] = k < (int)m ? d.dig[k] : 0;
+            stride[k] = k < (int)m ? d.stride[k] : 0;
+        }
+        if (d.lazy) {
+            const uint32_t k = atomicAdd(&nlazy, 1u);
+            slazy[k] = (uint16_t)t;
+            slevel[k] = (uint16_t)d.level;
+            if (k < kLazyLds) {
+#pragma unroll
+                for (int q = 0; q < kMaxDep; q++) sdig[k][q] = dig[q];
+                sdig[k][kMaxDep] = vi;
+                sdig[k][kMaxDep + 1] = K;
+            }
+        } else {
+            level = d.level;
+        }
+    }
+    __syncthreads();
+    const uint32_t lazies = nlazy, wave = __builtin_amdgcn_readfirstlane(t >> 6), waves = blockDim.x >> 6;
+    for (uint32_t q = 0; q < min(lazies, kLazyLds); q++) {
+        const uint32_t *src = (const uint32_t *)bt[slazy[q]].lazy;
+        for (uint32_t k = t; k < sizeof(ClassArgs) / 4; k += blockDim.x) ((uint32_t *)&sargs[q])[k] = src[k];
+    }
     __syncthreads();
     for (uint32_t lev = 0; lev < nlev; lev++) {
-        if (mine && d.level == lev) {
+        if (level == lev) {
             uint64_t idx = 0;
-            for (uint32_t k = 0; k < d.m; k++) idx += (uint64_t)scfg[d.dig[k]] * d.stride[k];
-            uint32_t c = d.A[idx];
+#pragma unroll
+            for (int k = 0; k < kMaxDep; k++)
+                if (k < (int)m) idx += (uint64_t)scfg[dig[k]] * stride[k];
+            uint32_t c = A[idx];
             // every index above is in range as long as each stored argmin is
-            if (c >= d.K) { atomicOr(&sbad, 4u); c = 0; }
-            scfg[d.vi] = c;
+            if (c >= K) { atomicOr(&sbad, 4u); c = 0; }
+            scfg[vi] = c;
+        }
+        if constexpr (sizeof(KeyT) == 8) {
+            for (uint32_t q = wave; q < lazies; q += waves) {
+                if (slevel[q] != lev) continue;
+                uint32_t w[kMaxDep], c, at, top;
+                if (q < kLazyLds) {
+#pragma unroll
+                    for (int k = 0; k < kMaxDep; k++) w[k] = scfg[sdig[q][k]];
+                    at = sdig[q][kMaxDep];
+                    top = sdig[q][kMaxDep + 1];
+                    c = lazy_argmin<KeyT>(sargs[q], w);
+                } else {
+                    const BacktrackDesc &e = bt[__builtin_amdgcn_readfirstlane(slazy[q])];
+#pragma unroll
+                    for (int k = 0; k < kMaxDep; k++) w[k] = k < (int)e.m ? scfg[e.dig[k]] : 0;
+                    at = e.vi;
+                    top = e.K;
+                    c = lazy_argmin<KeyT>(*e.lazy, w);
+                }
+                if (c >= top) { atomicOr(&sbad, 4u); c = 0; }
+                if ((t & 63) == 0) scfg[at] = c;
+            }
         }
         __syncthreads();
     }
@@ -622,6 +738,7 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
     const ReduceArgs *dd = (const ReduceArgs *)(dg + n);
     const DirectArgs *dx = (const DirectArgs *)(dd + n);
     const ClassArgs *dcl = (const ClassArgs *)(dx + n);
+    const JointArgs *dj = (const JointArgs *)(dcl + n);
     const BatchEntry *dbe = (const BatchEntry *)(ws + P.off_batch);
     uint32_t *dcfg = (uint32_t *)(ws + P.off_cfg);
     SearchOut *dout = (SearchOut *)(ws + P.off_out);
@@ -666,7 +783,7 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
     }
     if (!g->overridden) {
         ClassOut ct{};
-        if (P.class_fills) {
+        if (P.class_fills + P.joint_fills) {
             ct.Lk = ws + P.off_Lk;
             ct.fk = ws + P.off_fk;
             ct.fp64 = std::is_same<KeyT, double>::value;
@@ -679,6 +796,11 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
                            (uint32_t)nv, dE, (uint32_t)ne, dex, dL, dls, dsig, si.nL, P.sig_count, g->r, dfk, nF,
                            fsent, ct, nbase);
         launches_n++;
+        if (P.joint_fills) {
+            hipLaunchKernelGGL(k_joint_tables, dim3((uint32_t)P.jtabs.size()), dim3(kJointMaxK), 0, s,
+                               (const DevJointTab *)(ws + P.off_jtdesc), (const DevClassTab *)(ws + P.off_ctdesc), ws);
+            launches_n++;
+        }
         if (g->volume && g->mat_total) {
             hipLaunchKernelGGL(g->factors ? k_edge_volume : k_edge_volume_pow2, dim3(grid_for(g->mat_rows, 1, 65535)),
                                dim3(kVolumeThreads), 0, s, dV, dE, (uint32_t)ne, dex, (uint64_t *)(ws + P.off_vmat),
@@ -722,8 +844,8 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
         for (size_t gi = 0; gi < si.groups.size(); gi++) {
             const int ln = si.group_lane[gi];
             for (int i : si.groups[gi])
-                for (const auto &t : P.v[i].terms)
-                    if (P.v[t.j].lane != ln) lane_ev_used[1 + (size_t)P.v[t.j].slot * kLanes + P.v[t.j].lane] = 1;
+                for (int j : P.v[i].reads)
+                    if (P.v[j].lane != ln) lane_ev_used[1 + (size_t)P.v[j].slot * kLanes + P.v[j].lane] = 1;
         }
     }
     // hoisted preps: a side batch starts after everything enqueued on s before
@@ -776,8 +898,8 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
                 int need[kLanes];
                 for (int &x : need) x = -1;
                 for (int i : si.groups[b.group])
-                    for (const auto &t : P.v[i].terms)
-                        if (P.v[t.j].lane != b.lane) need[P.v[t.j].lane] = std::max(need[P.v[t.j].lane], P.v[t.j].slot);
+                    for (int j : P.v[i].reads)
+                        if (P.v[j].lane != b.lane) need[P.v[j].lane] = std::max(need[P.v[j].lane], P.v[j].slot);
                 for (int l = 0; l < kLanes; l++)
                     if (need[l] > waited[b.lane][l]) {
                         if (need[l] >= b.group / nl)   // a table is read at a later slot only
@@ -798,6 +920,8 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
         case Batch::kGeneric:
         case Batch::kDirect:
         case Batch::kClass:
+        case Batch::kHalf:
+        case Batch::kJoint:
         {
             // with profiling, the launch itself records its start and end
             // (events attached to the dispatch, no extra packets in the stream)
@@ -810,8 +934,26 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
             } else if constexpr (kWide) {
                 return fail(g, PASE_ERR_INTERNAL, "a 128-bit key plan holds a row, direct or class fill");
             } else if (b.kind == Batch::kClass) {
-                hipExtLaunchKernelGGL((k_fill_class<KeyT>), dim3(b.blocks), dim3(b.variant), b.lds, bs, e0, e1, 0,
-                                      dcl, e, b.nentries, b.nentries == 1 ? b.pos0 : ~0u, (uint32_t)(si.lanes && b.lane == 0));
+                const uint32_t one = b.nentries == 1 ? b.pos0 : ~0u, prio = si.lanes && b.lane == 0;
+                const dim3 threads(b.variant & ~1u);
+                if (b.variant & 1u)
+                    hipExtLaunchKernelGGL((k_fill_class<KeyT, true>), dim3(b.blocks), threads, b.lds, bs, e0, e1, 0, dcl,
+                                          e, b.nentries, one, prio);
+                else
+                    hipExtLaunchKernelGGL((k_fill_class<KeyT, false>), dim3(b.blocks), threads, b.lds, bs, e0, e1, 0, dcl,
+                                          e, b.nentries, one, prio);
+            } else if (b.kind == Batch::kHalf) {
+                hipExtLaunchKernelGGL((k_fill_half<KeyT>), dim3(b.blocks), dim3(b.variant), b.lds, bs, e0, e1, 0,
+                                      dj, e, b.nentries, (uint32_t)(si.lanes && b.lane == 0));
+            } else if (b.kind == Batch::kJoint) {
+                const uint32_t one = b.nentries == 1 ? b.pos0 : ~0u, prio = si.lanes && b.lane == 0;
+                const dim3 threads(b.variant & ~1u);
+                if (b.variant & 1u)
+                    hipExtLaunchKernelGGL((k_fill_joint<KeyT, 2>), dim3(b.blocks), threads, b.lds, bs, e0, e1, 0, dj, e,
+                                          b.nentries, one, prio);
+                else
+                    hipExtLaunchKernelGGL((k_fill_joint<KeyT, 1>), dim3(b.blocks), threads, b.lds, bs, e0, e1, 0, dj, e,
+                                          b.nentries, one, prio);
             } else if (b.kind == Batch::kRows) {
                 if (!launch_rows<KeyT>(dr, dg, e, b, bs, e0, e1)) return fail(g, PASE_ERR_INTERNAL, "no kernel for TZ");
             } else {
@@ -842,7 +984,8 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
     }
     if (profile) HIPCHK(hipEventRecord(d->phase_ev[2], s));
     if ((uint32_t)n <= kMaxBacktrackThreads)
-        hipLaunchKernelGGL((k_backtrack_levels<KeyT>), dim3(1), dim3((n + 63) / 64 * 64), 0, s,
+        // (at least four waves when positions without a table are evaluated)
+        hipLaunchKernelGGL((k_backtrack_levels<KeyT>), dim3(1), dim3(std::max((n + 63) / 64 * 64, P.joint_fills ? 256 : 64)), 0, s,
                            (const BacktrackDesc *)(ws + P.off_bt), (uint32_t)n, si.nlev,
                            (const void *)(ws + P.off_T + P.v[n - 1].T_off), dcfg, dout);
     else

@@ -397,11 +397,11 @@ static void fuse_minima(pase_graph_t g, Plan &P) {
     const int n = (int)P.v.size();
     for (int i2 = 0; i2 < n; i2++) {
         VPlan &b = P.v[i2];
-        if (b.kernel != kRows || b.classes || b.z >= 0 || b.nsplit != 1 || b.terms.size() != 1 || b.terms[0].dig.size() < 2)
+        if (b.kernel != kRows || b.classes || b.joint >= 0 || b.z >= 0 || b.nsplit != 1 || b.terms.size() != 1 || b.terms[0].dig.size() < 2)
             continue;
         const int i1 = b.terms[0].j;
         VPlan &a = P.v[i1];
-        if (a.kernel != kRows || a.classes || a.z != b.vi || !a.O.empty() || a.R != b.R || a.nsplit != 1 || a.consumer != i2 ||
+        if (a.kernel != kRows || a.classes || a.joint >= 0 || a.z != b.vi || !a.O.empty() || a.R != b.R || a.nsplit != 1 || a.consumer != i2 ||
             a.lane != b.lane || a.fuse_into >= 0 || a.fused_from >= 0)
             continue;
         a.fuse_into = i2;
@@ -421,8 +421,19 @@ static void fuse_minima(pase_graph_t g, Plan &P) {
 // takes several times longer but leaves most of the GPU to the launches of
 // the slots in between (a full-size prep grid beside them slows them down
 // more than it saves).
+//
+// A joint fill has a half fill in place of a prep: it runs in the slot of the
+// vertex whose side it computes, and counts as hoisted (prep_after is that
+// slot) when it reads tables and that slot is two or more before the fill's.
 static void hoist_preps(pase_graph_t g, Plan &P, bool lanes) {
     for (auto &vp : P.v) {
+        if (vp.joint >= 0) {
+            const VPlan &vj = P.v[vp.joint];
+            if (!vp.jearly || vj.terms.empty() || vj.slot + 2 > vp.slot) continue;
+            vp.prep_after = vj.slot;
+            vp.prep_lane = vj.lane;
+            continue;
+        }
         if ((vp.kernel != kRows && vp.kernel != kGeneric) || vp.classes || vp.fused_from >= 0 || vp.fuse_into >= 0) continue;
         uint64_t elems = 0;
         int ready = -1;
@@ -477,13 +488,13 @@ static void hoist_preps(pase_graph_t g, Plan &P, bool lanes) {
 // (A class fill counts from a quarter of the threshold: it is bound by the
 // stores of its table, which hold up the other lane's loads as well.)
 static bool bulk_fill(const VPlan &vp, double bulk_us) {
-    return vp.kernel == kRows && vp.est_us * (vp.classes ? 4.0 : 1.0) >= bulk_us;
+    return vp.kernel == kRows && vp.est_us * (vp.classes || vp.joint >= 0 ? 4.0 : 1.0) >= bulk_us;
 }
 
 static void assign_bulk_lanes(Plan &P, double bulk_us) {
     for (auto &vp : P.v) {
         bool bulk = bulk_fill(vp, bulk_us);
-        for (const auto &t : vp.terms) bulk |= P.v[t.j].lane == 1;
+        for (int j : vp.reads) bulk |= P.v[j].lane == 1;
         vp.lane = bulk ? 1 : 0;
     }
 }
@@ -500,7 +511,7 @@ static void assign_bulk_lanes(Plan &P, double bulk_us) {
 static void assign_split_lanes(Plan &P, double bulk_us) {
     for (auto &vp : P.v) {
         bool one = vp.level < kSplitBatchedLevels || bulk_fill(vp, bulk_us);
-        for (const auto &t : vp.terms) one |= P.v[t.j].lane == 1 && P.v[t.j].level >= kSplitBatchedLevels;
+        for (int j : vp.reads) one |= P.v[j].lane == 1 && P.v[j].level >= kSplitBatchedLevels;
         vp.lane = one ? 1 : 0;
     }
 }
@@ -713,9 +724,153 @@ static pase_status build_plan(pase_graph_t g) {
                                    (double)rows * vp.K * (4.0 + 6.0 * (double)(vp.edges.size() + vp.terms.size())) / 1e7);
         return true;
     };
+    // Joint fill: a vertex without a class digit that can take one of its
+    // lookups' vertices in (the structure is described at JointSide).  The
+    // digit y with the most configurations.  Classes are kept small -- each
+    // end of the three edges has at most one loop dim that the tensor does not
+    // map -- so that at most one pair of combined classes belongs to an entry;
+    // the dense fill costs two operations per (c, y), this about 100 per
+    // configuration and row, so K_i and Ky from 24 up.  uint64 keys: the sums of both
+    // vertices' terms must not wrap (fp64 sums past 2^53 round, but never below
+    // a key that is exact).
+    std::vector<uint64_t> qmax, tmax;
+    uint32_t joint_kt = 2;
+    if (class_ok && n <= (int)kMaxBacktrackThreads) {
+        pase_status kst;
+        joint_kt = choose_key_type(g, &kst);
+        if (kst != PASE_OK || !cost_bounds(g, &qmax, &tmax)) joint_kt = 2;
+    }
+    auto mapped = [&](int e, int u) {   // loop dims of vertex u that edge e's tensor maps
+        const auto &d = g->E[e];
+        uint32_t m = 0;
+        for (uint32_t k = 0; k < d.rank; k++) {
+            const int x = (int)d.src == u ? d.src_dim[k] : d.dst_dim[k];
+            if (x >= 0) m |= 1u << x;
+        }
+        return m;
+    };
+    auto tight = [&](int e) {   // both ends of an edge map all but one of their loop dims
+        for (int u : {(int)g->E[e].src, (int)g->E[e].dst})
+            if ((uint32_t)__builtin_popcount(mapped(e, u)) + 1 < g->V[u].ndims) return false;
+        return true;
+    };
+    // classes of u's configurations under edge e: the split tuples of the mapped dims
+    auto classes_of = [&](int e, int u) {
+        const uint32_t m = (uint32_t)__builtin_popcount(mapped(e, u));
+        if (!g->factors) {
+            uint32_t L = 0, n = 1;
+            while ((1u << L) < g->p) L++;
+            for (uint32_t k = 1; k <= m; k++) n = n * (L + k) / k;   // C(L + m, m)
+            return n;
+        }
+        // tuples of m factors with product <= q, for every q up to p
+        std::vector<uint32_t> cnt(g->p + 1, 1);
+        for (uint32_t k = 0; k < m; k++) {
+            std::vector<uint32_t> next(g->p + 1, 0);
+            for (uint32_t q = 1; q <= g->p; q++)
+                for (uint32_t f = 1; f <= q; f++) next[q] += cnt[q / f];
+            cnt.swap(next);
+        }
+        return cnt[g->p];
+    };
+    // With y's classes fixed, v_i's and v_j's configurations each have one free
+    // dim; unless the edge between them ties the two together, all pairs of
+    // them that share a class share the combined classes.
+    auto one_pair = [&](int eo, int ei, int ey, int vi, int vj) {
+        const uint32_t fi = ((1u << g->V[vi].ndims) - 1) & ~mapped(ei, vi);
+        const uint32_t fj = ((1u << g->V[vj].ndims) - 1) & ~mapped(ey, vj);
+        const auto &d = g->E[eo];
+        for (uint32_t k = 0; k < d.rank; k++) {
+            const int a = (int)d.src == vi ? d.src_dim[k] : d.dst_dim[k], b = (int)d.src == vi ? d.dst_dim[k] : d.src_dim[k];
+            if (a >= 0 && b >= 0 && (fi >> a & 1u) && (fj >> b & 1u)) return false;
+        }
+        return true;
+    };
+    auto plan_joint = [&](int i) {
+        VPlan &vp = P.v[i];
+        if (joint_kt == 2 || vp.K > kJointMaxK || vp.K < 24 || vp.D.size() < 2) return false;
+        auto edge_to = [&](const VPlan &v, int w) {   // the one edge of v to w: its id, -1 none, -2 several
+            int at = -1;
+            for (int e : v.edges)
+                if ((int)g->E[e].src == w || (int)g->E[e].dst == w) at = at == -1 ? e : -2;
+            return at;
+        };
+        auto in = [](const TermRef &t, int w) { return std::count(t.dig.begin(), t.dig.end(), w) > 0; };
+        int bj = -1, by = -1;
+        uint32_t bcls[4] = {0, 0, 0, 0};
+        for (const auto &tj : vp.terms) {
+            const VPlan &vj = P.v[tj.j];
+            if (!vj.classes || vj.joint >= 0 || vj.K > kJointMaxK || tj.dig.empty()) continue;
+            const int eo = edge_to(vj, vp.vi);
+            bool looked = eo < 0 || !tight(eo);
+            for (const auto &t : vj.terms) looked |= in(t, vp.vi);
+            const unsigned __int128 top = ((unsigned __int128)qmax[i] + qmax[tj.j] + 2) << std::max(vp.bits, vj.bits);
+            if (looked || (joint_kt == 1 && top >> 64)) continue;
+            for (int y : tj.dig) {
+                const int ey = edge_to(vj, y), ei = edge_to(vp, y);
+                bool bad = ey < 0 || !tight(ey) || ei == -2 || (ei >= 0 && !tight(ei)) || g->K[y] > kJointMaxK;
+                for (const auto &t : vj.terms) bad |= in(t, y);
+                uint32_t ni = 0, nti = 0;
+                for (const auto &t : vp.terms)
+                    if (t.j != tj.j) { bad |= in(t, y); nti++; }
+                for (int e : vp.edges) ni += e != ei;
+                if (bad || ni > kJointTerms || nti > kJointTerms || vj.edges.size() - 2 > kJointTerms ||
+                    vj.terms.size() > kJointTerms || (ei >= 0 && !one_pair(eo, ei, ey, vp.vi, vj.vi)))
+                    continue;
+                if (by >= 0 && g->K[y] <= g->K[by]) continue;
+                const uint32_t cls[4] = {ei >= 0 ? classes_of(ei, vp.vi) : 0, classes_of(ey, vj.vi), classes_of(eo, vj.vi),
+                                         classes_of(eo, vp.vi)};
+                if (joint_lds(vp.K, vj.K, cls[3], cls[0], cls[1], ei >= 0) > kJointMaxLds ||
+                    half_lds(vj.K, cls[2], cls[1]) > kJointMaxLds)
+                    continue;
+                std::copy(cls, cls + 4, bcls);
+                bj = tj.j;
+                by = y;
+            }
+        }
+        if (bj < 0 || g->K[by] < 24) return false;
+        const VPlan &vj = P.v[bj];
+        // v_j's digits first (the upper ones), the others after them in the
+        // order of the largest other lookup; y fastest in the table
+        std::vector<int> order;
+        int big = -1;
+        for (size_t t = 0; t < vp.terms.size(); t++)
+            if (vp.terms[t].j != bj && (big < 0 || P.v[vp.terms[t].j].N > P.v[vp.terms[big].j].N)) big = (int)t;
+        if (big >= 0)
+            for (int u : P.v[vp.terms[big].j].layout)
+                if (u != vp.vi) order.push_back(u);
+        for (int u : vp.D)
+            if (std::find(order.begin(), order.end(), u) == order.end()) order.push_back(u);
+        const auto has = [](const std::vector<int> &v, int u) { return std::find(v.begin(), v.end(), u) != v.end(); };
+        std::vector<int> R;
+        vp.jupper = 1;
+        for (int u : order)
+            if (u != by && has(vj.D, u)) { R.push_back(u); vp.jupper *= g->K[u]; }
+        for (int u : order)
+            if (u != by && !has(vj.D, u)) R.push_back(u);
+        vp.R = R;
+        vp.joint = bj;
+        std::copy(bcls, bcls + 4, vp.jcls);
+        vp.z = by;
+        vp.O.clear();
+        vp.MO = 1;
+        vp.MR = vp.N / g->K[by];
+        vp.TZ = 0;
+        vp.TM = 1;
+        vp.nsplit = 1;
+        vp.cper = vp.K;
+        vp.parts = 0;
+        vp.layout = vp.R;
+        vp.layout.push_back(by);
+        vp.stride.assign(vp.layout.size(), 1);
+        for (int k = (int)vp.layout.size() - 2; k >= 0; k--) vp.stride[k] = vp.stride[k + 1] * g->K[vp.layout[k + 1]];
+        vp.est_us = 6.0 + (double)vp.MR * (1.2e-3 + 1.5e-5 * vp.K);
+        return true;
+    };
     auto plan_one = [&](int i, uint32_t ftz, uint32_t ftm, bool no_split) {
         VPlan &vp = P.v[i];
         vp.classes = false;
+        vp.joint = -1;
         const uint32_t tile_cols = ftz ? ftz : g->tile_cols, tile_rows = ftm ? ftm : g->tile_rows;
         // small vertices: the direct fill (one launch, no prep blocks), whose
         // time is a launch plus the gather of every term of every cell
@@ -737,6 +892,17 @@ static pase_status build_plan(pase_graph_t g) {
         if (!ftz && kernel_mode == 0 && plan_class(i, small)) {
             vp.kernel = small ? kDirect : kRows;
             return;
+        }
+        // the joint fill, unless the dense one below is estimated faster: its
+        // rows cost 1.3 ns each at K = 35 (86 us against 27 + 6 us of prep on the
+        // three-layer LSTM at p = 16), 8 ns at K = 462 (69 us against 143 + 26 us);
+        // a dense fill takes at least 8 us, and its prep as much
+        const VPlan plain = vp;
+        VPlan jointp;
+        const bool joint = !ftz && kernel_mode == 0 && plan_joint(i);
+        if (joint) {
+            jointp = vp;
+            vp = plain;
         }
         RowsChoice best;
         // candidates: every digit of D(i) as the column digit z, and -- only
@@ -812,7 +978,10 @@ static pase_status build_plan(pase_graph_t g) {
                 if (rc.ok && (!best.ok || rc.cost < best.cost)) best = rc;
             }
         }
-        if (best.ok) {
+        if (joint && (!best.ok || jointp.est_us <= std::max(best.cost, 8.0) + 8.0)) {
+            vp = jointp;
+            vp.kernel = kRows;
+        } else if (best.ok) {
             vp.kernel = kRows;
             vp.z = best.z;
             vp.O = best.O;
@@ -846,6 +1015,23 @@ static pase_status build_plan(pase_graph_t g) {
             vp.stride[k] = vp.stride[k + 1] * g->K[vp.layout[k + 1]];
     };
     for (int i = 0; i < n; i++) plan_one(i, 0, 0, false);
+    // the tables each vertex's launches read: a joint fill's half fill runs in
+    // the other vertex's slot (its tables are that vertex's reads), or, without
+    // levels or hoisting, just before the fill
+    for (int i = 0; i < n; i++) {
+        VPlan &vp = P.v[i];
+        vp.jearly = vp.joint >= 0 && g->schedule != kSchedSeq && g->hoist_elems != 0;
+        for (const auto &t : vp.terms) {
+            if (t.j == vp.joint) {
+                P.v[t.j].absorbed = i;
+                if (!vp.jearly) {
+                    for (const auto &u : P.v[t.j].terms) vp.reads.push_back(u.j);
+                    continue;
+                }
+            }
+            vp.reads.push_back(t.j);
+        }
+    }
     // One launch per level and kernel variant: a small column-form row vertex
     // of a level is re-planned with the tile shape of the level's largest one
     // when its fill then stays under half of that vertex's, so that the two
@@ -861,16 +1047,17 @@ static pase_status build_plan(pase_graph_t g) {
         for (int i = 0; i < n; i++) {
             const VPlan &vp = P.v[i];
             if (vp.kernel != kRows || vp.z < 0) continue;
+            if (vp.absorbed >= 0 && !g->keep_tables) continue;   // not launched
             int &d = dom[vp.level];
             if (d < 0 || vp.est_us > P.v[d].est_us) d = i;
         }
         for (int i = 0; i < n; i++) {
             const int d = dom[P.v[i].level];
-            if (d < 0 || d == i || P.v[i].kernel != kRows || P.v[i].z < 0) continue;
+            if (d < 0 || d == i || P.v[i].kernel != kRows || P.v[i].z < 0 || P.v[i].joint >= 0) continue;
             // (split chains: only the batched levels share launches level-wide)
             if (g->schedule == kSchedSplit && P.v[i].level >= kSplitBatchedLevels) continue;
             const VPlan &dv = P.v[d];
-            if (P.v[i].classes || dv.classes) {
+            if (P.v[i].classes || dv.classes || dv.joint >= 0) {
                 // class fills of a batched level share one launch, and with it
                 // the largest one's rows per workgroup and use of LDS
                 VPlan &ci = P.v[i];
@@ -894,7 +1081,7 @@ static pase_status build_plan(pase_graph_t g) {
         }
     }
     for (const auto &vp : P.v) {
-        if (vp.kernel != kRows || vp.classes) continue;
+        if (vp.kernel != kRows || vp.classes || vp.joint >= 0) continue;
         P.rows_vertices++;
         P.rows_cells += vp.N * vp.K;
         if (vp.z < 0) P.stream_cells += vp.N * vp.K;
@@ -903,39 +1090,58 @@ static pase_status build_plan(pase_graph_t g) {
     if (g->schedule == kSchedBulk) assign_bulk_lanes(P, (double)g->bulk_us);
     if (g->schedule == kSchedSplit) assign_split_lanes(P, (double)g->bulk_us);
     if (g->fuse_min && kernel_mode == 0) fuse_minima(g, P);
-    // class tables, one per distinct edge shape (v_i's end, the other end)
+    // class tables, one per distinct edge shape (the end u, the other end)
     P.overridden = g->overridden;
-    for (auto &vp : P.v) {
-        if (!vp.classes) continue;
-        P.class_fills++;
-        if (vp.z < 0) continue;
-        for (int e : vp.edges) {
+    auto class_table = [&](int u, int w) {   // of the one edge joining vertices u and w, by u's classes
+        for (int e : incident[u]) {
             const auto &d = g->E[e];
-            const bool is_src = (int)d.src == vp.vi;
-            if ((is_src ? (int)d.dst : (int)d.src) != vp.z) continue;
+            const bool is_src = (int)d.src == u;
+            if ((is_src ? (int)d.dst : (int)d.src) != w) continue;
             DevClassTab t;
             std::memset(&t, 0, sizeof t);
-            t.K = vp.K;
-            t.Kz = g->K[vp.z];
-            t.ndu = g->V[vp.vi].ndims;
-            t.ndz = g->V[vp.z].ndims;
+            t.K = g->K[u];
+            t.Kz = g->K[w];
+            t.ndu = g->V[u].ndims;
+            t.ndz = g->V[w].ndims;
             t.rank = d.rank;
             t.factors = g->factors ? 1 : 0;
             for (uint32_t k = 0; k < kMaxDims; k++) {
                 t.udim[k] = (int8_t)(k < d.rank ? (is_src ? d.src_dim[k] : d.dst_dim[k]) : -1);
                 t.zdim[k] = (int8_t)(k < d.rank ? (is_src ? d.dst_dim[k] : d.src_dim[k]) : -1);
             }
-            for (size_t k = 0; k < P.ctabs.size() && vp.ctab < 0; k++) {
+            for (size_t k = 0; k < P.ctabs.size(); k++) {
                 const DevClassTab &o = P.ctabs[k];
                 if (o.ndu == t.ndu && o.ndz == t.ndz && o.rank == t.rank &&
                     !std::memcmp(o.udim, t.udim, sizeof t.udim) && !std::memcmp(o.zdim, t.zdim, sizeof t.zdim))
-                    vp.ctab = (int)k;
+                    return (int)k;
             }
-            if (vp.ctab < 0) {
-                t.blk0 = P.ctab_blocks;
-                P.ctab_blocks += (t.K + t.Kz + 256 / kClassTabLanes - 1) / (256 / kClassTabLanes);
-                vp.ctab = (int)P.ctabs.size();
-                P.ctabs.push_back(t);
+            t.blk0 = P.ctab_blocks;
+            P.ctab_blocks += (t.K + t.Kz + 256 / kClassTabLanes - 1) / (256 / kClassTabLanes);
+            P.ctabs.push_back(t);
+            return (int)P.ctabs.size() - 1;
+        }
+        return -1;
+    };
+    for (auto &vp : P.v) {
+        if (vp.classes) {
+            P.class_fills++;
+            if (vp.z >= 0) vp.ctab = class_table(vp.vi, vp.z);
+        }
+        if (vp.joint >= 0) {
+            const int vj = P.v[vp.joint].vi;
+            P.joint_fills++;
+            vp.jtab[0] = class_table(vp.vi, vp.z);
+            vp.jtab[1] = class_table(vj, vp.z);
+            vp.jtab[2] = class_table(vj, vp.vi);
+            vp.jtab[3] = class_table(vp.vi, vj);
+            for (size_t k = 0; k < P.jtabs.size() && vp.jshape < 0; k++)
+                if (std::equal(vp.jtab, vp.jtab + 4, P.jtabs[k].tab)) vp.jshape = (int)k;
+            if (vp.jshape < 0) {
+                DevJointTab t;
+                std::memset(&t, 0, sizeof t);
+                std::copy(vp.jtab, vp.jtab + 4, t.tab);
+                vp.jshape = (int)P.jtabs.size();
+                P.jtabs.push_back(t);
             }
         }
     }
@@ -1016,11 +1222,13 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
     off = align_up(off + n * sizeof(BacktrackDesc), A);
     P.off_desc = off;
     off = align_up(off + n * (sizeof(PrepArgs) + sizeof(RowsArgs) + sizeof(GenericArgs) + sizeof(ReduceArgs) +
-                              sizeof(DirectArgs) + sizeof(ClassArgs)), A);
+                              sizeof(DirectArgs) + sizeof(ClassArgs) + sizeof(JointArgs)), A);
     P.off_batch = off;
     off = align_up(off + 3 * (uint64_t)n * sizeof(BatchEntry), A);
     P.off_ctdesc = off;
     off = align_up(off + P.ctabs.size() * sizeof(DevClassTab), A);
+    P.off_jtdesc = off;
+    off = align_up(off + P.jtabs.size() * sizeof(DevJointTab), A);
     // one zero key: the row term that pads a row-kernel vertex up to the
     // row-term count of the launch it shares (uploaded zeroed with the rest)
     P.off_zero = off;
@@ -1036,25 +1244,52 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
 
     // class fills: key-space costs and class tables, written on the device
     P.off_Lk = P.off_fk = P.off_ctab = off;
-    if (P.class_fills) {
+    if (P.class_fills + P.joint_fills) {
         P.off_fk = off = align_up(off + sumK * 8, A);
         P.off_ctab = off = align_up(off + P.sig_count * 8, A);
         for (auto &t : P.ctabs) {
             t.inv_off = off;
             off = align_up(off + t.K * 2, 16);
+            t.perm_off = off;
+            off = align_up(off + t.K * 2, 16);
+            t.first_off = off;
+            off = align_up(off + t.K * 2, 16);
             t.zs_off = off;
             off = align_up(off + t.Kz * sizeof(ClassEntry), 16);
+            t.zr_off = off;
+            off = align_up(off + t.Kz * 4, 16);
+        }
+        for (auto &t : P.jtabs) {
+            t.off_i = off;
+            off += P.ctabs[t.tab[3]].K * sizeof(JointIdI);
+            t.off_j = off;
+            off += P.ctabs[t.tab[2]].K * sizeof(JointIdI);
+            t.off_y = off;
+            off += P.ctabs[t.tab[1]].Kz * sizeof(JointY);
+            for (int k = 0; k < 3; k++) {   // v_i's to v_j, v_i's to y, v_j's to y
+                const int tab = t.tab[k == 0 ? 3 : k - 1];
+                t.off_start[k] = off;
+                off += tab < 0 ? 0 : (P.ctabs[tab].K + 1) * 2;
+            }
+            t.off_jown = off;
+            off = align_up(off + P.ctabs[t.tab[2]].K * 2, 16);
         }
         off = align_up(off, A);
     }
 
+    auto formed = [&](const VPlan &vp) { return vp.absorbed < 0 || g->keep_tables; };
     // T arena: interval packing over launch slots -- a table is written in the
     // slot of its vertex and last read in the slot of its reader
     struct Iv { int i, s, e; uint64_t size; };
     std::vector<Iv> iv;
     for (int i = 0; i < n; i++) {
-        int end = (resident || g->keep_tables || i == n - 1) ? P.nslots : P.v[P.v[i].consumer].slot;
-        iv.push_back({i, P.v[i].slot, end, align_up(P.v[i].N * kb, A)});
+        // (the reader of a table may be part of a joint fill in a later slot; its own table is not formed)
+        const int reader = i == n - 1 ? i : P.v[i].consumer, by = P.v[reader].absorbed;
+        int end = (resident || g->keep_tables || i == n - 1) ? P.nslots
+                  : std::max(P.v[reader].slot, by >= 0 ? P.v[by].slot : 0);
+        // an absorbed vertex's argmin is evaluated after the fills: the tables it looks up stay
+        if (by >= 0) end = P.nslots;
+        iv.push_back({i, P.v[i].slot, end, formed(P.v[i]) ? align_up(P.v[i].N * kb, A) : A});
     }
     std::vector<int> order(n);
     std::iota(order.begin(), order.end(), 0);
@@ -1082,7 +1317,7 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
     P.off_T = off;
     off = align_up(off + tbytes, A);
     uint64_t abytes = 0;
-    for (auto &vp : P.v) { vp.A_off = abytes; abytes += align_up(vp.N * 2, A); }
+    for (auto &vp : P.v) { vp.A_off = abytes; abytes += formed(vp) ? align_up(vp.N * 2, A) : A; }
     P.A_bytes = abytes;
     P.off_A = off;
     off = align_up(off + abytes, A);
@@ -1092,7 +1327,10 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
     std::vector<VPlan *> hoisted;
     for (auto &vp : P.v) {
         uint64_t e = 0, pb = 0;
-        if (vp.classes) {
+        if (vp.joint >= 0) {
+            // the half table
+            e = align_up(joint_half_elems(vp.K, P.v[vp.joint].K, g->K[vp.z]) * vp.jupper, 32);
+        } else if (vp.classes) {
             // no blocks
         } else if (vp.kernel == kRows) {
             e += align_up(vp.MO * vp.K * vp.ldz, 32);
@@ -1109,7 +1347,7 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
         vp.partial_off = psum[sl];
         psum[sl] += pb;
         pmax = std::max(pmax, psum[sl]);
-        if (vp.prep_after >= -1) {   // hoisted: blocks live from an earlier slot on
+        if (vp.prep_after >= -1 || vp.jearly) {   // hoisted: blocks live from an earlier slot on
             hoisted.push_back(&vp);
             continue;
         }

@@ -66,10 +66,38 @@ struct DevEdge {
 // equal split signatures.  Written on the device by k_cost_tables.
 struct DevClassTab {
     uint64_t ex_u, ex_z;      // byte offsets of the two ends' split rows
-    uint64_t inv_off;         // byte offset of inv: uint16[K], configuration c's place when sorted by class
-    uint64_t zs_off;          // byte offset of zs: ClassEntry[Kz], the other end's configurations sorted by class
+    // byte offsets of the outputs: for u's configurations their place when sorted by class, the inverse
+    // of that, and the first place of their class (uint16[K] each); for the other end's the class's
+    // places, sorted by class (zs: ClassEntry[Kz]) and by configuration (zr: first | count << 16, uint32[Kz])
+    uint64_t inv_off, perm_off, first_off, zs_off, zr_off;
     uint32_t K, Kz, ndu, ndz, rank, factors, blk0, pad;
     int8_t udim[kMaxDims], zdim[kMaxDims];
+};
+
+// Class ids of a joint fill's shape (below), from its four class tables:
+// consecutive numbers for the classes that occur, so that class minima are
+// small arrays, and places in class order, so that a class is a range.
+// Written by k_joint_tables.
+constexpr uint32_t kNoClass = 0xffff;
+struct JointIdI {             // of a configuration of v_i
+    uint16_t own, yplace;     // places: by class of the edge to v_j; by class of the edge to y, then of that to v_j
+    uint16_t other, pad;      // its class of the edge to v_j among v_j's configurations (kNoClass: none there)
+};
+struct JointIdJ {             // of a configuration of v_j
+    uint16_t own, other;      // its class of the edge to v_i, that class among v_i's configurations
+    uint16_t y, both;         // its class of the edge to y; the lowest configuration that shares both classes
+};
+struct JointY {               // of a configuration of y
+    uint16_t i, j;            // its class among v_i's, v_j's configurations (kNoClass: none)
+    uint16_t first, count;    // places by y of v_i's configurations in those that share a class of the edge
+    uint16_t pj;              // between the sides, and `both` of v_j's (kNoClass: none)
+    uint16_t pad[3];
+};
+struct DevJointTab {
+    uint64_t off_i, off_j, off_y;   // byte offsets: JointIdI[Ki], JointIdJ[Kj], JointY[Ky]
+    uint64_t off_start[3];    // first places of v_i's classes to v_j, v_i's to y, v_j's to y (and the end): uint16
+    uint64_t off_jown;        // uint16[Kj]: by place in v_j's order to y, `other`
+    int32_t tab[4];           // class tables: i to y (-1: no edge), j to y, j to i, i to j
 };
 
 struct ClassEntry {           // one configuration z of the other end
@@ -245,7 +273,69 @@ struct ClassArgs {
     uint32_t ne, nt, nblk, lds;   // lds: bytes of dynamic LDS
     ClassEdge e[kMaxClassEdges];
     ClassTerm t[kMaxClassTerms];
+    const uint64_t *sig_zc, *sig_zo;   // signatures of the edge to z by c, by z (one entry's evaluation)
 };
+
+// Joint fill.  A vertex i without a class digit whose lookup T_j does have one
+// in c: v_j meets v_i in one edge and in no lookup of its own, and a digit y of
+// T_j meets v_j in one edge and no lookup, v_i in at most one edge, and no other
+// lookup of i.  Then
+//     T_i[rest][y] = min_{c, c'} XI[c] + XJ[c'] + t(c', c) + t_i(c, y) + t_j(c', y)
+// with XI, XJ the sums of i's and j's other terms (functions of the rest
+// digits only), and each t one of 0 (same class), f of one end, f of the other.
+// Expanding them, with J0[c] = min_c' XJ + t, J1[c] = min_c' XJ + f_y(c') + t
+// and I0, I1 alike over c, the minimum over all cases is that of
+//     min_c t_i(c, y) + XI[c] + min(J0[c] + f_y'(y), J1[c]),
+//     min_{c' in class of y} XJ[c'] + min(I0[c'] + f(y), I1[c'], min_{c in class of y} XI[c] + t(c', c)),
+// all of which are minima over classes and over everything: per row a few
+// times K_i + K_j + Kz operations instead of K_i * Kz, and T_j itself is never
+// formed.  f >= 0 makes every case an upper bound of the true cost, so minimum
+// and argmin are those of the dense fill.  (v_j's configuration is looked up
+// in the back-substitution by one evaluation of its K_j keys.)
+//
+// Everything on v_j's side depends on XJ's digits alone, which are some of the
+// rest digits (called upper; the others are lower): the half fill computes,
+// per upper index, J0 and J1 by c and the minima of XJ and XJ + f over y's
+// classes, and the joint fill combines them with XI for every lower index.
+struct JointSide {            // terms of one side
+    const void *Lk;           // key-space layer costs
+    uint32_t K, ne, nt;
+    int32_t shift;            // its keys x 2^shift are keys of v_i (0 for v_i itself)
+    ClassEdge e[2];           // (digits: of the upper and lower digits together, slowest first)
+    ClassTerm t[2];
+};
+
+struct JointArgs {
+    JointSide s[2];           // v_i, v_j
+    const void *fi_o, *fj_o;  // f of the edge between them by c, by c' (v_j's key space)
+    const void *fi_y, *fi_yy; // f of the edge from v_i to y by c, by y (null: no edge)
+    const void *fj_y, *fj_yy; // of the edge from v_j to y by c', by y (v_j's key space)
+    const JointIdI *ii;
+    const JointIdJ *ij;
+    const JointY *y;
+    const uint16_t *start_o, *start_yi, *start_yj, *jown;
+    const uint16_t *jplace;   // v_j's places in its order to y
+    // half table, per upper index: J0[Ki], J1[Ki], XJ[Kj] by place in the order to y, and by y the minima
+    // of XJ, of XJ + f, of XJ over the pair's combined class (Ky each)
+    void *half;
+    void *T;                  // index (upper * lower count + lower) * Ky + y
+    uint16_t *A;
+    uint32_t Ky, bits, out_shift, has_e;   // has_e: v_i has an edge to y
+    uint32_t oi, oj, yi, yj;  // classes: of the edge between the sides among v_i's, v_j's; of those to y
+    uint32_t upper, lower, nR;   // table rows = upper * lower
+    uint32_t rad[kMaxDep];
+    uint32_t seg;             // workgroups per upper index
+    uint32_t nblk, hblk, threads, lds, hlds;   // h: of the half fill
+};
+
+constexpr uint32_t kJointMaxK = 1024;         // two configurations per thread of a 512-thread workgroup
+constexpr uint32_t kJointTerms = 2;           // rest edges, and lookups, per side
+constexpr uint32_t kJointMaxLds = 80 << 10;   // two workgroups per CU
+inline uint64_t joint_half_elems(uint64_t Ki, uint64_t Kj, uint64_t Ky) { return 2 * Ki + Kj + 3 * Ky; }
+inline uint64_t joint_lds(uint64_t Ki, uint64_t Kj, uint64_t oi, uint64_t yi, uint64_t yj, bool has_e) {
+    return 8 * (32 + Ki + oi + yj + Kj + (has_e ? 6 * Ki + oi + 4 * yi + yj : 0)) + 2 * (oi + yi + yj + 3 + Kj) + 16;
+}
+inline uint64_t half_lds(uint64_t Kj, uint64_t oj, uint64_t yj) { return 8 * (16 + 2 * oj + 2 * yj + Kj); }
 
 constexpr uint32_t kClassMaxK = 4096;         // configurations of either end of the class edge
 constexpr uint32_t kClassMaxLds = 64 << 10;   // two workgroups per CU (160 KB) with room beside them
@@ -275,6 +365,8 @@ struct BacktrackDesc {        // per position, for the back-substitution kernel
     uint32_t K;               // configurations of v_i: a stored argmin must be below it
     uint32_t dig[kMaxDep];    // vertex ids of the layout digits
     uint64_t stride[kMaxDep];
+    const ClassArgs *lazy;    // table not formed (the vertex is part of a joint fill): its terms; else null
+    uint32_t pos, pad;
 };
 
 constexpr uint32_t kMaxBacktrackThreads = 1024;   // one thread per position
@@ -318,6 +410,16 @@ struct VPlan {
     bool keep = false;              // X kept in LDS
     uint32_t threads = 256;         // workgroup size
     int ctab = -1;                  // its class table
+    // joint fill (kernel kRows): position of the vertex whose table it does without (-1: none), with z
+    // the digit y, R the rest digits, and four class tables (i to y, j to y, j to i, i to j)
+    int joint = -1;
+    int jtab[4] = {-1, -1, -1, -1};
+    int jshape = -1;                // its class ids
+    uint32_t jcls[4] = {0, 0, 0, 0};   // classes: i and j to y, j to i, i to j
+    uint64_t jupper = 1;            // product of the upper digits (the first of R)
+    bool jearly = false;            // the half fill runs in the other vertex's slot, else just before the fill
+    int absorbed = -1;              // the vertex whose joint fill does without this one's table
+    std::vector<int> reads;         // positions whose tables its launches read
     std::vector<int> O, R;          // outer / row digits (vertex ids), slowest first
     uint32_t TZ = 0, TM = 1, ldz = 0, nchunks = 0, nsplit = 1, cper = 0, parts = 1;
     uint64_t MO = 1, MR = 1;
@@ -369,8 +471,9 @@ struct Plan {
     // class fills: tables per edge shape (byte offsets relative to off_ctab until layout) and the
     // key-space layer costs and edge f values, all written by k_cost_tables
     std::vector<DevClassTab> ctabs;
-    uint32_t class_fills = 0, ctab_blocks = 0;
-    uint64_t off_ctdesc = 0, off_ctab = 0, off_Lk = 0, off_fk = 0;
+    std::vector<DevJointTab> jtabs;
+    uint32_t class_fills = 0, joint_fills = 0, ctab_blocks = 0;
+    uint64_t off_ctdesc = 0, off_jtdesc = 0, off_ctab = 0, off_Lk = 0, off_fk = 0;
     bool overridden = false;        // planned for caller-given costs
 };
 

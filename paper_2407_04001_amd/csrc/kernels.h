@@ -869,9 +869,14 @@ __device__ __forceinline__ void class_table_item(const DevClassTab &t, uint32_t 
         zeqb += __shfl_xor(zeqb, m, 64);
     }
     if (sub) return;
-    if (e < t.K) ((uint16_t *)(ws + t.inv_off))[e] = (uint16_t)(ulow + ueqb);
-    else if (e < n)
+    if (e < t.K) {
+        ((uint16_t *)(ws + t.inv_off))[e] = (uint16_t)(ulow + ueqb);
+        ((uint16_t *)(ws + t.perm_off))[ulow + ueqb] = (uint16_t)e;
+        ((uint16_t *)(ws + t.first_off))[e] = (uint16_t)ulow;
+    } else if (e < n) {
         ((ClassEntry *)(ws + t.zs_off))[zlow + zeqb] = ClassEntry{(uint16_t)ulow, (uint16_t)ueq, e - t.K};
+        ((uint32_t *)(ws + t.zr_off))[e - t.K] = ulow | ueq << 16;
+    }
 }
 
 // Workgroup lb of one vertex's class fill: 2^lr rows (the fastest bits of the
@@ -887,7 +892,7 @@ __device__ __forceinline__ void class_item_small(const ClassArgs &a, uint32_t lb
     using Ops = KeyOps<KeyT>;
     using Val = typename Ops::Val;
     constexpr int ME = NE > 0 ? NE : 1, MT = NT > 0 ? NT : 1;
-    constexpr int U = 4;
+    constexpr int U = NE + NT <= 2 ? 4 : 2;   // configurations in flight per thread (registers)
     const uint32_t threads = blockDim.x, lr = a.lr, R = 1u << lr, G = threads >> lr, K = a.K, Kz = a.Kz;
     const bool has_z = a.has_z;
     const uint32_t rl = threadIdx.x & (R - 1), g = threadIdx.x >> lr;
@@ -1047,7 +1052,7 @@ __device__ __forceinline__ void class_item_staged(const ClassArgs &a, uint32_t l
     using Ops = KeyOps<KeyT>;
     using Val = typename Ops::Val;
     constexpr int ME = NE > 0 ? NE : 1, MT = NT > 0 ? NT : 1;
-    constexpr int U = 4;
+    constexpr int U = NE + NT <= 2 ? 4 : 2;   // configurations in flight per thread (registers)
     struct alignas(16) Rec { KeyT x, f; };              // layer cost and f of a configuration (edge: signature and f)
     struct alignas(16) EdgeRec { uint64_t sig; KeyT f; };
     struct alignas(16) ZRec { uint32_t place, z; KeyT f; };   // place: first | count << 16
@@ -1221,6 +1226,546 @@ __device__ __forceinline__ void class_item(const ClassArgs &a, uint32_t b, char 
     if (lb >= (a.rows + (1u << a.lr) - 1) >> a.lr) return;   // the whole workgroup leaves together
     if (a.staged) class_item_staged<KeyT, NE, NT>(a, lb, lds);
     else class_item_small<KeyT, NE, NT>(a, lb, lds);
+}
+
+// ------------------------------------------------------------------ joint fill
+// Keys moved between lanes: both halves of the 64-bit pattern.
+template <int CTRL, typename KeyT> __device__ __forceinline__ KeyT dpp_key(KeyT v) {
+    struct W { uint32_t lo, hi; } x = __builtin_bit_cast(W, v);
+    x.lo = __builtin_amdgcn_update_dpp(x.lo, x.lo, CTRL, 0xf, 0xf, false);
+    x.hi = __builtin_amdgcn_update_dpp(x.hi, x.hi, CTRL, 0xf, 0xf, false);
+    return __builtin_bit_cast(KeyT, x);
+}
+
+// Minima of N = 8 or 4 keys over the wave.  Two exchange steps leave each
+// row of 16 lanes with one key of every N / 4 (lane swaps between two
+// registers, so no key is reduced where another will do), four steps within
+// the rows finish: 42 instructions for 8 keys instead of 144.  Key k's minimum
+// lands in lane 15 + 16 * (k / (N / 4)) of out[k % (N / 4)].
+template <int N, typename KeyT> __device__ __forceinline__ void wave_minima(const KeyT (&v)[N], KeyT (&out)[N / 4]) {
+    using Ops = KeyOps<KeyT>;
+    struct W { uint32_t lo, hi; };
+    KeyT w[N / 2];
+#pragma unroll
+    for (int k = 0; k < N / 2; k++) {
+        const W a = __builtin_bit_cast(W, v[k]), b = __builtin_bit_cast(W, v[k + N / 2]);
+        const auto lo = __builtin_amdgcn_permlane32_swap(a.lo, b.lo, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(a.hi, b.hi, false, false);
+        w[k] = Ops::min(__builtin_bit_cast(KeyT, W{lo[0], hi[0]}), __builtin_bit_cast(KeyT, W{lo[1], hi[1]}));
+    }
+#pragma unroll
+    for (int k = 0; k < N / 4; k++) {
+        const W a = __builtin_bit_cast(W, w[k]), b = __builtin_bit_cast(W, w[k + N / 4]);
+        const auto lo = __builtin_amdgcn_permlane16_swap(a.lo, b.lo, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(a.hi, b.hi, false, false);
+        KeyT x = Ops::min(__builtin_bit_cast(KeyT, W{lo[0], hi[0]}), __builtin_bit_cast(KeyT, W{lo[1], hi[1]}));
+        x = Ops::min(x, dpp_key<0x111>(x));   // row_shr 1, 2, 4, 8: lane 15 of a row ends with its minimum
+        x = Ops::min(x, dpp_key<0x112>(x));
+        x = Ops::min(x, dpp_key<0x114>(x));
+        x = Ops::min(x, dpp_key<0x118>(x));
+        out[k] = x;
+    }
+}
+
+template <typename KeyT> __device__ __forceinline__ KeyT shift_key(KeyT x, int32_t s) {
+    if constexpr (std::is_same<KeyT, double>::value) return x * __builtin_ldexp(1.0, s);
+    else return s >= 0 ? x << s : x >> -s;
+}
+
+// Class ids of one joint shape: one workgroup, a thread per configuration
+// (at most kJointMaxK).
+struct JointTabLds {
+    uint16_t rank[4][kJointMaxK];   // by place of the four class orders: number of the class there
+    uint16_t wave_sum[4][16];
+    JointIdJ id[2][kJointMaxK];     // both sides: own, other, y, both
+    uint16_t place[kJointMaxK];     // v_i: place by (y class, own class)
+};
+__device__ __forceinline__ void joint_table_item(const DevJointTab &jt, const DevClassTab *__restrict__ tabs,
+                                                 char *__restrict__ ws, JointTabLds &lds) {
+    const uint32_t t = threadIdx.x, lane = t & 63, wave = t >> 6;
+    auto place0 = [&](int k, uint32_t c) { return ((const uint16_t *)(ws + tabs[jt.tab[k]].first_off))[c]; };
+    auto perm = [&](int k, uint32_t p) { return ((const uint16_t *)(ws + tabs[jt.tab[k]].perm_off))[p]; };
+    auto zr = [&](int k, uint32_t z) { return ((const uint32_t *)(ws + tabs[jt.tab[k]].zr_off))[z]; };
+    // number the classes of each order: a place starts a class when it is the
+    // first place of the configuration there
+    bool starts[4];
+    for (int k = 0; k < 4; k++) {
+        const bool in = jt.tab[k] >= 0 && t < tabs[jt.tab[k]].K;
+        starts[k] = in && place0(k, perm(k, t)) == t;
+        const uint64_t m = __ballot(starts[k]);
+        if (lane == 0) lds.wave_sum[k][wave] = (uint16_t)__popcll(m);
+        // (classes started up to and including this place, within the wave)
+        lds.rank[k][t] = (uint16_t)__popcll(m & (~0ull >> (63 - lane)));
+    }
+    __syncthreads();
+    for (int k = 0; k < 4; k++) {
+        uint32_t s = 0;
+        for (uint32_t w = 0; w < wave; w++) s += lds.wave_sum[k][w];
+        const uint32_t r = lds.rank[k][t] + s - 1;
+        lds.rank[k][t] = (uint16_t)r;
+        const int at = k == 3 ? 0 : k == 0 ? 1 : k == 1 ? 2 : -1;   // i to j, i to y, j to y
+        if (at >= 0 && jt.tab[k] >= 0) {
+            uint16_t *out = (uint16_t *)(ws + jt.off_start[at]);
+            if (starts[k]) out[r] = (uint16_t)t;
+            if (t + 1 == tabs[jt.tab[k]].K) out[r + 1] = (uint16_t)(t + 1);
+        }
+    }
+    __syncthreads();
+    // side 0: v_i (orders 3: to j, 0: to y), side 1: v_j (orders 2: to i, 1: to y)
+    const bool has_e = jt.tab[0] >= 0;
+    for (int sd = 0; sd < 2; sd++) {
+        const int o = sd ? 2 : 3, oo = sd ? 3 : 2, y = sd ? 1 : 0;
+        if (t >= tabs[jt.tab[o]].K) continue;
+        JointIdJ id;
+        id.own = lds.rank[o][place0(o, t)];
+        const uint32_t z = zr(oo, t);
+        id.other = z >> 16 ? lds.rank[oo][z & 0xffff] : (uint16_t)kNoClass;
+        id.y = jt.tab[y] >= 0 ? lds.rank[y][place0(y, t)] : (uint16_t)0;
+        id.both = (uint16_t)t;
+        lds.id[sd][t] = id;
+    }
+    __syncthreads();
+    for (int sd = 0; sd < 2; sd++) {
+        const int o = sd ? 2 : 3, y = sd ? 1 : 0;
+        const uint32_t K = tabs[jt.tab[o]].K;
+        if (t >= K || !has_e) continue;
+        // within its class to y: the lowest configuration that shares the
+        // other class, and how many come before it by (other class, index)
+        const JointIdJ id = lds.id[sd][t];
+        uint32_t best = t, before = 0;
+        for (uint32_t p = place0(y, t); p < K; p++) {
+            const uint32_t c = perm(y, p);
+            const JointIdJ q = lds.id[sd][c];
+            if (q.y != id.y) break;
+            if (q.own == id.own && c < best) best = c;
+            before += q.own < id.own || (q.own == id.own && c < t);
+        }
+        lds.id[sd][t].both = (uint16_t)best;
+        if (sd == 0) lds.place[t] = (uint16_t)(place0(y, t) + before);
+    }
+    __syncthreads();
+    if (t < tabs[jt.tab[3]].K)
+        ((JointIdI *)(ws + jt.off_i))[t] =
+            JointIdI{((const uint16_t *)(ws + tabs[jt.tab[3]].inv_off))[t], has_e ? lds.place[t] : (uint16_t)0,
+                     lds.id[0][t].other, 0};
+    if (t < tabs[jt.tab[2]].K) {
+        ((JointIdJ *)(ws + jt.off_j))[t] = lds.id[1][t];
+        ((uint16_t *)(ws + jt.off_jown))[t] = lds.id[1][perm(1, t)].other;
+    }
+    if (t >= tabs[jt.tab[1]].Kz) return;
+    JointY r;
+    const uint32_t zj = zr(1, t), zi = has_e ? zr(0, t) : 0;
+    r.i = zi >> 16 ? lds.rank[0][zi & 0xffff] : (uint16_t)kNoClass;
+    r.j = zj >> 16 ? lds.rank[1][zj & 0xffff] : (uint16_t)kNoClass;
+    r.first = r.count = 0;
+    r.pj = (uint16_t)kNoClass;
+    r.pad[0] = r.pad[1] = r.pad[2] = 0;
+    for (uint32_t k = 0; k < zi >> 16 && r.pj == kNoClass; k++) {
+        const uint32_t c = perm(0, (zi & 0xffff) + k), want = lds.id[0][c].other;
+        for (uint32_t l = 0; l < zj >> 16 && want != kNoClass; l++) {
+            const uint32_t cp = perm(1, (zj & 0xffff) + l);
+            if (lds.id[1][cp].own != want) continue;
+            r.pj = lds.id[1][cp].both;
+            const uint32_t lowest = lds.id[0][c].both;
+            r.first = lds.place[lowest];
+            for (uint32_t m = 0; m < zi >> 16; m++) r.count += lds.id[0][perm(0, (zi & 0xffff) + m)].both == lowest;
+            break;
+        }
+    }
+    ((JointY *)(ws + jt.off_y))[t] = r;
+}
+
+// XI or XJ of configuration c (its row-independent data in sg, ef) at digits d.
+template <typename KeyT>
+__device__ __forceinline__ KeyT joint_sum(const JointSide &s, uint32_t nR, uint32_t c, KeyT lk,
+                                          const uint64_t (&sg)[kJointTerms], const KeyT (&ef)[kJointTerms],
+                                          const uint32_t (&d)[kMaxDep]) {
+    using Ops = KeyOps<KeyT>;
+    using Val = typename Ops::Val;
+    KeyT v = lk;
+#pragma unroll
+    for (int t = 0; t < (int)kJointTerms; t++)
+        if (t < (int)s.nt) {
+            uint64_t o = (uint64_t)c * s.t[t].sc;
+            for (int k = 0; k < kMaxDep; k++)
+                if (k < (int)nR) o += (uint64_t)d[k] * s.t[t].sd[k];
+            v = Ops::add(v, __builtin_bit_cast(KeyT, glb<Val>(s.t[t].ptr)[o]));
+        }
+#pragma unroll
+    for (int t = 0; t < (int)kJointTerms; t++)
+        if (t < (int)s.ne) {
+            uint32_t w = 0;
+            for (int k = 0; k < kMaxDep; k++) w = k == (int)s.e[t].dig ? d[k] : w;
+            const uint64_t so = glb<uint64_t>(s.e[t].sig_o)[w];
+            v = Ops::add(v, sg[t] == so ? (KeyT)0 : Ops::min(ef[t], glb<KeyT>(s.e[t].f_o)[w]));
+        }
+    return v;
+}
+
+// Non-negative keys order like their bit patterns: minima in LDS by 64-bit
+// integer atomics.  An untouched one (all ones) reads as the sentinel.
+template <typename KeyT> __device__ __forceinline__ void lds_min(uint64_t *p, KeyT v) {
+    atomicMin((unsigned long long *)p, __builtin_bit_cast(unsigned long long, v));
+}
+template <typename KeyT> __device__ __forceinline__ KeyT lds_key(const uint64_t *p) {
+    const uint64_t v = *p;
+    if constexpr (std::is_same<KeyT, double>::value)
+        return v == ~0ull ? KeyOps<double>::sentinel() : __builtin_bit_cast(double, v);
+    else return v;
+}
+
+// Half fill: workgroup b takes upper indices b, b + hblk, ...; configurations
+// over the threads, U per thread.
+template <typename KeyT, int U>
+__device__ __forceinline__ void half_item(const JointArgs &a, uint32_t b, char *lds) {
+    using Ops = KeyOps<KeyT>;
+    constexpr int M = (int)kJointTerms;
+    const uint32_t tid = threadIdx.x, threads = blockDim.x, lane = tid & 63;
+    const uint32_t Ki = a.s[0].K, Kj = a.s[1].K, Ky = a.Ky;
+    uint64_t *sl = (uint64_t *)lds, *mJ = sl + 16, *mJy = mJ + a.oj, *yJ = mJy + a.oj, *yJf = yJ + a.yj, *bJ = yJf + a.yj;
+    const uint32_t nslots = 16 + 2 * a.oj + 2 * a.yj + Kj;
+    const int32_t shift = a.s[1].shift;
+    const uint64_t stride = 2 * (uint64_t)Ki + Kj + 3 * (uint64_t)Ky;
+    for (uint32_t up = b; up < a.upper; up += a.hblk) {
+        __syncthreads();
+        for (uint32_t k = tid; k < nslots; k += threads) sl[k] = ~0ull;
+        uint32_t d[kMaxDep];
+        uint32_t x = up * a.lower;
+        for (int k = kMaxDep - 1; k >= 0; k--)
+            if (k < (int)a.nR) { d[k] = k ? x % a.rad[k] : x; if (k) x /= a.rad[k]; } else d[k] = 0;
+        KeyT xj[U], f[U], g[U], m[4] = {Ops::sentinel(), Ops::sentinel(), Ops::sentinel(), Ops::sentinel()};
+        JointIdJ id[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const uint32_t c = min(tid + u * threads, Kj - 1);
+            uint64_t sg[M];
+            KeyT ef[M];
+#pragma unroll
+            for (int t = 0; t < M; t++) {
+                sg[t] = t < (int)a.s[1].ne ? glb<uint64_t>(a.s[1].e[t].sig_c)[c] : 0;
+                ef[t] = t < (int)a.s[1].ne ? glb<KeyT>(a.s[1].e[t].f_c)[c] : (KeyT)0;
+            }
+            id[u] = __builtin_bit_cast(JointIdJ, glb<uint64_t>(a.ij)[c]);
+            f[u] = shift_key(glb<KeyT>(a.fj_o)[c], shift);
+            g[u] = shift_key(glb<KeyT>(a.fj_y)[c], shift);
+            // without its configuration bits, in v_i's key space
+            xj[u] = shift_key((KeyT)(joint_sum<KeyT>(a.s[1], a.nR, c, glb<KeyT>(a.s[1].Lk)[c], sg, ef, d) - (KeyT)c), shift);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const KeyT xf = Ops::add(xj[u], f[u]), xy = Ops::add(xj[u], g[u]);
+            m[0] = Ops::min(m[0], xj[u]);
+            m[1] = Ops::min(m[1], xf);
+            m[2] = Ops::min(m[2], xy);
+            m[3] = Ops::min(m[3], Ops::add(xy, f[u]));
+            if (tid + u * threads >= Kj) continue;
+            lds_min(&mJ[id[u].own], xj[u]);
+            lds_min(&mJy[id[u].own], xy);
+            lds_min(&yJ[id[u].y], xj[u]);
+            lds_min(&yJf[id[u].y], xf);
+            lds_min(&bJ[id[u].both], xj[u]);
+        }
+        KeyT r[1];
+        wave_minima<4>(m, r);
+        if ((lane & 15) == 15) lds_min(&sl[lane >> 4], r[0]);
+        __syncthreads();
+        const KeyT s0 = lds_key<KeyT>(&sl[0]), s1 = lds_key<KeyT>(&sl[1]), s2 = lds_key<KeyT>(&sl[2]),
+                   s3 = lds_key<KeyT>(&sl[3]);
+        const Glb<KeyT> out = (Glb<KeyT>)(uintptr_t)a.half + up * stride;
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const uint32_t c = tid + u * threads;
+            if (c < Ki) {
+                const JointIdI ii = __builtin_bit_cast(JointIdI, glb<uint64_t>(a.ii)[c]);
+                const KeyT fi = shift_key(glb<KeyT>(a.fi_o)[c], shift);
+                KeyT j0 = Ops::min(s1, Ops::add(fi, s0)), j1 = Ops::min(s3, Ops::add(fi, s2));
+                if (ii.other != kNoClass) {
+                    j0 = Ops::min(j0, lds_key<KeyT>(&mJ[ii.other]));
+                    j1 = Ops::min(j1, lds_key<KeyT>(&mJy[ii.other]));
+                }
+                out[c] = j0;
+                out[Ki + c] = j1;
+            }
+            if (c < Kj) out[2 * (uint64_t)Ki + glb<uint16_t>(a.jplace)[c]] = xj[u];
+            if (c < Ky) {
+                const JointY y = a.y[c];
+                const bool in = y.j != kNoClass;
+                const Glb<KeyT> oy = out + 2 * (uint64_t)Ki + Kj + c;
+                oy[0] = in ? lds_key<KeyT>(&yJ[y.j]) : Ops::sentinel();
+                oy[Ky] = in ? lds_key<KeyT>(&yJf[y.j]) : Ops::sentinel();
+                oy[2 * (uint64_t)Ky] = y.pj != kNoClass ? lds_key<KeyT>(&bJ[y.pj]) : Ops::sentinel();
+            }
+        }
+    }
+}
+
+// Joint fill: workgroup b takes one upper index and every seg-th of its lower
+// ones, one row at a time; configurations over the threads, U per thread, so
+// a table row is stored contiguously and everything that does not depend on
+// the lower digits stays in registers and LDS.  XI goes to LDS in class order,
+// so a class's minimum is a thread's walk over a few neighbouring values;
+// three barriers per row (XI and its minima; class minima; those of XJ + I),
+// then the row's entries.  Bound by the LDS traffic, about 26 accesses per
+// configuration; on small vertices by the latency of the steps.
+//
+// Measured on the Transformer at p = 64: a cross-attention score vertex (7056
+// rows, 3.3e6 entries of 462 configurations) 68 us against 167 + 26 us for the
+// dense fill and its prep; the fourth decoder's key/value projection (38808
+// rows) 311 us against 613 + 162 us -- and the five tables these two kinds read,
+// 180 MB each, are not formed at all (level 0: 244 -> 21 us).  140 registers
+// instead of 80 (one workgroup per CU instead of three) took 131 and 654 us.
+template <typename KeyT, int U, bool HASE>
+__device__ __forceinline__ void joint_item(const JointArgs &a, uint32_t b, char *lds) {
+    using Ops = KeyOps<KeyT>;
+    using Val = typename Ops::Val;
+    constexpr int M = (int)kJointTerms;
+    const uint32_t tid = threadIdx.x, threads = blockDim.x, lane = tid & 63;
+    const uint32_t Ki = a.s[0].K, Kj = a.s[1].K, Ky = a.Ky, oi = a.oi, yi = a.yi, yj = a.yj;
+    // XCD-contiguous ranges of workgroups: the segments of one upper index
+    // read neighbouring lines of the lookups
+    const uint32_t w = (b % 8) * (a.nblk / 8) + b / 8, up = w / a.seg;
+    if (up >= a.upper) return;   // the whole workgroup leaves together
+    uint64_t *slots = (uint64_t *)lds;                       // [2][16] row minima, by row parity
+    KeyT *XO = (KeyT *)(slots + 32);                         // XI by own class
+    KeyT *CI0 = XO + Ki, *VV0 = CI0 + oi, *XJ = VV0 + yj;    // minima of XI by own class; of XJ + that by y class
+    KeyT *XY = XJ + Kj;                                      // [2] XI by y class, by row parity
+    KeyT *PA = XY + (HASE ? 2 * Ki : 0), *PB = PA + (HASE ? Ki : 0);      // P0, P1 by y class
+    KeyT *FO = PB + (HASE ? Ki : 0), *FY = FO + (HASE ? Ki : 0);          // f to y by own class, f to v_j by y class
+    KeyT *CI1 = FY + (HASE ? Ki : 0), *Q0 = CI1 + (HASE ? oi : 0), *Q1 = Q0 + (HASE ? yi : 0);
+    KeyT *A0 = Q1 + (HASE ? yi : 0), *A1 = A0 + (HASE ? yi : 0), *VV1 = A1 + (HASE ? yi : 0);
+    uint16_t *so = (uint16_t *)(VV1 + (HASE ? yj : 0)), *sy = so + oi + 1, *sj = sy + yi + 1, *jown = sj + yj + 1;
+
+    const int32_t shift = a.s[1].shift;
+    const Glb<const KeyT> half = glb<KeyT>(a.half) + up * (2 * (uint64_t)Ki + Kj + 3 * (uint64_t)Ky);
+    KeyT lk[U], fo[U], fy[U], j0[U], j1[U], ef[U][M];
+    uint64_t sg[U][M];
+    uint32_t po[U], py[U];
+    KeyT hI[U], hJ[U], b0[U], b1[U], bp[U];
+    JointY dy[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+        const uint32_t c = tid + u * threads, ci = min(c, Ki - 1), y = min(c, Ky - 1);
+        lk[u] = glb<KeyT>(a.s[0].Lk)[ci];
+        fo[u] = shift_key(glb<KeyT>(a.fi_o)[ci], shift);   // (the edge between the two is in v_j's keys)
+        fy[u] = HASE ? glb<KeyT>(a.fi_y)[ci] : (KeyT)0;
+        j0[u] = half[ci];
+        j1[u] = half[Ki + ci];
+        const JointIdI id = __builtin_bit_cast(JointIdI, glb<uint64_t>(a.ii)[ci]);
+        po[u] = id.own;
+        py[u] = id.yplace;
+#pragma unroll
+        for (int t = 0; t < M; t++) {
+            sg[u][t] = t < (int)a.s[0].ne ? glb<uint64_t>(a.s[0].e[t].sig_c)[ci] : 0;
+            ef[u][t] = t < (int)a.s[0].ne ? glb<KeyT>(a.s[0].e[t].f_c)[ci] : (KeyT)0;
+        }
+        hJ[u] = shift_key(glb<KeyT>(a.fj_yy)[y], shift);
+        hI[u] = HASE ? glb<KeyT>(a.fi_yy)[y] : (KeyT)0;
+        const Glb<const KeyT> hy = half + 2 * (uint64_t)Ki + Kj + y;
+        b0[u] = hy[0];
+        b1[u] = hy[Ky];
+        bp[u] = hy[2 * (uint64_t)Ky];
+        dy[u] = a.y[y];
+        if (c < Ki && HASE) {
+            FO[po[u]] = fy[u];
+            FY[py[u]] = fo[u];
+        }
+        if (c < Kj) {
+            XJ[c] = half[2 * (uint64_t)Ki + c];
+            jown[c] = glb<uint16_t>(a.jown)[c];
+        }
+    }
+    for (uint32_t k = tid; k <= oi; k += threads) so[k] = glb<uint16_t>(a.start_o)[k];
+    if (HASE)
+        for (uint32_t k = tid; k <= yi; k += threads) sy[k] = glb<uint16_t>(a.start_yi)[k];
+    for (uint32_t k = tid; k <= yj; k += threads) sj[k] = glb<uint16_t>(a.start_yj)[k];
+    if (tid < 32) slots[tid] = ~0ull;
+    const uint32_t bits = a.bits, out_shift = a.out_shift;
+    const Glb<Val> T = (Glb<Val>)(uintptr_t)a.T;
+    const Glb<uint16_t> A = (Glb<uint16_t>)(uintptr_t)a.A;
+    uint32_t parity = 0;
+    auto xi_of = [&](uint32_t row, KeyT (&xi)[U]) {
+        uint32_t d[kMaxDep];
+        uint32_t x = row;
+        for (int k = kMaxDep - 1; k >= 0; k--)
+            if (k < (int)a.nR) { d[k] = k ? x % a.rad[k] : x; if (k) x /= a.rad[k]; } else d[k] = 0;
+#pragma unroll
+        for (int u = 0; u < U; u++)   // (past the end: the last configuration again)
+            xi[u] = joint_sum<KeyT>(a.s[0], a.nR, min(tid + u * threads, Ki - 1), lk[u], sg[u], ef[u], d);
+    };
+    KeyT xi[U];
+    if (w % a.seg < a.lower) xi_of(up * a.lower + w % a.seg, xi);
+    __syncthreads();
+    for (uint32_t lowi = w % a.seg; lowi < a.lower; lowi += a.seg, parity ^= 1) {
+        const uint32_t row = up * a.lower + lowi;
+        uint64_t *sl = slots + 16 * parity;
+        KeyT *XYp = XY + (HASE ? parity * Ki : 0);
+        KeyT m[8];
+#pragma unroll
+        for (int k = 0; k < 8; k++) m[k] = Ops::sentinel();
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const KeyT p0 = Ops::add(xi[u], j0[u]), p1 = Ops::add(xi[u], j1[u]);
+            m[0] = Ops::min(m[0], xi[u]);
+            m[1] = Ops::min(m[1], Ops::add(xi[u], fo[u]));
+            m[2] = Ops::min(m[2], p0);
+            m[3] = Ops::min(m[3], p1);
+            XO[po[u]] = xi[u];
+            if (HASE) {
+                const KeyT xy = Ops::add(xi[u], fy[u]);
+                m[4] = Ops::min(m[4], xy);
+                m[5] = Ops::min(m[5], Ops::add(xy, fo[u]));
+                m[6] = Ops::min(m[6], Ops::add(p0, fy[u]));
+                m[7] = Ops::min(m[7], Ops::add(p1, fy[u]));
+                XYp[py[u]] = xi[u];
+                PA[py[u]] = p0;
+                PB[py[u]] = p1;
+            }
+        }
+        if (HASE) {
+            KeyT r[2];
+            wave_minima<8>(m, r);
+            if ((lane & 15) == 15) {
+                lds_min(&sl[2 * (lane >> 4)], r[0]);
+                lds_min(&sl[2 * (lane >> 4) + 1], r[1]);
+            }
+        } else {
+            KeyT r[1], m4[4] = {m[0], m[1], m[2], m[3]};
+            wave_minima<4>(m4, r);
+            if ((lane & 15) == 15) lds_min(&sl[lane >> 4], r[0]);
+        }
+        __syncthreads();
+        // the next row's minima (their last readers are past the barrier) and XI
+        if (tid < 16) slots[16 * (parity ^ 1) + tid] = ~0ull;
+        if (lowi + a.seg < a.lower) xi_of(row + a.seg, xi);
+        // class minima: a thread per class of either order
+        for (uint32_t k = tid; k < oi + (HASE ? yi : 0); k += threads) {
+            if (k < oi) {
+                KeyT v = Ops::sentinel(), v1 = Ops::sentinel();
+                for (uint32_t p = so[k]; p < so[k + 1]; p++) {
+                    const KeyT x = XO[p];
+                    v = Ops::min(v, x);
+                    if (HASE) v1 = Ops::min(v1, Ops::add(x, FO[p]));
+                }
+                CI0[k] = v;
+                if (HASE) CI1[k] = v1;
+            } else if (HASE) {
+                KeyT q0 = Ops::sentinel(), q1 = Ops::sentinel(), v = Ops::sentinel(), v1 = Ops::sentinel();
+                for (uint32_t p = sy[k - oi]; p < sy[k - oi + 1]; p++) {
+                    const KeyT x = XYp[p];
+                    v = Ops::min(v, x);
+                    v1 = Ops::min(v1, Ops::add(x, FY[p]));
+                    q0 = Ops::min(q0, PA[p]);
+                    q1 = Ops::min(q1, PB[p]);
+                }
+                Q0[k - oi] = q0;
+                Q1[k - oi] = q1;
+                A0[k - oi] = v;
+                A1[k - oi] = v1;
+            }
+        }
+        __syncthreads();
+        for (uint32_t k = tid; k < yj; k += threads) {
+            KeyT v = Ops::sentinel(), v1 = Ops::sentinel();
+            for (uint32_t p = sj[k]; p < sj[k + 1]; p++) {
+                const uint32_t o = jown[p];
+                if (o == kNoClass) continue;
+                const KeyT x = XJ[p];
+                v = Ops::min(v, Ops::add(x, CI0[o]));
+                if (HASE) v1 = Ops::min(v1, Ops::add(x, CI1[o]));
+            }
+            VV0[k] = v;
+            if (HASE) VV1[k] = v1;
+        }
+        __syncthreads();
+        KeyT s[8];
+#pragma unroll
+        for (int k = 0; k < (HASE ? 8 : 4); k++) s[k] = lds_key<KeyT>(&sl[k]);
+#pragma unroll
+        for (int u = 0; u < U; u++) {
+            const uint32_t y = tid + u * threads;
+            if (y >= Ky) break;
+            KeyT best = Ops::min(Ops::add(s[2], hJ[u]), s[3]);
+            const bool ni = HASE && dy[u].i != kNoClass, nj = dy[u].j != kNoClass;
+            if (HASE) best = Ops::min(Ops::add(best, hI[u]), Ops::min(Ops::add(s[6], hJ[u]), s[7]));
+            if (nj) {   // c' in y's class: XJ + I0, XJ + I1
+                KeyT v = Ops::min(VV0[dy[u].j], Ops::min(Ops::add(b1[u], s[0]), Ops::add(b0[u], s[1])));
+                if (HASE) v = Ops::add(v, hI[u]);
+                best = Ops::min(best, v);
+                if (HASE)
+                    best = Ops::min(best, Ops::min(VV1[dy[u].j], Ops::min(Ops::add(b1[u], s[4]), Ops::add(b0[u], s[5]))));
+            }
+            if (ni) {
+                best = Ops::min(best, Ops::min(Ops::add(Q0[dy[u].i], hJ[u]), Q1[dy[u].i]));
+                if (nj) {   // both in y's classes: t(c', c) one of the f, or 0
+                    best = Ops::min(best, Ops::min(Ops::add(A0[dy[u].i], b1[u]), Ops::add(A1[dy[u].i], b0[u])));
+                    for (uint32_t k = 0; k < dy[u].count; k++)
+                        best = Ops::min(best, Ops::add(XYp[dy[u].first + k], bp[u]));
+                }
+            }
+            Val v;
+            uint32_t cc;
+            Ops::split(best, bits, out_shift, v, cc);
+            const uint64_t idx = (uint64_t)row * Ky + y;
+            T[idx] = v;
+            A[idx] = (uint16_t)cc;
+        }
+    }
+}
+
+// The lowest optimal configuration of one entry of a vertex described by class
+// fill terms, by one wave: w[k] = the configurations of its layout digits (z
+// first when it has one).
+template <typename KeyT>
+__device__ __forceinline__ uint32_t lazy_argmin(const ClassArgs &a, const uint32_t (&w)[kMaxDep]) {
+    using Ops = KeyOps<KeyT>;
+    using Val = typename Ops::Val;
+    constexpr int U = 4;   // configurations in flight per lane
+    const uint32_t lane = threadIdx.x & 63, z = a.has_z ? 1 : 0, K = a.K;
+    KeyT best = Ops::sentinel();
+    for (uint32_t c0 = lane; c0 < K; c0 += 64 * U) {
+        KeyT x[U];
+#pragma unroll
+        for (int u = 0; u < U; u++) x[u] = glb<KeyT>(a.Lk)[min(c0 + 64 * u, K - 1)];
+        auto edge = [&](const uint64_t *sc, const uint64_t *so, const void *fc, const void *fo, uint32_t o) {
+            const uint64_t s = glb<uint64_t>(so)[o];
+            const KeyT f = glb<KeyT>(fo)[o];
+            uint64_t sg[U];
+            KeyT fg[U];
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const uint32_t c = min(c0 + 64 * u, K - 1);
+                sg[u] = glb<uint64_t>(sc)[c];
+                fg[u] = glb<KeyT>(fc)[c];
+            }
+#pragma unroll
+            for (int u = 0; u < U; u++) x[u] = Ops::add(x[u], sg[u] == s ? (KeyT)0 : Ops::min(f, fg[u]));
+        };
+        if (z) edge(a.sig_zc, a.sig_zo, a.fzc, a.fzo, w[0]);
+        for (uint32_t t = 0; t < a.ne; t++) {
+            uint32_t o = 0;
+            for (int k = 0; k < kMaxDep; k++) o = k == (int)(z + a.e[t].dig) ? w[k] : o;
+            edge(a.e[t].sig_c, a.e[t].sig_o, a.e[t].f_c, a.e[t].f_o, o);
+        }
+        for (uint32_t t = 0; t < a.nt; t++) {
+            uint64_t o = 0;
+            for (int k = 0; k < kMaxDep; k++)
+                if (k >= (int)z && k - (int)z < (int)a.nR) o += (uint64_t)w[k] * a.t[t].sd[k - z];
+            KeyT tv[U];
+#pragma unroll
+            for (int u = 0; u < U; u++)
+                tv[u] = __builtin_bit_cast(KeyT, glb<Val>(a.t[t].ptr)[o + (uint64_t)min(c0 + 64 * u, K - 1) * a.t[t].sc]);
+#pragma unroll
+            for (int u = 0; u < U; u++) x[u] = Ops::add(x[u], tv[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; u++) best = Ops::min(best, x[u]);
+    }
+    for (uint32_t m = 32; m > 0; m >>= 1) best = Ops::min(best, shfl_xor_key(best, (int)m));
+    Val v;
+    uint32_t cc;
+    Ops::split(best, a.bits, 0, v, cc);
+    return cc;
 }
 
 }  // namespace pase

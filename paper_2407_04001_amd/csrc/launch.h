@@ -25,20 +25,23 @@ struct Launch {
     DirectArgs da;
     bool cls = false;      // class fill (no prep)
     ClassArgs ca;
+    bool joint = false;    // joint fill
+    JointArgs ja;
 };
 
 // A batched launch: vertices (sequence positions) sharing one kernel variant
 // within one launch group, with their first workgroups.
 struct Batch {
-    enum Kind { kPrep, kRows, kGeneric, kReduce, kDirect, kClass } kind;
+    enum Kind { kPrep, kRows, kGeneric, kReduce, kDirect, kClass, kHalf, kJoint } kind;
     int lane;              // bulk lane schedule: the stream it runs on (0 = the caller's)
     int group;             // launch group (a slot, or a (slot, lane) pair) it belongs to
     uint32_t variant;      // rows: (TZ * 4 + TM) * 8 + NA (NA 7 = runtime count); generic: NT (0 = runtime);
-                           // class: threads per workgroup
+                           // class, half, joint: threads per workgroup;
+                           // class + 1: more than two edges or lookups, joint + 1: two configurations per thread
     uint32_t entry0;       // first BatchEntry of this batch
     uint32_t nentries;
     uint32_t blocks;       // workgroups of the launch
-    uint32_t lds = 0;      // class fills: dynamic LDS of the launch
+    uint32_t lds = 0;      // class and joint fills: dynamic LDS of the launch
     uint32_t pos0 = 0;     // first member
     bool side = false;     // a hoisted prep launch: on the side stream, after the work enqueued before it
 };

@@ -139,7 +139,109 @@ pase_status build_launches(pase_graph_t g, char *ws, std::vector<Launch<KeyT>> &
             L.prep.total += bk.elems;
             return (int)L.prep.nblocks++;
         };
-        if (vp.classes) {
+        // the two ends' element offsets of an edge of vertex `me`: its own, the other's
+        auto edge_ends = [&](int e, int me, uint64_t &oc, uint64_t &oo) {
+            const bool is_src = (int)g->E[e].src == me;
+            const uint64_t s0 = soff[e], d0 = s0 + g->K[g->E[e].src];
+            oc = is_src ? s0 : d0;
+            oo = is_src ? d0 : s0;
+        };
+        if (vp.joint >= 0) {
+            if constexpr (sizeof(KeyT) != 8) {
+                return fail(g, PASE_ERR_INTERNAL, "joint fill with 128-bit keys");
+            } else {
+                const VPlan &vj = P.v[vp.joint];
+                JointArgs &ja = L.ja;
+                std::memset(&ja, 0, sizeof ja);
+                const uint64_t *sig = (const uint64_t *)(ws + P.off_sig);
+                const KeyT *fk = (const KeyT *)(ws + P.off_fk), *Lk = (const KeyT *)(ws + P.off_Lk);
+                auto rest_digit = [&](int u) { return (uint32_t)(std::find(vp.R.begin(), vp.R.end(), u) - vp.R.begin()); };
+                ja.Ky = g->K[vp.z];
+                ja.bits = vp.bits;
+                ja.out_shift = vp.out_shift;
+                ja.upper = (uint32_t)vp.jupper;
+                ja.lower = (uint32_t)(vp.MR / vp.jupper);
+                ja.nR = (uint32_t)vp.R.size();
+                for (size_t k = 0; k < vp.R.size(); k++) ja.rad[k] = g->K[vp.R[k]];
+                for (int sd = 0; sd < 2; sd++) {
+                    const VPlan &v = sd ? vj : vp;
+                    JointSide &s = ja.s[sd];
+                    const int other = sd ? vp.vi : vj.vi;
+                    s.K = v.K;
+                    s.shift = (int32_t)vp.bits - (int32_t)v.bits;
+                    s.Lk = Lk + koff[v.vi];
+                    for (int e : v.edges) {
+                        const int u = (int)g->E[e].src == v.vi ? (int)g->E[e].dst : (int)g->E[e].src;
+                        uint64_t oc, oo;
+                        edge_ends(e, v.vi, oc, oo);
+                        if (u == other) {   // (one of v_j's edges: v_j comes first)
+                            ja.fj_o = fk + oc;
+                            ja.fi_o = fk + oo;
+                            continue;
+                        }
+                        if (u == vp.z) {
+                            (sd ? ja.fj_y : ja.fi_y) = fk + oc;
+                            (sd ? ja.fj_yy : ja.fi_yy) = fk + oo;
+                            continue;
+                        }
+                        if (s.ne >= kJointTerms || rest_digit(u) >= ja.nR) return fail(g, PASE_ERR_INTERNAL, "joint edges");
+                        ClassEdge &ce = s.e[s.ne++];
+                        ce.sig_c = sig + oc;
+                        ce.sig_o = sig + oo;
+                        ce.f_c = fk + oc;
+                        ce.f_o = fk + oo;
+                        ce.dig = rest_digit(u);
+                    }
+                    for (const auto &t : v.terms) {
+                        if (t.j == vp.joint) continue;
+                        if (s.nt >= kJointTerms) return fail(g, PASE_ERR_INTERNAL, "joint lookups");
+                        ClassTerm &ct = s.t[s.nt++];
+                        // strides by v's plan digits, then by v_i's rest digits
+                        uint32_t sdv[kMaxDep], vrad[kMaxDep];
+                        lookup_strides(P, sd ? vp.joint : i, t.j, ct.sc, sdv);
+                        for (size_t k = 0; k < v.layout.size(); k++) vrad[k] = g->K[v.layout[k]];
+                        if (max_index(v.K, ct.sc, sdv, vrad, (int)v.layout.size()) >= P.v[t.j].N) bounds_ok = false;
+                        ct.ptr = ws + P.off_T + P.v[t.j].T_off;
+                        for (size_t k = 0; k < v.layout.size(); k++) {
+                            if (!sdv[k]) continue;
+                            const uint32_t r = rest_digit(v.layout[k]);
+                            if (r >= ja.nR) return fail(g, PASE_ERR_INTERNAL, "joint lookup digit");
+                            ct.sd[r] = sdv[k];
+                        }
+                    }
+                }
+                const DevJointTab &jt = P.jtabs[vp.jshape];
+                ja.ii = (const JointIdI *)(ws + jt.off_i);
+                ja.ij = (const JointIdJ *)(ws + jt.off_j);
+                ja.y = (const JointY *)(ws + jt.off_y);
+                ja.start_o = (const uint16_t *)(ws + jt.off_start[0]);
+                ja.start_yi = (const uint16_t *)(ws + jt.off_start[1]);
+                ja.start_yj = (const uint16_t *)(ws + jt.off_start[2]);
+                ja.jown = (const uint16_t *)(ws + jt.off_jown);
+                ja.jplace = (const uint16_t *)(ws + P.ctabs[vp.jtab[1]].inv_off);
+                ja.yi = vp.jcls[0];
+                ja.yj = vp.jcls[1];
+                ja.oj = vp.jcls[2];
+                ja.oi = vp.jcls[3];
+                ja.has_e = ja.fi_y != nullptr;
+                if (!ja.fj_y || !ja.fi_o) return fail(g, PASE_ERR_INTERNAL, "joint edge");
+                ja.half = blocks;
+                boff = joint_half_elems(vp.K, vj.K, ja.Ky) * ja.upper;
+                ja.T = ws + P.off_T + vp.T_off;
+                ja.A = (uint16_t *)(ws + P.off_A + vp.A_off);
+                const uint32_t most = std::max(std::max(vp.K, vj.K), ja.Ky);
+                ja.threads = std::min<uint32_t>(512, (most + 63) / 64 * 64);
+                if (most > kJointMaxK || (uint64_t)ja.threads * 2 < most) return fail(g, PASE_ERR_INTERNAL, "joint size");
+                ja.lds = (uint32_t)joint_lds(vp.K, vj.K, ja.oi, ja.yi, ja.yj, ja.has_e);
+                ja.hlds = (uint32_t)half_lds(vj.K, ja.oj, ja.yj);
+                if (ja.lds > kJointMaxLds || ja.hlds > kJointMaxLds) return fail(g, PASE_ERR_INTERNAL, "joint fill LDS");
+                // segments: about 2048 workgroups (each brings its upper index's half table in), or one per row
+                ja.seg = (uint32_t)std::max<uint64_t>(1, std::min<uint64_t>(ja.lower, 2048 / ja.upper));
+                ja.nblk = (uint32_t)(((uint64_t)ja.upper * ja.seg + 7) / 8 * 8);
+                ja.hblk = std::min<uint32_t>(ja.upper, 1024);
+                L.joint = true;
+            }
+        } else if (vp.classes) {
             if constexpr (sizeof(KeyT) != 8) {
                 return fail(g, PASE_ERR_INTERNAL, "class fill with 128-bit keys");
             } else {
@@ -158,24 +260,19 @@ pase_status build_launches(pase_graph_t g, char *ws, std::vector<Launch<KeyT>> &
                 ca.keep = vp.keep;
                 ca.staged = vp.lr >= kClassStagedRows;
                 ca.nblk = (uint32_t)((((vp.MR + (1u << vp.lr) - 1) >> vp.lr) + 7) / 8 * 8);
-                // the two ends' signatures and f arrays of an edge: v_i's, the other's
-                auto ends = [&](int e, uint64_t &oc, uint64_t &oo) {
-                    const bool is_src = (int)g->E[e].src == vp.vi;
-                    const uint64_t s0 = soff[e], d0 = s0 + g->K[g->E[e].src];
-                    oc = is_src ? s0 : d0;
-                    oo = is_src ? d0 : s0;
-                };
                 const uint64_t *sig = (const uint64_t *)(ws + P.off_sig);
                 const KeyT *fk = (const KeyT *)(ws + P.off_fk);
                 bool zdone = vp.z < 0;
                 for (int e : vp.edges) {
                     uint64_t oc, oo;
-                    ends(e, oc, oo);
+                    edge_ends(e, vp.vi, oc, oo);
                     if (other_of(e) == vp.z) {
                         if (zdone || vp.ctab < 0) return fail(g, PASE_ERR_INTERNAL, "class edge");
                         zdone = true;
                         ca.fzc = fk + oc;
                         ca.fzo = fk + oo;
+                        ca.sig_zc = sig + oc;
+                        ca.sig_zo = sig + oo;
                         ca.inv = (const uint16_t *)(ws + P.ctabs[vp.ctab].inv_off);
                         ca.zs = (const ClassEntry *)(ws + P.ctabs[vp.ctab].zs_off);
                         continue;
@@ -551,6 +648,11 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         b.A = (const uint16_t *)(ws + P.off_A + vp.A_off);
         b.vi = (uint32_t)vp.vi;
         b.K = vp.K;
+        b.pos = (uint32_t)i;
+        // a vertex whose table is not formed: one evaluation of its terms
+        if (vp.absorbed >= 0 && !g->keep_tables)
+            b.lazy = (const ClassArgs *)(ws + P.off_desc + (uint64_t)n * (sizeof(PrepArgs) + sizeof(RowsArgs) +
+                                         sizeof(GenericArgs) + sizeof(ReduceArgs) + sizeof(DirectArgs))) + i;
         b.m = (uint32_t)vp.layout.size();
         for (size_t k = 0; k < vp.layout.size(); k++) {
             b.dig[k] = (uint32_t)vp.layout[k];
@@ -567,7 +669,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
     // ---- kernel descriptors: per position, one of each kind
     const uint64_t desc_bytes =
         (uint64_t)n * (sizeof(PrepArgs) + sizeof(RowsArgs) + sizeof(GenericArgs) + sizeof(ReduceArgs) + sizeof(DirectArgs) +
-                      sizeof(ClassArgs));
+                      sizeof(ClassArgs) + sizeof(JointArgs));
     if ((st = region(P.off_desc, desc_bytes, P.off_batch, "descriptors")) != PASE_OK) return st;
     PrepArgs *hp = (PrepArgs *)(img + P.off_desc);
     RowsArgs *hr = (RowsArgs *)(hp + n);
@@ -575,6 +677,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
     ReduceArgs *hd = (ReduceArgs *)(hg + n);
     DirectArgs *hx = (DirectArgs *)(hd + n);
     ClassArgs *hc = (ClassArgs *)(hx + n);
+    JointArgs *hj = (JointArgs *)(hc + n);
     for (int i = 0; i < n; i++) {
         hp[i] = launches[i].prep;
         hr[i] = launches[i].ra;
@@ -582,9 +685,12 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         hd[i] = launches[i].red;
         hx[i] = launches[i].da;
         hc[i] = launches[i].ca;
+        hj[i] = launches[i].ja;
     }
     if (!P.ctabs.empty()) {
-        if ((st = region(P.off_ctdesc, P.ctabs.size() * sizeof(DevClassTab), P.off_zero, "class tables")) != PASE_OK) return st;
+        if ((st = region(P.off_ctdesc, P.ctabs.size() * sizeof(DevClassTab), P.off_jtdesc, "class tables")) != PASE_OK) return st;
+        if ((st = region(P.off_jtdesc, P.jtabs.size() * sizeof(DevJointTab), P.off_zero, "joint tables")) != PASE_OK) return st;
+        if (!P.jtabs.empty()) std::memcpy(img + P.off_jtdesc, P.jtabs.data(), P.jtabs.size() * sizeof(DevJointTab));
         DevClassTab *ht = (DevClassTab *)(img + P.off_ctdesc);
         for (size_t k = 0; k < P.ctabs.size(); k++) {
             ht[k] = P.ctabs[k];
@@ -613,6 +719,8 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         Batch b{kind, cur_lane, cur_group, variant, nbe, 0, 0};
         b.pos0 = (uint32_t)members[0];
         for (int i : members) {
+            if (kind == Batch::kJoint) b.lds = std::max(b.lds, launches[i].ja.lds);
+            if (kind == Batch::kHalf) b.lds = std::max(b.lds, launches[i].ja.hlds);
             if (kind == Batch::kClass) b.lds = std::max(b.lds, launches[i].ca.lds);
             if (nbe >= be_cap) { be_overflow = true; return; }
             hbe[nbe].pos = (uint32_t)i;
@@ -626,7 +734,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         si.batches.push_back(b);
     };
     // per-group scratch, reused across groups (cleared, capacity kept)
-    std::vector<int> prepped, direct, cls, grp;
+    std::vector<int> prepped, direct, cls, joint, half, grp;
     std::vector<std::pair<uint32_t, int>> rows, gens, reds;
     std::map<uint32_t, int> shape_dom;   // TZ * 4 + TM -> largest vertex of the group
     constexpr bool kF64 = std::is_same<KeyT, double>::value;
@@ -637,13 +745,13 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
     si.group_waits.assign(si.groups.size(), {});
     if (si.hoist)
         for (int i = 0; i < n; i++)
-            if (P.v[i].prep_after >= -1) hoist_after[(size_t)(P.v[i].prep_after + 1)].push_back(i);
+            if (P.v[i].prep_after >= -1 && P.v[i].joint < 0) hoist_after[(size_t)(P.v[i].prep_after + 1)].push_back(i);
     // with lanes: a hoisted prep is a prep batch of its own at the end of the
     // group (prep_after, lane of the tables it reads)
     std::vector<std::vector<int>> lane_hoist_at(si.groups.size());   // group -> positions
     if (si.lane_hoist)
         for (int i = 0; i < n; i++)
-            if (P.v[i].prep_after >= 0)
+            if (P.v[i].prep_after >= 0 && P.v[i].joint < 0)
                 lane_hoist_at[(size_t)P.v[i].prep_after * nl + P.v[i].prep_lane].push_back(i);
     const bool hoisting = si.hoist || si.lane_hoist;
     auto add_side = [&](size_t k) {
@@ -661,20 +769,58 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         prepped.clear();
         direct.clear();
         cls.clear();
+        joint.clear();
+        half.clear();
         // a fused minimum's blocks are built with its producer's, before the
         // producer's fill reads them; its own fill is a reduction (below)
         std::vector<int> fills;   // members with a prep here or hoisted: rows / generic fills
         for (int i : mem) {
+            // (the half fill of a joint fill carries that fill's position)
+            if (P.v[i].absorbed >= 0) {
+                if (P.v[P.v[i].absorbed].jearly) half.push_back(P.v[i].absorbed);
+                if (!g->keep_tables) continue;   // no table of its own
+            }
+            if (launches[i].joint) {
+                joint.push_back(i);
+                if (!P.v[i].jearly) half.push_back(i);
+                continue;
+            }
             if (launches[i].cls) cls.push_back(i);
             else if (launches[i].direct) direct.push_back(i);
             else if (!launches[i].fused) (hoisting && P.v[i].prep_after >= -1 ? fills : prepped).push_back(i);
             if (P.v[i].fuse_into >= 0) prepped.push_back(P.v[i].fuse_into);
         }
         add_batch(Batch::kDirect, 0, direct, [](const Launch<KeyT> &L) { return L.da.nblk; });
-        uint32_t cls_threads = 256;
-        for (int i : cls) cls_threads = std::max(cls_threads, P.v[i].threads);
-        add_batch(Batch::kClass, cls_threads, cls, [](const Launch<KeyT> &L) { return L.ca.nblk; });
+        // class fills: one launch for the vertices of at most two edges and two
+        // lookups, one for the others
+        for (uint32_t many = 0; many < 2; many++) {
+            uint32_t threads = 256;
+            grp.clear();
+            for (int i : cls)
+                if ((launches[i].ca.ne > 2 || launches[i].ca.nt > 2) == (many == 1)) {
+                    grp.push_back(i);
+                    threads = std::max(threads, P.v[i].threads);
+                }
+            add_batch(Batch::kClass, threads + many, grp, [](const Launch<KeyT> &L) { return L.ca.nblk; });
+        }
         add_batch(Batch::kPrep, 0, prepped, [](const Launch<KeyT> &L) { return L.prep.nwg; });
+        uint32_t half_threads = 64;
+        for (int i : half) half_threads = std::max(half_threads, launches[i].ja.threads);
+        add_batch(Batch::kHalf, half_threads, half, [](const Launch<KeyT> &L) { return L.ja.hblk; });
+        // joint fills: one launch for one configuration per thread, one for two
+        for (uint32_t two = 0; two < 2; two++) {
+            uint32_t threads = 64;
+            grp.clear();
+            for (int i : joint) {
+                const JointArgs &ja = launches[i].ja;
+                const uint32_t most = std::max(std::max(ja.s[0].K, ja.s[1].K), ja.Ky);
+                if ((most > ja.threads) == (two == 1)) {
+                    grp.push_back(i);
+                    threads = std::max(threads, ja.threads);
+                }
+            }
+            add_batch(Batch::kJoint, threads + two, grp, [](const Launch<KeyT> &L) { return L.ja.nblk; });
+        }
         prepped.insert(prepped.end(), fills.begin(), fills.end());
         rows.clear();
         gens.clear();
@@ -802,7 +948,7 @@ pase_status plan_check(pase_graph_t g, uint64_t *image_bytes) {
     // every vertex appears in exactly one fill batch (direct, row or generic)
     std::vector<int> fills(g->plan.v.size(), 0);
     const BatchEntry *be = (const BatchEntry *)(img.data() + g->plan.off_batch);
-    std::vector<int> prep_batch(g->plan.v.size(), -1), fill_batch(g->plan.v.size(), -1);
+    std::vector<int> prep_batch(g->plan.v.size(), -1), fill_batch(g->plan.v.size(), -1), half_batch(g->plan.v.size(), -1);
     for (size_t bi = 0; bi < si.batches.size(); bi++) {
         const Batch &b = si.batches[bi];
         for (uint32_t k = 0; k < b.nentries; k++) {
@@ -810,12 +956,13 @@ pase_status plan_check(pase_graph_t g, uint64_t *image_bytes) {
             if (pos >= fills.size()) return fail(g, PASE_ERR_INTERNAL, "batch entry out of range");
             const bool fused = g->plan.v[pos].fused_from >= 0;
             if (b.kind == Batch::kRows || b.kind == Batch::kGeneric || b.kind == Batch::kDirect ||
-                b.kind == Batch::kClass ||
+                b.kind == Batch::kClass || b.kind == Batch::kJoint ||
                 (b.kind == Batch::kReduce && fused)) {
                 fills[pos]++;
                 fill_batch[pos] = (int)bi;
             }
             if (b.kind == Batch::kPrep) prep_batch[pos] = (int)bi;
+            if (b.kind == Batch::kHalf) half_batch[pos] = (int)bi;
         }
     }
     // every vertex with blocks has them built before its fill; a hoisted
@@ -823,7 +970,7 @@ pase_status plan_check(pase_graph_t g, uint64_t *image_bytes) {
     // waited for by the vertex's group
     for (size_t i = 0; i < g->plan.v.size(); i++) {
         const VPlan &vp = g->plan.v[i];
-        if (vp.kernel == kDirect || vp.classes || vp.fused_from >= 0) continue;
+        if (vp.kernel == kDirect || vp.classes || vp.joint >= 0 || vp.fused_from >= 0) continue;
         if (prep_batch[i] < 0 || prep_batch[i] > fill_batch[i])
             return fail(g, PASE_ERR_INTERNAL, "a prep does not precede its fill");
         if (si.hoist && vp.prep_after >= -1) {
@@ -848,14 +995,29 @@ pase_status plan_check(pase_graph_t g, uint64_t *image_bytes) {
             if (b.lane != vp.prep_lane || b.group != vp.prep_after * kLanes + vp.prep_lane)
                 return fail(g, PASE_ERR_INTERNAL, "a hoisted prep is not on its lane");
             bool waited = vp.prep_lane == vp.lane;
-            for (const auto &t : vp.terms) {
-                const VPlan &pj = g->plan.v[t.j];
-                if (pj.slot <= vp.prep_after && pj.lane == vp.prep_lane && fill_batch[t.j] > prep_batch[i])
+            for (int j : vp.reads) {
+                const VPlan &pj = g->plan.v[j];
+                if (pj.slot <= vp.prep_after && pj.lane == vp.prep_lane && fill_batch[j] > prep_batch[i])
                     return fail(g, PASE_ERR_INTERNAL, "a hoisted prep runs before the tables it reads");
                 waited |= pj.lane == vp.prep_lane && pj.slot >= vp.prep_after;
             }
             if (!waited) return fail(g, PASE_ERR_INTERNAL, "a hoisted prep on another lane is not waited for");
         }
+    }
+    // every table a launch reads is filled before it, in an earlier slot (a
+    // joint fill reads the other vertex's half fill, that one its lookups)
+    for (size_t i = 0; i < g->plan.v.size(); i++) {
+        const VPlan &vp = g->plan.v[i];
+        if (fill_batch[i] < 0) continue;
+        if (vp.joint >= 0 && (half_batch[i] < 0 || half_batch[i] >= fill_batch[i]))
+            return fail(g, PASE_ERR_INTERNAL, "a half fill does not precede its joint fill");
+        for (int j : vp.reads)
+            if (j != vp.joint && (fill_batch[j] < 0 || fill_batch[j] >= fill_batch[i] || g->plan.v[j].slot >= vp.slot))
+                return fail(g, PASE_ERR_INTERNAL, "a table is read before it is filled");
+        if (vp.joint >= 0)
+            for (const auto &t : g->plan.v[vp.joint].terms)
+                if (fill_batch[t.j] < 0 || fill_batch[t.j] >= half_batch[i])
+                    return fail(g, PASE_ERR_INTERNAL, "a half fill reads a table before it is filled");
     }
     // a fused minimum: its blocks are built before its producer's fill, and its
     // reduction comes after that fill
@@ -865,8 +1027,8 @@ pase_status plan_check(pase_graph_t g, uint64_t *image_bytes) {
         if (prep_batch[i] < 0 || fill_batch[j] < 0 || prep_batch[i] > fill_batch[j] || fill_batch[i] < fill_batch[j])
             return fail(g, PASE_ERR_INTERNAL, "fused minimum out of order");
     }
-    for (int f : fills)
-        if (f != 1) return fail(g, PASE_ERR_INTERNAL, "a vertex is not filled exactly once");
+    for (size_t i = 0; i < fills.size(); i++)
+        if (fills[i] != (g->plan.v[i].absorbed >= 0 && !g->keep_tables ? 0 : 1)) return fail(g, PASE_ERR_INTERNAL, "a vertex is not filled exactly once");
     *image_bytes = bytes;
     return PASE_OK;
 }

@@ -119,3 +119,114 @@ def test_shapes_every_entry(shape, key):
         if keep:
             for i, v in enumerate(o.sequence()):
                 assert pg.fingerprint(v) == o.fingerprint(i), (v, pg.vertex_info(v))
+
+
+# ------------------------------------------------------------------ joint fill
+def triangle(di, dj, dy, has_e, looks, perm=False, r=1, upper=2):
+    """v_j (1) joined to v_i (2), y (3) and an upper digit (4); v_i joined to y
+    (has_e) and, twice, to a lower digit (5), so that no digit of v_i meets it
+    in one edge alone; the digits joined to each other.  looks: a vertex (0)
+    whose table over (v_j, the upper digit) v_j looks up, and the edge j-upper
+    left out.  Without has_e there is no upper digit either (v_i would come
+    first).  The order is (0,) v_j, v_i, ..."""
+    b = _Builder("triangle", 4, comm_weight=r)
+    dims = (2, dj, di, dy, upper, 1)
+    for k, d in enumerate(dims):
+        if k == 0 and not looks:
+            b.vertex("pad", [3], ["x0"], [], 1)
+            continue
+        b.vertex(f"v{k}", [12 + k] * d, [f"x{i}" for i in range(d)], [d - 1] if d > 2 else [], 1)
+
+    def edge(u, v, elems, free=0):
+        rank = min(dims[u] if u or looks else 1, dims[v]) - free
+        d = list(range(max(1, rank)))
+        b.edge(u, v, d, d[::-1] if perm else d, elems=elems)
+    edge(1, 2, 40)
+    edge(1, 3, 24)
+    if has_e:
+        edge(2, 3, 33)
+    edge(2, 5, 5)
+    edge(2, 5, 9)
+    if has_e and not looks:
+        edge(1, 4, 17)
+    for u, v in ((3, 4), (3, 5), (4, 5)):
+        b.edge(u, v, [0], [0], elems=11)
+    if looks:
+        edge(0, 1, 21)
+        if has_e:
+            edge(0, 4, 6)
+    else:
+        b.edge(0, 5, [0], [0], elems=3)
+    return b.done()
+
+
+# (dims of v_i, v_j, y; edge from v_i to y; v_j looks a table up; permuted maps; p, every integer): K 35 to
+# 252 on one configuration per thread, 700 and more on two; classes of one and of several configurations
+TRIANGLES = [(4, 4, 4, True, False, False, 8, False), (4, 4, 4, True, True, True, 16, False),
+             (5, 4, 4, True, False, True, 16, False), (4, 5, 4, True, True, False, 16, False),
+             (4, 4, 3, False, False, True, 16, False), (4, 4, 3, False, True, False, 32, False),
+             (3, 4, 4, True, False, False, 12, True), (4, 4, 3, False, True, True, 10, True),
+             (5, 4, 5, True, True, True, 32, False), (3, 2, 2, False, False, True, 64, True),
+          (3, 2, 2, True, False, False, 60, True)]
+
+
+@pytest.mark.parametrize("case", range(len(TRIANGLES)))
+def test_joint_plan(case):
+    """Every triangle plans v_i as a joint fill (a class form column digit y,
+    found in a lookup), under every schedule, tables kept and not; the launch
+    plan checks; a smaller workspace without v_j's table."""
+    from paper_2407_04001_amd import pase as P
+    P.load()
+    di, dj, dy, has_e, looks, perm, p, every = TRIANGLES[case]
+    g = triangle(di, dj, dy, has_e, looks, perm, upper=1 if p > 48 else 2)
+    pg = P.Graph(g)
+    pg.set_option(P.OPT_DIRECT_CELLS, 1)
+    pg.enumerate_configs(p, all_integers=every)
+    x = pg.vertex_info(2)
+    assert (x["kernel"], x["column"], x["tile_cols"]) == (1, 3, 0) and x["lookups"] >= 1, x
+    assert 2 in pg.dependent_set(1) and 3 in pg.dependent_set(1) and 3 in pg.dependent_set(2)
+    for sched in (0, 1, 4, 5):
+        for hoist in (0, 1 << 20):
+            pg.set_option(P.OPT_SCHEDULE, sched)
+            pg.set_option(P.OPT_HOIST_ELEMS, hoist)
+            pg.set_option(P.OPT_KEEP_TABLES, 1)
+            assert pg.plan_check() > 0
+            kept = pg.workspace_size()
+            pg.set_option(P.OPT_KEEP_TABLES, 0)
+            assert pg.plan_check() > 0 and pg.workspace_size() <= kept
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("key", [0, 1])
+@pytest.mark.parametrize("case", range(len(TRIANGLES)))
+def test_joint_every_table(case, key):
+    """Joint fills against the oracle: every table with tables kept, and the
+    strategy with v_j's table left out (its argmin evaluated afterwards), under
+    each schedule, with the half fill in its own slot or just before the fill,
+    and through the allocation-free entry point."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_04001_amd import pase as P
+    from oracle.oracle import Oracle
+    di, dj, dy, has_e, looks, perm, p, every = TRIANGLES[case]
+    g = triangle(di, dj, dy, has_e, looks, perm, upper=1 if p > 48 else 2)
+    print(f"joint fill {TRIANGLES[case]} key={key}", flush=True)
+    o = Oracle(g)
+    o.configs(p, all_integers=every)
+    o.solve(threads=os.cpu_count() or 1)
+    pg = P.Graph(g)
+    pg.set_option(P.OPT_DIRECT_CELLS, 1)
+    pg.enumerate_configs(p, all_integers=every)
+    pg.set_option(P.OPT_KEY_TYPE, key)
+    for sched, hoist in ((5, 1 << 20), (0, 1 << 20), (1, 1 << 20), (5, 0)):
+        pg.set_option(P.OPT_SCHEDULE, sched)
+        pg.set_option(P.OPT_HOIST_ELEMS, hoist)
+        for keep in (1, 0):
+            pg.set_option(P.OPT_KEEP_TABLES, keep)
+            assert pg.find_best_strategy() == o.result(), (sched, hoist, keep)
+            if keep:
+                for i, v in enumerate(o.sequence()):
+                    assert pg.fingerprint(v) == o.fingerprint(i), (v, sched, hoist)
+    if pg.workspace_size() <= P.NOALLOC_WORKSPACE_BYTES:
+        assert P.pase_find_best_strategy_noalloc(pg.h, pg.nv) == o.result()
