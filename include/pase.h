@@ -119,14 +119,15 @@ typedef enum {
                                    2: only the row kernel's launches with a column chunk per lane
                                    (the dominant kernel; fewer events, so less overhead) */
     PASE_OPT_SCHEDULE = 6,      /* 5 (default): split chains -- the leaves (dependency level 0)
-                                   share their kernel launches on a stream of their own; after
+                                   share their kernel launches on the caller's stream; after
                                    them every row-kernel vertex whose planned fill takes at least
                                    PASE_OPT_BULK_US, with every vertex reading its table, runs on
-                                   that stream level by level, and all other vertices level by
-                                   level on the caller's stream at the highest wave priority;
-                                   events only where a table is read across the two, so the chain
-                                   of small vertices and the chain of large fills never wait for
-                                   each other level by level.  0: vertices of one dependency level
+                                   that stream level by level (lane 1), and all other vertices
+                                   level by level on a side stream at the highest wave priority
+                                   (lane 0); events only where a table is read across the two, so
+                                   the chain of small vertices and the chain of large fills never
+                                   wait for each other level by level.  Without such a fill after
+                                   the leaves everything runs on the caller's stream.  0: vertices of one dependency level
                                    (whose tables do not read each other) share their kernel
                                    launches, one stream, table memory packed by lifetimes.  1: one
                                    vertex at a time in sequence order (same packing).  4: bulk
@@ -390,8 +391,8 @@ typedef struct {
     uint32_t parts;      /* row kernel: waves sharing one tile's c range (1, 2 or 4) */
     double fill_ms;      /* PASE_OPT_PROFILE: event time of this vertex's fill kernel */
     uint32_t level;      /* dependency level: 1 + the largest level of the tables it reads */
-    uint32_t lane;       /* bulk lane schedule: the stream it runs on: 0 = the caller's (small vertices,
-                            highest wave priority), 1 = the bulk stream (large fills and their readers) */
+    uint32_t lane;       /* schedules 4 and 5: the lane it runs on: 0 = small vertices (highest wave
+                            priority), 1 = large fills and their readers, and the leaves under 5 */
     uint64_t key_bound;  /* upper bound of every summed cost before the min over c (keys stay
                             below (key_bound + 1) * 2^ceil(log2 K_v)); ~0 if it exceeds 64 bits */
     uint64_t table_bound; /* upper bound of every entry of its DP table; ~0 likewise */

@@ -572,7 +572,7 @@ struct DeviceState {
     hipEvent_t phase_ev[4] = {};       // profiling: search phases (cost tables | fill | back-substitution)
     hipStream_t last_stream = nullptr;
     char *last_ws = nullptr;           // workspace of the last search (its tables are read there)
-    hipStream_t side = nullptr;        // lanes: lane 1's stream; level layout: hoisted preps
+    hipStream_t side = nullptr;        // lanes: lane 0's stream; level layout: hoisted preps
                                        // (default priority, as every stream here)
     std::vector<hipEvent_t> lane_ev;   // bulk lane schedule: joins (no timing)
     std::vector<hipEvent_t> hoist_ev;  // hoisted preps: per side batch, its start and its end (no timing)
@@ -811,10 +811,10 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
     if (profile) HIPCHK(hipEventRecord(d->phase_ev[1], s));
     std::vector<int> fill_of(n, -1);   // timed fill batch of each vertex (profiling)
     uint32_t fb = 0;
-    // bulk lane schedule: the bulk stream starts after the upload and the cost
+    // lane schedules: the side stream starts after the upload and the cost
     // tables; a group (slot, lane) waits, for the other lane, for the latest
     // slot of that lane whose tables it reads (always an earlier slot: its
-    // event is recorded already); the caller's stream joins the bulk stream at
+    // event is recorded already); the caller's stream joins the side stream at
     // the end
     const int nl = si.lanes ? kLanes : 1;
     hipStream_t lane_stream[kLanes];
@@ -827,7 +827,9 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
     std::vector<char> lane_ev_used;
     if (si.lanes) {
         if (!d->side) HIPCHK(hipStreamCreateWithFlags(&d->side, hipStreamNonBlocking));
-        lane_stream[1] = d->side;
+        // lane 1 on the caller's stream: the leaves, the large fills and the
+        // tail after them then run without a hop between streams
+        lane_stream[0] = d->side;
         const size_t nev = 1 + (size_t)(P.nslots + 1) * kLanes;
         while (d->lane_ev.size() < nev) {
             hipEvent_t e;
@@ -835,7 +837,7 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
             d->lane_ev.push_back(e);
         }
         HIPCHK(hipEventRecord(d->lane_ev[0], s));
-        for (int l = 1; l < kLanes; l++)
+        for (int l = 0; l < kLanes; l++)
             if (lane_stream[l] != s) HIPCHK(hipStreamWaitEvent(lane_stream[l], d->lane_ev[0], 0));
         // a group's event is recorded only when a group of the other lane
         // waits on it: a record is a packet of its own in the lane's queue,
@@ -976,7 +978,7 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
     }
     if (si.lanes) {
         // join: the caller's stream waits for the last work of the other lanes
-        for (int l = 1; l < kLanes; l++)
+        for (int l = 0; l < kLanes; l++)
             if (lane_stream[l] != s) {
                 HIPCHK(hipEventRecord(lev(l, P.nslots), lane_stream[l]));
                 HIPCHK(hipStreamWaitEvent(s, lev(l, P.nslots), 0));
@@ -1012,7 +1014,7 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
 
     g->stats.launches = launches_n;
     g->stats.slots = (uint32_t)P.nslots;
-    g->stats.schedule = si.lanes ? (uint32_t)g->schedule : (P.by_level ? (uint32_t)kSchedLevel : (uint32_t)kSchedSeq);
+    g->stats.schedule = si.planned_lanes ? (uint32_t)g->schedule : (P.by_level ? (uint32_t)kSchedLevel : (uint32_t)kSchedSeq);
     g->stats.fill_ms = g->stats.rows_fill_ms = g->stats.stream_fill_ms = 0;
     g->stats.cost_tables_ms = g->stats.fill_span_ms = g->stats.backtrack_ms = 0;
     g->stats.rows_launches = g->stats.stream_launches = 0;

@@ -478,9 +478,9 @@ static void hoist_preps(pase_graph_t g, Plan &P, bool lanes) {
 
 // Bulk lane schedule.  Row-kernel vertices planned to take at least bulk_us
 // (the large fills, which keep the whole GPU busy on their own) run on lane 1
-// (a stream of its own), and so does every vertex that reads a table of lane 1
+// (the caller's stream), and so does every vertex that reads a table of lane 1
 // (it has to wait for that fill anyway); every other vertex -- one whose
-// producers are all small -- runs on lane 0 (the caller's stream), level by
+// producers are all small -- runs on lane 0 (a side stream), level by
 // level, at the highest wave priority.  A level group of lane 0 then never
 // waits for a large fill, so a chain of small dependent vertices runs beside
 // the large fills instead of after them.  Producers precede their reader in

@@ -445,8 +445,8 @@ struct VPlan {
     // schedule
     int level = 0;                  // dependency level: 1 + max level of the tables it reads
     int slot = 0;                   // launch slot: its level (level schedule) or its position
-    int lane = 0;                   // bulk lane schedule: 0 = the caller's stream (small vertices, level
-                                    // by level), 1 = the bulk stream (the large fills and their readers)
+    int lane = 0;                   // lane schedules: 0 = the side stream (small vertices, level by level),
+                                    // 1 = the caller's stream (the leaves, the large fills and their readers)
 };
 
 struct Plan {

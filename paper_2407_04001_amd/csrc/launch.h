@@ -33,7 +33,7 @@ struct Launch {
 // within one launch group, with their first workgroups.
 struct Batch {
     enum Kind { kPrep, kRows, kGeneric, kReduce, kDirect, kClass, kHalf, kJoint } kind;
-    int lane;              // bulk lane schedule: the stream it runs on (0 = the caller's)
+    int lane;              // lane schedules: the stream it runs on (1 = the caller's)
     int group;             // launch group (a slot, or a (slot, lane) pair) it belongs to
     uint32_t variant;      // rows: (TZ * 4 + TM) * 8 + NA (NA 7 = runtime count); generic: NT (0 = runtime);
                            // class, half, joint: threads per workgroup;
@@ -52,7 +52,8 @@ struct SearchImage {
     std::vector<Batch> batches;            // in enqueue order
     std::vector<std::vector<int>> groups;  // positions of each launch group
     std::vector<int> group_lane;           // lane of each launch group
-    bool lanes = false;                    // a lane schedule runs (one stream per lane in use)
+    bool planned_lanes = false;            // a lane schedule was planned (every buffer resident)
+    bool lanes = false;                    // and both lanes have work after the leaves: one stream each
     bool hoist = false;                    // hoisted preps run on a side stream (level layout)
     bool lane_hoist = false;               // hoisted preps run early on their vertex's lane (lanes)
     std::vector<std::vector<int>> group_waits;   // per launch group: the side batches it waits for
