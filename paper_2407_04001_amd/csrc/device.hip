@@ -267,7 +267,7 @@ __global__ __launch_bounds__(kPrepThreads) void k_prep(const PrepArgs *__restric
     for (uint32_t vb = blockIdx.x; vb < nvb; vb += gridDim.x) {
         const uint32_t kb = batch_find(be, nbe, vb);
         set_priority(be[kb]);
-        prep_item<KeyT>(descs[be[kb].pos], vb - be[kb].first, V, E, L, lsum, sig, cb, r);
+        prep_item<KeyT>(descs[be[kb].idx], vb - be[kb].first, V, E, L, lsum, sig, cb, r);
     }
 }
 
@@ -282,10 +282,10 @@ __global__ __launch_bounds__(256) void k_fill_rows(const RowsArgs *__restrict__ 
     // launch instead of a launch of its own (its workgroups use no LDS and no
     // barrier, and need fewer registers than the row fill)
     if (be[kb].kind == kEntryGeneric2) {
-        generic_item<KeyT, 2>(gdescs[be[kb].pos], blockIdx.x - be[kb].first);
+        generic_item<KeyT, 2>(gdescs[be[kb].idx], blockIdx.x - be[kb].first);
         return;
     }
-    rows_item<KeyT, TZ, TM, NA>(descs[be[kb].pos], blockIdx.x - be[kb].first, xch);
+    rows_item<KeyT, TZ, TM, NA>(descs[be[kb].idx], blockIdx.x - be[kb].first, xch);
 }
 
 template <typename KeyT>
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(256) void k_reduce_splits(const ReduceArgs *__restr
                                                       const BatchEntry *__restrict__ be, uint32_t nbe) {
     const uint32_t kb = batch_find(be, nbe, blockIdx.x);
     set_priority(be[kb]);
-    reduce_item<KeyT>(descs[be[kb].pos], blockIdx.x - be[kb].first);
+    reduce_item<KeyT>(descs[be[kb].idx], blockIdx.x - be[kb].first);
 }
 
 template <typename KeyT, int NT>
@@ -301,7 +301,7 @@ __global__ __launch_bounds__(256) void k_fill_generic(const GenericArgs *__restr
                                                      const BatchEntry *__restrict__ be, uint32_t nbe) {
     const uint32_t kb = batch_find(be, nbe, blockIdx.x);
     set_priority(be[kb]);
-    generic_item<KeyT, NT>(descs[be[kb].pos], blockIdx.x - be[kb].first);
+    generic_item<KeyT, NT>(descs[be[kb].idx], blockIdx.x - be[kb].first);
 }
 
 // Direct fill of the small vertices of one level (batched like the others).
@@ -315,11 +315,11 @@ __global__ __launch_bounds__(256) void k_fill_direct(const DirectArgs *__restric
     __shared__ KeyT xch[4];   // per-wave minima of a group of several waves
     const uint32_t kb = batch_find(be, nbe, blockIdx.x);
     set_priority(be[kb]);
-    direct_item<KeyT>(descs[be[kb].pos], blockIdx.x - be[kb].first, V, E, L, lsum, sig, cb, r, xch);
+    direct_item<KeyT>(descs[be[kb].idx], blockIdx.x - be[kb].first, V, E, L, lsum, sig, cb, r, xch);
 }
 
-// Class fill of the vertices of one level; `one` names the vertex of a
-// one-vertex launch (the chains of small vertices: its descriptor is then the
+// Class fill of the vertices of one level; `one` names the descriptor
+// of a one-vertex launch (the chains of small vertices: its descriptor is then the
 // first load, without a search through the batch), ~0 otherwise.  MANY: the
 // vertices with three or four edges or lookups, whose registers (160) would
 // cost all others half of their waves (6 per SIMD with 84 registers).
@@ -332,7 +332,7 @@ __global__ __launch_bounds__(512, MANY ? 3 : 6) void k_fill_class(const ClassArg
     uint32_t pos = one, lb = blockIdx.x;
     if (one == ~0u) {
         const uint32_t kb = batch_find(be, nbe, blockIdx.x);
-        pos = be[kb].pos;
+        pos = be[kb].idx;
         lb -= be[kb].first;
     }
     const ClassArgs &a = descs[pos];
@@ -365,7 +365,7 @@ __global__ __launch_bounds__(512, U == 1 ? 6 : 4) void k_fill_joint(const JointA
     uint32_t pos = one, lb = blockIdx.x;
     if (one == ~0u) {
         const uint32_t kb = batch_find(be, nbe, blockIdx.x);
-        pos = be[kb].pos;
+        pos = be[kb].idx;
         lb -= be[kb].first;
     }
     const JointArgs &a = descs[pos];
@@ -379,7 +379,7 @@ __global__ __launch_bounds__(512) void k_fill_half(const JointArgs *__restrict__
     extern __shared__ __align__(16) char lds[];
     if (prio) __builtin_amdgcn_s_setprio(3);
     const uint32_t kb = batch_find(be, nbe, blockIdx.x);
-    const JointArgs &a = descs[be[kb].pos];
+    const JointArgs &a = descs[be[kb].idx];
     const uint32_t most = max(max(a.s[0].K, a.s[1].K), a.Ky);
     if (most <= blockDim.x) half_item<KeyT, 1>(a, blockIdx.x - be[kb].first, lds);
     else half_item<KeyT, 2>(a, blockIdx.x - be[kb].first, lds);
@@ -732,13 +732,13 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
     uint8_t *dls = (uint8_t *)(ws + P.off_lsum);
     uint64_t *dsig = (uint64_t *)(ws + P.off_sig);
     const Contrib *dC = (const Contrib *)(ws + P.off_contrib);
-    const PrepArgs *dp = (const PrepArgs *)(ws + P.off_desc);
-    const RowsArgs *dr = (const RowsArgs *)(dp + n);
-    const GenericArgs *dg = (const GenericArgs *)(dr + n);
-    const ReduceArgs *dd = (const ReduceArgs *)(dg + n);
-    const DirectArgs *dx = (const DirectArgs *)(dd + n);
-    const ClassArgs *dcl = (const ClassArgs *)(dx + n);
-    const JointArgs *dj = (const JointArgs *)(dcl + n);
+    const PrepArgs *dp = (const PrepArgs *)(ws + P.off_desc[kDescPrep]);
+    const RowsArgs *dr = (const RowsArgs *)(ws + P.off_desc[kDescRows]);
+    const GenericArgs *dg = (const GenericArgs *)(ws + P.off_desc[kDescGeneric]);
+    const ReduceArgs *dd = (const ReduceArgs *)(ws + P.off_desc[kDescReduce]);
+    const DirectArgs *dx = (const DirectArgs *)(ws + P.off_desc[kDescDirect]);
+    const ClassArgs *dcl = (const ClassArgs *)(ws + P.off_desc[kDescClass]);
+    const JointArgs *dj = (const JointArgs *)(ws + P.off_desc[kDescJoint]);
     const BatchEntry *dbe = (const BatchEntry *)(ws + P.off_batch);
     uint32_t *dcfg = (uint32_t *)(ws + P.off_cfg);
     SearchOut *dout = (SearchOut *)(ws + P.off_out);
@@ -936,7 +936,7 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
             } else if constexpr (kWide) {
                 return fail(g, PASE_ERR_INTERNAL, "a 128-bit key plan holds a row, direct or class fill");
             } else if (b.kind == Batch::kClass) {
-                const uint32_t one = b.nentries == 1 ? b.pos0 : ~0u, prio = si.lanes && b.lane == 0;
+                const uint32_t one = b.nentries == 1 ? b.idx0 : ~0u, prio = si.lanes && b.lane == 0;
                 const dim3 threads(b.variant & ~1u);
                 if (b.variant & 1u)
                     hipExtLaunchKernelGGL((k_fill_class<KeyT, true>), dim3(b.blocks), threads, b.lds, bs, e0, e1, 0, dcl,
@@ -948,7 +948,7 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
                 hipExtLaunchKernelGGL((k_fill_half<KeyT>), dim3(b.blocks), dim3(b.variant), b.lds, bs, e0, e1, 0,
                                       dj, e, b.nentries, (uint32_t)(si.lanes && b.lane == 0));
             } else if (b.kind == Batch::kJoint) {
-                const uint32_t one = b.nentries == 1 ? b.pos0 : ~0u, prio = si.lanes && b.lane == 0;
+                const uint32_t one = b.nentries == 1 ? b.idx0 : ~0u, prio = si.lanes && b.lane == 0;
                 const dim3 threads(b.variant & ~1u);
                 if (b.variant & 1u)
                     hipExtLaunchKernelGGL((k_fill_joint<KeyT, 2>), dim3(b.blocks), threads, b.lds, bs, e0, e1, 0, dj, e,

@@ -653,12 +653,16 @@ static pase_status build_plan(pase_graph_t g) {
     // -> 6 us on its small chain vertices); a direct vertex without such a
     // digit takes the same kernel's plain minimum (8.2 -> 5.5 us per launch on
     // the residual CNN at p = 8).  The tile knobs and a hoisting threshold below its default
-    // ask for the dense fills and their preps, which they then get.
-    const bool class_ok = kernel_mode == 0 && !g->volume && !g->overridden && !g->tile_cols && !g->tile_rows &&
-                          !g->tile_parts && !g->c_splits && (!g->hoist_elems || g->hoist_elems >= kHoistElems);
+    // ask for the dense fills and their preps, which they then get.  With the
+    // volume model a direct vertex takes the plain minimum as well, each edge's
+    // matrix read as a lookup.
+    const bool min_ok = kernel_mode == 0 && !g->overridden && !g->tile_cols && !g->tile_rows &&
+                        !g->tile_parts && !g->c_splits && (!g->hoist_elems || g->hoist_elems >= kHoistElems);
+    const bool class_ok = min_ok && !g->volume;
     auto plan_class = [&](int i, bool direct) {
         VPlan &vp = P.v[i];
-        if (!class_ok || vp.K > kClassMaxK || vp.terms.size() > (size_t)kMaxClassTerms) return false;
+        const size_t lookups = vp.terms.size() + (g->volume ? vp.edges.size() : 0);
+        if (!min_ok || (g->volume && !direct) || vp.K > kClassMaxK || lookups > (size_t)kMaxClassTerms) return false;
         auto edges_to = [&](int w) {
             int k = 0;
             for (int e : vp.edges) k += (int)g->E[e].src == w || (int)g->E[e].dst == w;
@@ -668,9 +672,10 @@ static pase_status build_plan(pase_graph_t g) {
         for (int w : vp.D) {
             bool looked = g->K[w] > kClassMaxK || edges_to(w) != 1;
             for (const auto &t : vp.terms) looked |= std::count(t.dig.begin(), t.dig.end(), w) > 0;
-            if (!looked && (z < 0 || g->K[w] > g->K[z])) z = w;
+            if (class_ok && !looked && (z < 0 || g->K[w] > g->K[z])) z = w;
         }
-        if ((z < 0 && !direct) || vp.edges.size() - (z >= 0) > (size_t)kMaxClassEdges) return false;
+        const size_t edges = (g->volume ? 0 : vp.edges.size()) - (z >= 0);
+        if ((z < 0 && !direct) || edges > (size_t)kMaxClassEdges) return false;
         const std::vector<int> order = gather_layout(vp);
         std::vector<int> R;
         for (int u : order)
@@ -678,7 +683,7 @@ static pase_status build_plan(pase_graph_t g) {
         uint64_t rows = 1;
         for (int u : R) rows *= g->K[u];
         const uint32_t Kz = z >= 0 ? g->K[z] : 1;
-        const uint32_t ne = (uint32_t)vp.edges.size() - (z >= 0), nt = (uint32_t)vp.terms.size();
+        const uint32_t ne = (uint32_t)edges, nt = (uint32_t)lookups;
         auto fits = [&](uint32_t lr, bool keep) {
             return class_lds(vp.K, Kz, ne, nt, lr, z >= 0, keep, 512) <= kClassMaxLds;
         };
@@ -1220,9 +1225,26 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
     off = align_up(off + ncontrib * sizeof(Contrib), A);
     P.off_bt = off;
     off = align_up(off + n * sizeof(BacktrackDesc), A);
-    P.off_desc = off;
-    off = align_up(off + n * (sizeof(PrepArgs) + sizeof(RowsArgs) + sizeof(GenericArgs) + sizeof(ReduceArgs) +
-                              sizeof(DirectArgs) + sizeof(ClassArgs) + sizeof(JointArgs)), A);
+    // launch descriptors: only those that some launch reads (all kinds for all
+    // vertices were 4 KB a vertex, half of the upload)
+    static const uint64_t kDescBytes[kDescKinds] = {sizeof(PrepArgs), sizeof(RowsArgs), sizeof(GenericArgs),
+                                                    sizeof(ReduceArgs), sizeof(DirectArgs), sizeof(ClassArgs),
+                                                    sizeof(JointArgs)};
+    std::fill(std::begin(P.ndesc), std::end(P.ndesc), 0u);
+    for (auto &vp : P.v) {
+        const bool dense = !vp.classes && vp.joint < 0 && vp.kernel != kDirect;
+        const bool has[kDescKinds] = {dense, dense && vp.kernel == kRows, dense && vp.kernel == kGeneric,
+                                      dense && vp.kernel == kRows && (vp.nsplit > 1 || vp.fused_from >= 0),
+                                      vp.kernel == kDirect && !vp.classes, vp.classes, vp.joint >= 0};
+        for (int k = 0; k < kDescKinds; k++) {
+            vp.desc[k] = has[k] ? P.ndesc[k] : ~0u;
+            P.ndesc[k] += has[k];
+        }
+    }
+    for (int k = 0; k < kDescKinds; k++) {
+        P.off_desc[k] = off;
+        off = align_up(off + P.ndesc[k] * kDescBytes[k], A);
+    }
     P.off_batch = off;
     off = align_up(off + 3 * (uint64_t)n * sizeof(BatchEntry), A);
     P.off_ctdesc = off;

@@ -149,11 +149,12 @@ struct PrepArgs {
     Block blk[kMaxBlocks];
 };
 
-// One vertex of a batched launch: its descriptor index (sequence position)
-// and its first workgroup.  The workgroups of a launch are the concatenation
+// One vertex of a batched launch: its descriptor index and its first
+// workgroup.  The workgroups of a launch are the concatenation
 // of the workgroups of its vertices.
 struct BatchEntry {
-    uint32_t pos;
+    uint32_t pos;             // sequence position (host)
+    uint32_t idx;             // its descriptor of the launch's kind
     uint32_t first;
     uint32_t prio;            // 1: the bulk lane schedule's small vertices -- their waves issue first
     uint32_t kind;            // row-kernel launches: 0 a row fill, 1 a two-term generic fill riding along
@@ -253,7 +254,7 @@ struct ClassEdge {            // an edge to a rest digit
 
 struct ClassTerm {            // a lookup T_j (key space)
     const void *ptr;
-    uint32_t sc, pad;         // element stride of c
+    uint32_t sc, raw;         // element stride of c; 1: plain uint64 costs (a volume model edge's matrix)
     uint32_t sd[kMaxDep];     // element strides of the rest digits
 };
 
@@ -387,6 +388,9 @@ struct TermRef {
     std::vector<int> dig;     // D(j) - {v_i}: vertex ids
 };
 
+// Kinds of launch descriptors: a vertex has those its launches need.
+enum DescKind { kDescPrep, kDescRows, kDescGeneric, kDescReduce, kDescDirect, kDescClass, kDescJoint, kDescKinds };
+
 enum KernelKind { kGeneric = 0, kRows = 1, kDirect = 2 };
 
 struct VPlan {
@@ -420,6 +424,7 @@ struct VPlan {
     bool jearly = false;            // the half fill runs in the other vertex's slot, else just before the fill
     int absorbed = -1;              // the vertex whose joint fill does without this one's table
     std::vector<int> reads;         // positions whose tables its launches read
+    uint32_t desc[kDescKinds] = {}; // index of its descriptor of each kind
     std::vector<int> O, R;          // outer / row digits (vertex ids), slowest first
     uint32_t TZ = 0, TM = 1, ldz = 0, nchunks = 0, nsplit = 1, cper = 0, parts = 1;
     uint64_t MO = 1, MR = 1;
@@ -467,7 +472,8 @@ struct Plan {
     int nslots = 0;                 // launch slots (levels, or positions when sequential)
     bool by_level = false;          // the vertices of one dependency level share launches
     bool resident = false;          // every table and scratch buffer resident at once (no reuse)
-    uint64_t off_desc = 0, off_batch = 0;   // per-vertex launch descriptors, batch tables
+    uint64_t off_desc[kDescKinds] = {}, off_batch = 0;   // launch descriptors by kind, batch tables
+    uint32_t ndesc[kDescKinds] = {};
     // class fills: tables per edge shape (byte offsets relative to off_ctab until layout) and the
     // key-space layer costs and edge f values, all written by k_cost_tables
     std::vector<DevClassTab> ctabs;

@@ -887,6 +887,14 @@ __device__ __forceinline__ void class_table_item(const DevClassTab &t, uint32_t 
 // KB, so the workgroup fits beside those of a large fill on another stream).
 // All loads of a thread are independent (U configurations and entries in
 // flight): about three memory round trips in all.
+// A lookup's value as a key; raw: a plain integer cost read through the table's
+// type (keys of 64 bits only, the same width).
+template <typename KeyT>
+__device__ __forceinline__ KeyT class_term(uint32_t raw, uint32_t bits, typename KeyOps<KeyT>::Val v) {
+    if (raw) return KeyOps<KeyT>::from_u64(__builtin_bit_cast(uint64_t, v) << bits);
+    return __builtin_bit_cast(KeyT, v);
+}
+
 template <typename KeyT, int NE, int NT>
 __device__ __forceinline__ void class_item_small(const ClassArgs &a, uint32_t lb, char *lds) {
     using Ops = KeyOps<KeyT>;
@@ -965,7 +973,7 @@ __device__ __forceinline__ void class_item_small(const ClassArgs &a, uint32_t lb
                 ef[u][t] = fc[t][c];
             }
 #pragma unroll
-            for (int t = 0; t < NT; t++) tv[u][t] = __builtin_bit_cast(KeyT, tp[t][(uint64_t)c * tsc[t]]);
+            for (int t = 0; t < NT; t++) tv[u][t] = class_term<KeyT>(a.t[t].raw, bits, tp[t][(uint64_t)c * tsc[t]]);
         }
 #pragma unroll
         for (int u = 0; u < U; u++) {
@@ -1136,7 +1144,7 @@ __device__ __forceinline__ void class_item_staged(const ClassArgs &a, uint32_t l
         if (NT > 0) {
             const uint32_t c = cs[p];
 #pragma unroll
-            for (int t = 0; t < NT; t++) v.t[t] = __builtin_bit_cast(KeyT, tp[t][(uint64_t)c * tsc[t]]);
+            for (int t = 0; t < NT; t++) v.t[t] = class_term<KeyT>(a.t[t].raw, bits, tp[t][(uint64_t)c * tsc[t]]);
         }
         v.r = rec[p];
 #pragma unroll

@@ -13,8 +13,10 @@
 namespace pase {
 
 // One vertex's kernel descriptors, resolved against the workspace base.
+// (Only the descriptors the vertex has are written.)
 template <typename KeyT>
 struct Launch {
+    Launch() {}
     PrepArgs prep;
     bool rows = false;
     bool direct = false;
@@ -42,7 +44,7 @@ struct Batch {
     uint32_t nentries;
     uint32_t blocks;       // workgroups of the launch
     uint32_t lds = 0;      // class and joint fills: dynamic LDS of the launch
-    uint32_t pos0 = 0;     // first member
+    uint32_t idx0 = 0;     // descriptor of the first member
     bool side = false;     // a hoisted prep launch: on the side stream, after the work enqueued before it
 };
 

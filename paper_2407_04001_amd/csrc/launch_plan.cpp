@@ -47,7 +47,8 @@ pase_status build_launches(pase_graph_t g, char *ws, std::vector<Launch<KeyT>> &
                            std::vector<Contrib> &contrib) {
     const Plan &P = g->plan;
     const int n = (int)P.v.size();
-    out.assign(n, Launch<KeyT>());
+    out.clear();
+    out.resize(n);
     contrib.clear();
     const uint64_t *ovedge = (const uint64_t *)(ws + P.off_ovedge);
     // element offsets of every vertex's layer costs and every edge's signatures
@@ -58,7 +59,8 @@ pase_status build_launches(pase_graph_t g, char *ws, std::vector<Launch<KeyT>> &
         const VPlan &vp = P.v[i];
         Launch<KeyT> &L = out[i];
         KeyT *blocks = (KeyT *)(ws + P.off_block + vp.block_off);
-        std::memset(&L.prep, 0, sizeof L.prep);
+        const bool dense = !vp.classes && vp.joint < 0 && vp.kernel != kDirect;
+        if (dense) std::memset(&L.prep, 0, sizeof L.prep);
         L.prep.blocks = blocks;
         L.prep.vi = (uint32_t)vp.vi;
         L.prep.K = vp.K;
@@ -266,6 +268,19 @@ pase_status build_launches(pase_graph_t g, char *ws, std::vector<Launch<KeyT>> &
                 for (int e : vp.edges) {
                     uint64_t oc, oo;
                     edge_ends(e, vp.vi, oc, oo);
+                    if (g->volume) {   // the edge's matrix as a lookup
+                        if (ca.nt >= (uint32_t)kMaxClassTerms) return fail(g, PASE_ERR_INTERNAL, "class lookups");
+                        ClassTerm &ct = ca.t[ca.nt++];
+                        const uint32_t Kd = g->K[g->E[e].dst];
+                        const bool is_src = (int)g->E[e].src == vp.vi;
+                        const uint32_t dig = (uint32_t)(std::find(vp.R.begin(), vp.R.end(), other_of(e)) - vp.R.begin());
+                        if (dig >= ca.nR) return fail(g, PASE_ERR_INTERNAL, "class edge digit");
+                        ct.ptr = (const uint64_t *)(ws + P.off_vmat) + g->mat_off[e];
+                        ct.raw = 1;
+                        ct.sc = is_src ? Kd : 1;
+                        ct.sd[dig] = is_src ? 1 : Kd;
+                        continue;
+                    }
                     if (other_of(e) == vp.z) {
                         if (zdone || vp.ctab < 0) return fail(g, PASE_ERR_INTERNAL, "class edge");
                         zdone = true;
@@ -657,8 +672,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         b.pos = (uint32_t)i;
         // a vertex whose table is not formed: one evaluation of its terms
         if (vp.absorbed >= 0 && !g->keep_tables)
-            b.lazy = (const ClassArgs *)(ws + P.off_desc + (uint64_t)n * (sizeof(PrepArgs) + sizeof(RowsArgs) +
-                                         sizeof(GenericArgs) + sizeof(ReduceArgs) + sizeof(DirectArgs))) + i;
+            b.lazy = (const ClassArgs *)(ws + P.off_desc[kDescClass]) + vp.desc[kDescClass];
         b.m = (uint32_t)vp.layout.size();
         for (size_t k = 0; k < vp.layout.size(); k++) {
             b.dig[k] = (uint32_t)vp.layout[k];
@@ -669,30 +683,29 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         nlev = std::max(nlev, b.level + 1);
     }
     si.nlev = nlev;
-    if ((st = region(P.off_bt, n * sizeof(BacktrackDesc), P.off_desc, "back-substitution")) != PASE_OK) return st;
+    if ((st = region(P.off_bt, n * sizeof(BacktrackDesc), P.off_desc[0], "back-substitution")) != PASE_OK) return st;
     std::memcpy(img + P.off_bt, bt.data(), n * sizeof(BacktrackDesc));
 
-    // ---- kernel descriptors: per position, one of each kind
-    const uint64_t desc_bytes =
-        (uint64_t)n * (sizeof(PrepArgs) + sizeof(RowsArgs) + sizeof(GenericArgs) + sizeof(ReduceArgs) + sizeof(DirectArgs) +
-                      sizeof(ClassArgs) + sizeof(JointArgs));
-    if ((st = region(P.off_desc, desc_bytes, P.off_batch, "descriptors")) != PASE_OK) return st;
-    PrepArgs *hp = (PrepArgs *)(img + P.off_desc);
-    RowsArgs *hr = (RowsArgs *)(hp + n);
-    GenericArgs *hg = (GenericArgs *)(hr + n);
-    ReduceArgs *hd = (ReduceArgs *)(hg + n);
-    DirectArgs *hx = (DirectArgs *)(hd + n);
-    ClassArgs *hc = (ClassArgs *)(hx + n);
-    JointArgs *hj = (JointArgs *)(hc + n);
+    // ---- kernel descriptors, by kind
+    auto put = [&](int i, DescKind k, const void *src, size_t bytes) {
+        const uint32_t at = P.v[i].desc[k];
+        if (at == ~0u) return;
+        std::memcpy(img + P.off_desc[k] + (uint64_t)at * bytes, src, bytes);
+    };
+    for (int k = 0; k < kDescKinds; k++)
+        if ((st = region(P.off_desc[k], 0, k + 1 < kDescKinds ? P.off_desc[k + 1] : P.off_batch, "descriptors")) != PASE_OK)
+            return st;
     for (int i = 0; i < n; i++) {
-        hp[i] = launches[i].prep;
-        hr[i] = launches[i].ra;
-        hg[i] = launches[i].ga;
-        hd[i] = launches[i].red;
-        hx[i] = launches[i].da;
-        hc[i] = launches[i].ca;
-        hj[i] = launches[i].ja;
+        const Launch<KeyT> &L = launches[i];
+        put(i, kDescPrep, &L.prep, sizeof L.prep);
+        put(i, kDescRows, &L.ra, sizeof L.ra);
+        put(i, kDescGeneric, &L.ga, sizeof L.ga);
+        put(i, kDescReduce, &L.red, sizeof L.red);
+        put(i, kDescDirect, &L.da, sizeof L.da);
+        put(i, kDescClass, &L.ca, sizeof L.ca);
+        put(i, kDescJoint, &L.ja, sizeof L.ja);
     }
+    RowsArgs *hr = (RowsArgs *)(img + P.off_desc[kDescRows]);
     if (!P.ctabs.empty()) {
         if ((st = region(P.off_ctdesc, P.ctabs.size() * sizeof(DevClassTab), P.off_jtdesc, "class tables")) != PASE_OK) return st;
         if ((st = region(P.off_jtdesc, P.jtabs.size() * sizeof(DevJointTab), P.off_zero, "joint tables")) != PASE_OK) return st;
@@ -718,18 +731,22 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
     for (int i = 0; i < n; i++) si.groups[(size_t)P.v[i].slot * nl + (si.lanes ? P.v[i].lane : 0)].push_back(i);
     for (size_t k = 0; k < si.groups.size(); k++) si.group_lane[k] = (int)(k % nl);
     int cur_lane = 0, cur_group = 0;
-    bool be_overflow = false;
+    bool be_overflow = false, no_desc = false;
     auto add_batch = [&](Batch::Kind kind, uint32_t variant, const std::vector<int> &members,
                          uint32_t (*nblk)(const Launch<KeyT> &)) {
         if (members.empty()) return;
         Batch b{kind, cur_lane, cur_group, variant, nbe, 0, 0};
-        b.pos0 = (uint32_t)members[0];
+        static const DescKind kind_of[] = {kDescPrep, kDescRows, kDescGeneric, kDescReduce,
+                                           kDescDirect, kDescClass, kDescJoint, kDescJoint};
+        b.idx0 = P.v[members[0]].desc[kind_of[kind]];
         for (int i : members) {
             if (kind == Batch::kJoint) b.lds = std::max(b.lds, launches[i].ja.lds);
             if (kind == Batch::kHalf) b.lds = std::max(b.lds, launches[i].ja.hlds);
             if (kind == Batch::kClass) b.lds = std::max(b.lds, launches[i].ca.lds);
             if (nbe >= be_cap) { be_overflow = true; return; }
             hbe[nbe].pos = (uint32_t)i;
+            hbe[nbe].idx = P.v[i].desc[kind_of[kind]];
+            if (hbe[nbe].idx == ~0u) { no_desc = true; return; }
             hbe[nbe].first = b.blocks;
             hbe[nbe].prio = si.lanes && P.v[i].lane == 0 ? 1u : 0u;
             hbe[nbe].kind = 0;
@@ -851,7 +868,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
                     const int d = shape_dom[P.v[i].TZ * 4 + P.v[i].TM];
                     const uint32_t nd = std::min<uint32_t>(launches[d].ra.na, 4);
                     if (d != i && na < nd && P.v[i].est_us <= 0.5 * P.v[d].est_us) {
-                        RowsArgs &ra = hr[i];
+                        RowsArgs &ra = hr[P.v[i].desc[kDescRows]];
                         for (uint32_t t = na; t < nd; t++) {
                             std::memset(&ra.a[t], 0, sizeof ra.a[t]);
                             ra.a[t].ptr = ws + P.off_zero;
@@ -904,6 +921,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
                 for (int i : ride) {
                     if (nbe >= be_cap) { be_overflow = true; break; }
                     hbe[nbe].pos = (uint32_t)i;
+                    hbe[nbe].idx = P.v[i].desc[kDescGeneric];
                     hbe[nbe].first = b.blocks;
                     hbe[nbe].prio = si.lanes && P.v[i].lane == 0 ? 1u : 0u;
                     hbe[nbe].kind = kEntryGeneric2;
@@ -927,6 +945,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         for (auto &x : reds) grp.push_back(x.second);
         add_batch(Batch::kReduce, 0, grp, [](const Launch<KeyT> &L) { return L.red.nblk; });
         add_batch(Batch::kPrep, 0, lane_hoist_at[sl], [](const Launch<KeyT> &L) { return L.prep.nwg; });
+        if (no_desc) return fail(g, PASE_ERR_INTERNAL, "a launch without a descriptor");
         if (be_overflow) return fail(g, PASE_ERR_INTERNAL, "batch table overflow");
         add_side(sl + 1);
     }

@@ -121,6 +121,37 @@ def test_shapes_every_entry(shape, key):
                 assert pg.fingerprint(v) == o.fingerprint(i), (v, pg.vertex_info(v))
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("key", [0, 1])
+@pytest.mark.parametrize("shape", range(7))
+def test_volume_minimum(shape, key):
+    """The volume model at direct sizes: the plain minimum with every edge's
+    matrix as a lookup (up to three edges and a lookup per vertex, either end of
+    an edge), and with a smaller direct size, where some vertices take the dense
+    fills."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_04001_amd import pase as P
+    from oracle.oracle import Oracle
+    dims, p, every = SHAPES[shape]
+    g = star(dims)
+    print(f"volume minimum {dims} p={p} every={every} key={key}", flush=True)
+    o = Oracle(g)
+    o.configs(p, all_integers=every, volume=True)
+    o.solve(threads=os.cpu_count() or 1)
+    pg = P.Graph(g)
+    pg.set_option(P.OPT_TRANSFER, 1)
+    pg.enumerate_configs(p, all_integers=every)
+    pg.set_option(P.OPT_KEY_TYPE, key)
+    pg.set_option(P.OPT_KEEP_TABLES, 1)
+    for cells in (1 << 30, 1000):
+        pg.set_option(P.OPT_DIRECT_CELLS, cells)
+        assert pg.find_best_strategy() == o.result(), cells
+        for i, v in enumerate(o.sequence()):
+            assert pg.fingerprint(v) == o.fingerprint(i), (v, cells, pg.vertex_info(v))
+
+
 # ------------------------------------------------------------------ joint fill
 def triangle(di, dj, dy, has_e, looks, perm=False, r=1, upper=2):
     """v_j (1) joined to v_i (2), y (3) and an upper digit (4); v_i joined to y
