@@ -199,7 +199,10 @@ typedef enum {
                                    workgroups with 64-bit atomic minima of the packed keys (the
                                    strict "<" tie-break is unchanged: keys are distinct per c),
                                    so the predecessor's table is never written to HBM and read
-                                   back; 0: every vertex fills on its own.  Re-plans */
+                                   back; with the split match model and no kept tables, a pair
+                                   whose predecessor has one-digit lookups only and whose reader
+                                   has one edge to each of two digits is evaluated with the two
+                                   minima exchanged (the exchange fill) instead; 0: every vertex fills on its own.  Re-plans */
     PASE_OPT_HOIST_ELEMS = 21,  /* one-stream level layout (the level schedule, or the bulk lane
                                    schedule over its memory budget): a vertex whose prep blocks
                                    hold at least this many elements (default 2^20) and read only
@@ -398,7 +401,8 @@ typedef struct {
     uint64_t table_bound; /* upper bound of every entry of its DP table; ~0 likewise */
     uint32_t key_type;    /* key type of the plan (the same for every vertex): 0 fp64, 1 uint64, 2 128-bit */
     uint32_t fused;       /* PASE_OPT_FUSED_MIN: 1 = its fill also forms the minimum of its table's reader,
-                             2 = that reader (its fill is then a one-split reduction of those keys), 0 = neither */
+                             2 = that reader (its fill is then a one-split reduction of those keys, or
+                             an exchange fill that does without the other's table), 0 = neither */
     int32_t prep_after;   /* its prep blocks read only tables of slots up to this one (-1: none) and are
                              built right after it, beside the launches of the slots in between -- on a
                              side stream (level layout) or at the end of that slot's launches on lane

@@ -385,6 +385,24 @@ __global__ __launch_bounds__(512) void k_fill_half(const JointArgs *__restrict__
     else half_item<KeyT, 2>(a, blockIdx.x - be[kb].first, lds);
 }
 
+template <typename KeyT>
+__global__ __launch_bounds__(256) void k_exch_half(const ExchArgs *__restrict__ descs, const BatchEntry *__restrict__ be,
+                                                   uint32_t nbe, uint32_t prio) {
+    extern __shared__ __align__(16) char lds[];
+    if (prio) __builtin_amdgcn_s_setprio(3);
+    const uint32_t kb = batch_find(be, nbe, blockIdx.x);
+    exch_half_item<KeyT>(descs[be[kb].idx], blockIdx.x - be[kb].first, lds);
+}
+
+template <typename KeyT>
+__global__ __launch_bounds__(256) void k_fill_exch(const ExchArgs *__restrict__ descs, const BatchEntry *__restrict__ be,
+                                                   uint32_t nbe, uint32_t prio) {
+    __shared__ ExchLds lds;
+    if (prio) __builtin_amdgcn_s_setprio(3);
+    const uint32_t kb = batch_find(be, nbe, blockIdx.x);
+    exch_item<KeyT>(descs[be[kb].idx], blockIdx.x - be[kb].first, lds);
+}
+
 // ------------------------------------------------------------------ back-substitution
 // From the last position down: the configuration of v_i is A_i at the
 // already-chosen configurations of D(i) (every member of D(i) is later in the
@@ -739,6 +757,7 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
     const DirectArgs *dx = (const DirectArgs *)(ws + P.off_desc[kDescDirect]);
     const ClassArgs *dcl = (const ClassArgs *)(ws + P.off_desc[kDescClass]);
     const JointArgs *dj = (const JointArgs *)(ws + P.off_desc[kDescJoint]);
+    const ExchArgs *dxc = (const ExchArgs *)(ws + P.off_desc[kDescExch]);
     const BatchEntry *dbe = (const BatchEntry *)(ws + P.off_batch);
     uint32_t *dcfg = (uint32_t *)(ws + P.off_cfg);
     SearchOut *dout = (SearchOut *)(ws + P.off_out);
@@ -796,7 +815,7 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
                            (uint32_t)nv, dE, (uint32_t)ne, dex, dL, dls, dsig, si.nL, P.sig_count, g->r, dfk, nF,
                            fsent, ct, nbase);
         launches_n++;
-        if (P.joint_fills) {
+        if (!P.jtabs.empty()) {
             hipLaunchKernelGGL(k_joint_tables, dim3((uint32_t)P.jtabs.size()), dim3(kJointMaxK), 0, s,
                                (const DevJointTab *)(ws + P.off_jtdesc), (const DevClassTab *)(ws + P.off_ctdesc), ws);
             launches_n++;
@@ -924,6 +943,8 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
         case Batch::kClass:
         case Batch::kHalf:
         case Batch::kJoint:
+        case Batch::kExchHalf:
+        case Batch::kExch:
         {
             // with profiling, the launch itself records its start and end
             // (events attached to the dispatch, no extra packets in the stream)
@@ -956,6 +977,12 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
                 else
                     hipExtLaunchKernelGGL((k_fill_joint<KeyT, 1>), dim3(b.blocks), threads, b.lds, bs, e0, e1, 0, dj, e,
                                           b.nentries, one, prio);
+            } else if (b.kind == Batch::kExchHalf) {
+                hipExtLaunchKernelGGL((k_exch_half<KeyT>), dim3(b.blocks), dim3(256), b.lds, bs, e0, e1, 0, dxc, e,
+                                      b.nentries, (uint32_t)(si.lanes && b.lane == 0));
+            } else if (b.kind == Batch::kExch) {
+                hipExtLaunchKernelGGL((k_fill_exch<KeyT>), dim3(b.blocks), dim3(256), 0, bs, e0, e1, 0, dxc, e,
+                                      b.nentries, (uint32_t)(si.lanes && b.lane == 0));
             } else if (b.kind == Batch::kRows) {
                 if (!launch_rows<KeyT>(dr, dg, e, b, bs, e0, e1)) return fail(g, PASE_ERR_INTERNAL, "no kernel for TZ");
             } else {

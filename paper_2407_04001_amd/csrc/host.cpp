@@ -434,7 +434,9 @@ static void hoist_preps(pase_graph_t g, Plan &P, bool lanes) {
             vp.prep_lane = vj.lane;
             continue;
         }
-        if ((vp.kernel != kRows && vp.kernel != kGeneric) || vp.classes || vp.fused_from >= 0 || vp.fuse_into >= 0) continue;
+        if ((vp.kernel != kRows && vp.kernel != kGeneric) || vp.classes || vp.fused_from >= 0 || vp.fuse_into >= 0 ||
+            (vp.absorbed >= 0 && P.v[vp.absorbed].exch))
+            continue;
         uint64_t elems = 0;
         int ready = -1;
         int lane = -1;            // lane of the tables the blocks read (-2: more than one)
@@ -874,7 +876,7 @@ static pase_status build_plan(pase_graph_t g) {
     };
     auto plan_one = [&](int i, uint32_t ftz, uint32_t ftm, bool no_split) {
         VPlan &vp = P.v[i];
-        vp.classes = false;
+        vp.classes = vp.exch = false;
         vp.joint = -1;
         const uint32_t tile_cols = ftz ? ftz : g->tile_cols, tile_rows = ftm ? ftm : g->tile_rows;
         // small vertices: the direct fill (one launch, no prep blocks), whose
@@ -1019,7 +1021,48 @@ static pase_status build_plan(pase_graph_t g) {
         for (int k = (int)vp.layout.size() - 2; k >= 0; k--)
             vp.stride[k] = vp.stride[k + 1] * g->K[vp.layout[k + 1]];
     };
-    for (int i = 0; i < n; i++) plan_one(i, 0, 0, false);
+    // Exchange fill (the structure is described at ExchLookup): i reads one
+    // table over all of D(i) = {y, z}, whose vertex j has no edges and only
+    // one-digit lookups.  Both of i's edges tight, so that classes are small.
+    // Costs ten operations per (c_j, y, z) and two launches, against two per
+    // (c_j, c_i, y, z) and three: 660 -> 52 us at K = 84, 462, 462, 462 and
+    // 5158 + 1156 -> 197 us at 203, 731, 731, 731; from 24 configurations
+    // up, like the joint fill.  Not with kept tables (j's is then wanted).
+    auto plan_exchange = [&](int i) {
+        VPlan &vp = P.v[i];
+        if (!g->fuse_min || g->keep_tables || joint_kt == 2 || vp.classes || vp.joint >= 0 || vp.kernel == kDirect) return;
+        if (vp.terms.size() != 1 || vp.D.size() != 2 || vp.terms[0].dig.size() != 2 || vp.edges.size() != 2 ||
+            vp.K < 24 || vp.K > kExchMaxK)
+            return;
+        const int j = vp.terms[0].j;
+        VPlan &vj = P.v[j];
+        if (vj.classes || vj.joint >= 0 || vj.kernel == kDirect || !vj.edges.empty() || vj.D.size() != 3 ||
+            vj.consumer != i || vj.terms.size() != 3 || vj.K > kClassMaxK)
+            return;
+        std::vector<int> seen;
+        for (const auto &t : vj.terms) {
+            if (t.dig.size() != 1 || std::count(seen.begin(), seen.end(), t.dig[0])) return;
+            seen.push_back(t.dig[0]);
+        }
+        for (int u : vp.layout) {
+            int k = 0;
+            for (int e : vp.edges)
+                if ((int)g->E[e].src == u || (int)g->E[e].dst == u) k += tight(e) ? 1 : 2;
+            if (k != 1 || g->K[u] > kClassMaxK) return;
+        }
+        // uint64 keys: sums of a few cases' keys and of the mark of an empty
+        // class (2^62) must not wrap
+        const unsigned __int128 top = ((unsigned __int128)qmax[i] + qmax[j] + 2) << std::max(vp.bits, vj.bits);
+        if (joint_kt == 1 && top >> 60) return;
+        vp.joint = j;
+        vp.exch = true;
+        vp.nsplit = 1;
+        vp.cper = vp.K;
+    };
+    for (int i = 0; i < n; i++) {
+        plan_one(i, 0, 0, false);
+        plan_exchange(i);
+    }
     // the tables each vertex's launches read: a joint fill's half fill runs in
     // the other vertex's slot (its tables are that vertex's reads), or, without
     // levels or hoisting, just before the fill
@@ -1086,7 +1129,7 @@ static pase_status build_plan(pase_graph_t g) {
         }
     }
     for (const auto &vp : P.v) {
-        if (vp.kernel != kRows || vp.classes || vp.joint >= 0) continue;
+        if (vp.kernel != kRows || vp.classes || vp.joint >= 0 || (vp.absorbed >= 0 && !g->keep_tables)) continue;
         P.rows_vertices++;
         P.rows_cells += vp.N * vp.K;
         if (vp.z < 0) P.stream_cells += vp.N * vp.K;
@@ -1135,6 +1178,11 @@ static pase_status build_plan(pase_graph_t g) {
         if (vp.joint >= 0) {
             const int vj = P.v[vp.joint].vi;
             P.joint_fills++;
+            if (vp.exch) {
+                vp.jtab[0] = class_table(vp.vi, vp.layout[0]);
+                vp.jtab[1] = class_table(vp.vi, vp.layout[1]);
+                continue;
+            }
             vp.jtab[0] = class_table(vp.vi, vp.z);
             vp.jtab[1] = class_table(vj, vp.z);
             vp.jtab[2] = class_table(vj, vp.vi);
@@ -1229,13 +1277,15 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
     // vertices were 4 KB a vertex, half of the upload)
     static const uint64_t kDescBytes[kDescKinds] = {sizeof(PrepArgs), sizeof(RowsArgs), sizeof(GenericArgs),
                                                     sizeof(ReduceArgs), sizeof(DirectArgs), sizeof(ClassArgs),
-                                                    sizeof(JointArgs)};
+                                                    sizeof(JointArgs), sizeof(ExchArgs)};
     std::fill(std::begin(P.ndesc), std::end(P.ndesc), 0u);
     for (auto &vp : P.v) {
-        const bool dense = !vp.classes && vp.joint < 0 && vp.kernel != kDirect;
+        const bool lazy = vp.absorbed >= 0 && !g->keep_tables;   // (evaluated with the terms of a class fill)
+        const bool dense = !vp.classes && vp.joint < 0 && vp.kernel != kDirect && !lazy;
         const bool has[kDescKinds] = {dense, dense && vp.kernel == kRows, dense && vp.kernel == kGeneric,
                                       dense && vp.kernel == kRows && (vp.nsplit > 1 || vp.fused_from >= 0),
-                                      vp.kernel == kDirect && !vp.classes, vp.classes, vp.joint >= 0};
+                                      vp.kernel == kDirect && !vp.classes, vp.classes || lazy,
+                                      vp.joint >= 0 && !vp.exch, vp.exch};
         for (int k = 0; k < kDescKinds; k++) {
             vp.desc[k] = has[k] ? P.ndesc[k] : ~0u;
             P.ndesc[k] += has[k];
@@ -1351,8 +1401,10 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
         uint64_t e = 0, pb = 0;
         if (vp.joint >= 0) {
             // the half table
-            e = align_up(joint_half_elems(vp.K, P.v[vp.joint].K, g->K[vp.z]) * vp.jupper, 32);
-        } else if (vp.classes) {
+            if (vp.exch)
+                e = align_up(exch_half_elems(vp.K, P.v[vp.joint].K, align_up(g->K[vp.layout[0]], kExchCols), g->K[vp.layout[1]]), 32);
+            else e = align_up(joint_half_elems(vp.K, P.v[vp.joint].K, g->K[vp.z]) * vp.jupper, 32);
+        } else if (vp.classes || (vp.absorbed >= 0 && !g->keep_tables)) {
             // no blocks
         } else if (vp.kernel == kRows) {
             e += align_up(vp.MO * vp.K * vp.ldz, 32);
@@ -1877,7 +1929,8 @@ extern "C" pase_status pase_vertex_info_get(pase_graph_t g, uint32_t v, pase_ver
         x.key_bound = x.table_bound = ~0ull;
     }
     x.key_type = g->plan_key_type;
-    x.fused = vp.fuse_into >= 0 ? 1u : vp.fused_from >= 0 ? 2u : 0u;
+    x.fused = vp.fuse_into >= 0 || (vp.absorbed >= 0 && g->plan.v[vp.absorbed].exch) ? 1u
+              : vp.fused_from >= 0 || vp.exch ? 2u : 0u;
     x.prep_after = vp.prep_after;
     x.prep_lane = (uint32_t)vp.prep_lane;
     *out = x;

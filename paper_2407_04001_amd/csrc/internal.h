@@ -338,6 +338,49 @@ inline uint64_t joint_lds(uint64_t Ki, uint64_t Kj, uint64_t oi, uint64_t yi, ui
 }
 inline uint64_t half_lds(uint64_t Kj, uint64_t oj, uint64_t yj) { return 8 * (16 + 2 * oj + 2 * yj + Kj); }
 
+// Exchange fill.  A pair (j, i) where j has no edges and three lookups
+// of one digit each -- A over v_i, B over y, C over z -- and i, with an edge
+// to y and one to z, reads T_j alone:
+//     T_i[y][z] = min_x L_i[x] + t1(x, y) + t2(x, z) + min_c L_j[c] + A[c][x] + B[c][y] + C[c][z].
+// With the minima exchanged the inner one, over x at a fixed c, is that of
+// A'[x] = A[c][x] + L_i[x] plus two split-match edges, each of which is 0
+// (same class), f of x or f of the other end: minima of A' over everything, a
+// class of y, a class of z, or both.  So per c a few arrays over y and over z
+// (the half table), and
+//     T_i[y][z] = min_c min( a1[c][y] + C[c][z] + f2(z),  b1[c][y] + C[c][z],
+//                            B[c][y] + g[c][z] + f1(y),   B[c][y] + d[c][z],
+//                            B[c][y] + C[c][z] + I[c][x both classes] ):
+// about ten operations per (c, y, z) instead of two per (c, x, y, z), and T_j
+// is never formed.  Every case is a key of some x or an upper bound of one, so
+// minimum and lowest argmin are those of the two dense fills; j's argmin is
+// evaluated in the back-substitution.
+struct ExchLookup {           // one-digit lookup of v_j
+    const void *ptr;
+    uint32_t sc, sd;          // element strides of c and of the digit
+};
+
+struct ExchArgs {
+    const void *Li, *Lj;      // key-space layer costs
+    ExchLookup l[3];          // over x = v_i, y, z (v_j's key space)
+    const void *f1x, *f1y, *f2x, *f2z;   // f of the edges to y and z, by x and by the other end (v_i's)
+    // class tables of x by the edges to y and z
+    const uint16_t *perm1, *first1, *first2;
+    const uint32_t *zr1, *zr2;
+    // per c: a1, b1 and B by y (Kyp each), C, g and d by z, I by x
+    void *half;
+    void *T;                  // index y * Kz + z
+    uint16_t *A;
+    uint32_t Ki, Kj, Ky, Kyp, Kz;   // Kyp: Ky rounded up to kExchCols
+    int32_t shift;            // v_j's keys x 2^shift are v_i's
+    uint32_t bits, out_shift;
+    uint32_t nblk, lds;       // workgroups of the fill; dynamic LDS of the half fill
+};
+
+constexpr uint32_t kExchCols = 4;             // y's per workgroup of the fill (one per wave in its last step)
+constexpr uint32_t kExchMaxK = 1024;          // v_i's configurations (48 bytes of LDS each)
+inline uint64_t exch_half_elems(uint64_t Ki, uint64_t Kj, uint64_t Kyp, uint64_t Kz) { return Kj * (3 * Kyp + 3 * Kz + Ki); }
+inline uint64_t exch_lds(uint64_t Ki) { return 8 * (4 + 5 * Ki) + 6 * Ki + 16; }
+
 constexpr uint32_t kClassMaxK = 4096;         // configurations of either end of the class edge
 constexpr uint32_t kClassMaxLds = 64 << 10;   // two workgroups per CU (160 KB) with room beside them
 constexpr uint32_t kClassTabLanes = 16;       // threads per configuration of the class tables' counting
@@ -389,7 +432,7 @@ struct TermRef {
 };
 
 // Kinds of launch descriptors: a vertex has those its launches need.
-enum DescKind { kDescPrep, kDescRows, kDescGeneric, kDescReduce, kDescDirect, kDescClass, kDescJoint, kDescKinds };
+enum DescKind { kDescPrep, kDescRows, kDescGeneric, kDescReduce, kDescDirect, kDescClass, kDescJoint, kDescExch, kDescKinds };
 
 enum KernelKind { kGeneric = 0, kRows = 1, kDirect = 2 };
 
@@ -418,6 +461,9 @@ struct VPlan {
     // the digit y, R the rest digits, and four class tables (i to y, j to y, j to i, i to j)
     int joint = -1;
     int jtab[4] = {-1, -1, -1, -1};
+    // exchange fill: joint names the other vertex as well; the first two of jtab are v_i to y and to z, the
+    // plan digits
+    bool exch = false;
     int jshape = -1;                // its class ids
     uint32_t jcls[4] = {0, 0, 0, 0};   // classes: i and j to y, j to i, i to j
     uint64_t jupper = 1;            // product of the upper digits (the first of R)

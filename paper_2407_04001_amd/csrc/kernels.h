@@ -1721,6 +1721,179 @@ __device__ __forceinline__ void joint_item(const JointArgs &a, uint32_t b, char 
     }
 }
 
+// ------------------------------------------------------------------ exchange fill
+// What a class without configurations reads as: past every key, and summed
+// with two of them still no more than 2^63.
+template <typename KeyT> __device__ __forceinline__ KeyT exch_none() {
+    if constexpr (std::is_same<KeyT, double>::value) return KeyOps<double>::sentinel();
+    else return (KeyT)1 << 62;
+}
+
+// Half fill of an exchange: workgroup c evaluates A' = A[c][x] + L_i[x] over all
+// x and its minima over the classes to y and to z (in LDS, by the class's first
+// place), then what the fill reads by y and by z.  The lowest x of a pair of
+// classes holds their common minimum.  Bound by latency (a few memory round
+// trips, Kj workgroups).
+template <typename KeyT>
+__device__ __forceinline__ void exch_half_item(const ExchArgs &a, uint32_t c, char *lds) {
+    using Ops = KeyOps<KeyT>;
+    using Val = typename Ops::Val;
+    const uint32_t tid = threadIdx.x, lane = tid & 63, Ki = a.Ki, Ky = a.Ky, Kz = a.Kz;
+    uint64_t *sl = (uint64_t *)lds, *P1 = sl + 4, *P2 = P1 + Ki, *Q1 = P2 + Ki, *Q2 = Q1 + Ki, *I = Q2 + Ki;
+    uint16_t *pm = (uint16_t *)(I + Ki), *c1 = pm + Ki, *c2 = c1 + Ki;
+    const Glb<KeyT> out = (Glb<KeyT>)(uintptr_t)a.half + c * (3 * (uint64_t)a.Kyp + 3 * (uint64_t)Kz + Ki);
+    auto look = [&](int k, uint32_t d) -> KeyT {
+        const Val v = glb<Val>(a.l[k].ptr)[(uint64_t)c * a.l[k].sc + (uint64_t)d * a.l[k].sd];
+        return shift_key(__builtin_bit_cast(KeyT, v), a.shift);
+    };
+    for (uint32_t k = tid; k < 4 + 5 * Ki; k += blockDim.x) sl[k] = ~0ull;
+    for (uint32_t x = tid; x < Ki; x += blockDim.x) {
+        pm[x] = glb<uint16_t>(a.perm1)[x];
+        c1[x] = glb<uint16_t>(a.first1)[x];
+        c2[x] = glb<uint16_t>(a.first2)[x];
+    }
+    __syncthreads();
+    KeyT m[4] = {Ops::sentinel(), Ops::sentinel(), Ops::sentinel(), Ops::sentinel()};
+    for (uint32_t x = tid; x < Ki; x += blockDim.x) {
+        const KeyT v = Ops::add(glb<KeyT>(a.Li)[x], look(0, x)), f1 = glb<KeyT>(a.f1x)[x], f2 = glb<KeyT>(a.f2x)[x];
+        const KeyT v1 = Ops::add(v, f1), v2 = Ops::add(v, f2);
+        m[0] = Ops::min(m[0], v);
+        m[1] = Ops::min(m[1], v1);
+        m[2] = Ops::min(m[2], v2);
+        m[3] = Ops::min(m[3], Ops::add(v1, f2));
+        lds_min(&P1[c1[x]], v);
+        lds_min(&P2[c1[x]], v2);
+        lds_min(&Q1[c2[x]], v);
+        lds_min(&Q2[c2[x]], v1);
+        uint32_t p = c1[x];   // (ends at x itself at the latest)
+        while (c2[pm[p]] != c2[x]) p++;
+        lds_min(&I[pm[p]], v);
+    }
+    KeyT r[1];
+    wave_minima<4>(m, r);
+    if ((lane & 15) == 15) lds_min(&sl[lane >> 4], r[0]);
+    __syncthreads();
+    const KeyT s0 = lds_key<KeyT>(&sl[0]), s1 = lds_key<KeyT>(&sl[1]), s2 = lds_key<KeyT>(&sl[2]),
+               s3 = lds_key<KeyT>(&sl[3]);
+    const KeyT lj = shift_key((KeyT)(glb<KeyT>(a.Lj)[c] - (KeyT)c), a.shift);
+    for (uint32_t y = tid; y < a.Kyp; y += blockDim.x) {
+        const uint32_t w = min(y, Ky - 1), q = glb<uint32_t>(a.zr1)[w];
+        const KeyT f = glb<KeyT>(a.f1y)[w], b = Ops::add(lj, look(1, w));
+        KeyT u = Ops::min(Ops::add(s0, f), s1), v = Ops::min(Ops::add(s2, f), s3);
+        if (q >> 16) {
+            u = Ops::min(u, lds_key<KeyT>(&P1[q & 0xffff]));
+            v = Ops::min(v, lds_key<KeyT>(&P2[q & 0xffff]));
+        }
+        out[y] = Ops::add(u, b);
+        out[a.Kyp + y] = Ops::add(v, b);
+        out[2 * (uint64_t)a.Kyp + y] = b;
+    }
+    const Glb<KeyT> oz = out + 3 * (uint64_t)a.Kyp;
+    for (uint32_t z = tid; z < Kz; z += blockDim.x) {
+        const uint32_t q = glb<uint32_t>(a.zr2)[z];
+        const KeyT v = look(2, z);
+        oz[z] = v;
+        oz[Kz + z] = q >> 16 ? Ops::add(v, lds_key<KeyT>(&Q1[q & 0xffff])) : exch_none<KeyT>();
+        oz[2 * (uint64_t)Kz + z] = q >> 16 ? Ops::add(v, lds_key<KeyT>(&Q2[q & 0xffff])) : exch_none<KeyT>();
+    }
+    for (uint32_t x = tid; x < Ki; x += blockDim.x)
+        oz[3 * (uint64_t)Kz + x] = I[x] == ~0ull ? exch_none<KeyT>() : lds_key<KeyT>(&I[x]);
+}
+
+struct ExchLds {
+    uint32_t rep[kExchCols][64];       // lowest x in the classes of y and z, or kNoClass
+    uint64_t best[kExchCols][kExchCols][64];   // by wave, y, z
+};
+
+// Exchange fill: a workgroup takes kExchCols y's and 64 z's, one z per lane;
+// its four waves take every fourth c (so that even a table of 462 x 462 entries
+// has four waves per SIMD) and meet in LDS.  What depends on y is uniform over
+// a wave and comes through scalar loads; few (y, z) have an x in both classes,
+// so a wave reads that case only for y's where one of its lanes does.  Bound by
+// the latency of the loads per c.  K = 84, 462, 462, 462: 42 us after a half
+// fill of 9.5 us, against 652 us for the dense fill with the reader's minimum
+// in its epilogue and its prep; K = 203, 731, 731, 731: 184 + 13 us against
+// 5158 us and a generic fill of 1156 us that reads the 3.1 GB table back.
+template <typename KeyT>
+__device__ __forceinline__ void exch_item(const ExchArgs &a, uint32_t b, ExchLds &lds) {
+    using Ops = KeyOps<KeyT>;
+    using Val = typename Ops::Val;
+    constexpr int Y = (int)kExchCols;
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t nz = (a.Kz + 63) / 64, y0 = b / nz * Y, z = b % nz * 64 + lane, zc = min(z, a.Kz - 1);
+    // one y per wave: the lowest x of its class whose class to z is the lane's
+    {
+        const uint32_t y = min(y0 + wave, a.Ky - 1), q = glb<uint32_t>(a.zr1)[y], qz = glb<uint32_t>(a.zr2)[zc];
+        uint32_t rep = kNoClass;
+        for (uint32_t p0 = 0; p0 < q >> 16; p0 += 64) {
+            const uint32_t n = min(64u, (q >> 16) - p0);
+            const uint32_t x = glb<uint16_t>(a.perm1)[(q & 0xffff) + p0 + min(lane, n - 1)];
+            const uint32_t cl = glb<uint16_t>(a.first2)[x];
+            for (uint32_t k = 0; k < n; k++) {
+                const uint32_t xk = __builtin_amdgcn_readlane(x, k), ck = __builtin_amdgcn_readlane(cl, k);
+                if (rep == kNoClass && qz >> 16 && ck == (qz & 0xffff)) rep = xk;
+            }
+        }
+        lds.rep[wave][lane] = rep;
+    }
+    __syncthreads();
+    uint32_t rep[Y];
+    bool any[Y], some = false;
+#pragma unroll
+    for (int k = 0; k < Y; k++) {
+        rep[k] = lds.rep[k][lane];
+        any[k] = __ballot(rep[k] != kNoClass) != 0;
+        some |= any[k];
+    }
+    KeyT t1[Y], t2[Y], t3[Y], t5[Y];
+#pragma unroll
+    for (int k = 0; k < Y; k++) t1[k] = t2[k] = t3[k] = t5[k] = Ops::sentinel();
+    const uint64_t pitch = 3 * (uint64_t)a.Kyp + 3 * (uint64_t)a.Kz + a.Ki;
+    const KeyT *const half = (const KeyT *)a.half;
+#pragma unroll 2
+    for (uint32_t c = wave; c < a.Kj; c += Y) {
+        const KeyT *const __restrict__ hy = half + c * pitch + y0;   // (uniform)
+        const Glb<const KeyT> hz = glb<KeyT>(half + c * pitch + 3 * (uint64_t)a.Kyp);
+        const KeyT C = hz[zc], g = hz[a.Kz + zc], d = hz[2 * (uint64_t)a.Kz + zc];
+#pragma unroll
+        for (int k = 0; k < Y; k++) {
+            const KeyT a1 = hy[k], b1 = hy[a.Kyp + k], B = hy[2 * (uint64_t)a.Kyp + k];
+            t1[k] = Ops::min(t1[k], Ops::add(a1, C));
+            t2[k] = Ops::min(t2[k], Ops::min(Ops::add(b1, C), Ops::add(B, d)));
+            t3[k] = Ops::min(t3[k], Ops::add(B, g));
+        }
+        if (some) {
+#pragma unroll
+            for (int k = 0; k < Y; k++)
+                if (any[k]) {
+                    const KeyT x = hz[3 * (uint64_t)a.Kz + min(rep[k], a.Ki - 1)];
+                    t5[k] = Ops::min(t5[k], Ops::add(Ops::add(hy[2 * (uint64_t)a.Kyp + k], C), x));
+                }
+        }
+    }
+    const KeyT fz = glb<KeyT>(a.f2z)[zc];
+#pragma unroll
+    for (int k = 0; k < Y; k++) {
+        const KeyT fy = glb<KeyT>(a.f1y)[min(y0 + k, a.Ky - 1)];
+        // (a wave without a c holds sentinels only)
+        KeyT v = wave < a.Kj ? Ops::min(t2[k], Ops::min(Ops::add(t1[k], fz), Ops::add(t3[k], fy))) : Ops::sentinel();
+        if (rep[k] != kNoClass) v = Ops::min(v, t5[k]);
+        lds.best[wave][k][lane] = __builtin_bit_cast(uint64_t, v);
+    }
+    __syncthreads();
+    const uint32_t y = y0 + wave;
+    if (y >= a.Ky || z >= a.Kz) return;
+    KeyT best = Ops::sentinel();
+#pragma unroll
+    for (int w = 0; w < Y; w++) best = Ops::min(best, __builtin_bit_cast(KeyT, lds.best[w][wave][lane]));
+    Val v;
+    uint32_t x;
+    Ops::split(best, a.bits, a.out_shift, v, x);
+    const uint64_t idx = (uint64_t)y * a.Kz + z;
+    ((Glb<Val>)(uintptr_t)a.T)[idx] = v;
+    ((Glb<uint16_t>)(uintptr_t)a.A)[idx] = (uint16_t)x;
+}
+
 // The lowest optimal configuration of one entry of a vertex described by class
 // fill terms, by one wave: w[k] = the configurations of its layout digits (z
 // first when it has one).

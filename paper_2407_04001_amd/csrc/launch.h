@@ -29,12 +29,13 @@ struct Launch {
     ClassArgs ca;
     bool joint = false;    // joint fill
     JointArgs ja;
+    ExchArgs xa;           // exchange fill (joint is set as well)
 };
 
 // A batched launch: vertices (sequence positions) sharing one kernel variant
 // within one launch group, with their first workgroups.
 struct Batch {
-    enum Kind { kPrep, kRows, kGeneric, kReduce, kDirect, kClass, kHalf, kJoint } kind;
+    enum Kind { kPrep, kRows, kGeneric, kReduce, kDirect, kClass, kHalf, kJoint, kExchHalf, kExch } kind;
     int lane;              // lane schedules: the stream it runs on (1 = the caller's)
     int group;             // launch group (a slot, or a (slot, lane) pair) it belongs to
     uint32_t variant;      // rows: (TZ * 4 + TM) * 8 + NA (NA 7 = runtime count); generic: NT (0 = runtime);

@@ -59,7 +59,8 @@ pase_status build_launches(pase_graph_t g, char *ws, std::vector<Launch<KeyT>> &
         const VPlan &vp = P.v[i];
         Launch<KeyT> &L = out[i];
         KeyT *blocks = (KeyT *)(ws + P.off_block + vp.block_off);
-        const bool dense = !vp.classes && vp.joint < 0 && vp.kernel != kDirect;
+        const bool lazy = vp.absorbed >= 0 && !g->keep_tables && !vp.classes;   // of an exchange fill
+        const bool dense = !vp.classes && vp.joint < 0 && vp.kernel != kDirect && !lazy;
         if (dense) std::memset(&L.prep, 0, sizeof L.prep);
         L.prep.blocks = blocks;
         L.prep.vi = (uint32_t)vp.vi;
@@ -148,7 +149,78 @@ pase_status build_launches(pase_graph_t g, char *ws, std::vector<Launch<KeyT>> &
             oc = is_src ? s0 : d0;
             oo = is_src ? d0 : s0;
         };
-        if (vp.joint >= 0) {
+        if (vp.exch) {
+            const VPlan &vj = P.v[vp.joint];
+            ExchArgs &xa = L.xa;
+            std::memset(&xa, 0, sizeof xa);
+            const int y = vp.layout[0], z = vp.layout[1];
+            const KeyT *fk = (const KeyT *)(ws + P.off_fk), *Lk = (const KeyT *)(ws + P.off_Lk);
+            xa.Li = Lk + koff[vp.vi];
+            xa.Lj = Lk + koff[vj.vi];
+            xa.Ki = vp.K;
+            xa.Kj = vj.K;
+            xa.Ky = g->K[y];
+            xa.Kyp = (xa.Ky + kExchCols - 1) / kExchCols * kExchCols;
+            xa.Kz = g->K[z];
+            xa.bits = vp.bits;
+            xa.out_shift = vp.out_shift;
+            xa.shift = (int32_t)vp.bits - (int32_t)vj.bits;
+            if (vp.layout.size() != 2 || vp.stride[1] != 1 || vp.stride[0] != xa.Kz || xa.Ki > kExchMaxK)
+                return fail(g, PASE_ERR_INTERNAL, "exchange fill layout");
+            for (int e : vp.edges) {
+                uint64_t oc, oo;
+                edge_ends(e, vp.vi, oc, oo);
+                const bool to_y = other_of(e) == y;
+                if (!to_y && other_of(e) != z) return fail(g, PASE_ERR_INTERNAL, "exchange fill edge");
+                (to_y ? xa.f1x : xa.f2x) = fk + oc;
+                (to_y ? xa.f1y : xa.f2z) = fk + oo;
+            }
+            if (!xa.f1x || !xa.f2x || vj.terms.size() != 3 || vp.jtab[0] < 0 || vp.jtab[1] < 0) return fail(g, PASE_ERR_INTERNAL, "exchange fill edges");
+            for (const auto &t : vj.terms) {
+                const int k = t.dig[0] == vp.vi ? 0 : t.dig[0] == y ? 1 : t.dig[0] == z ? 2 : -1;
+                uint32_t sdv[kMaxDep], vrad[kMaxDep];
+                if (t.dig.size() != 1 || k < 0 || xa.l[k].ptr) return fail(g, PASE_ERR_INTERNAL, "exchange fill lookup");
+                lookup_strides(P, vp.joint, t.j, xa.l[k].sc, sdv);
+                for (size_t q = 0; q < vj.layout.size(); q++) {
+                    vrad[q] = g->K[vj.layout[q]];
+                    if (vj.layout[q] == t.dig[0]) xa.l[k].sd = sdv[q];
+                }
+                if (max_index(vj.K, xa.l[k].sc, sdv, vrad, (int)vj.layout.size()) >= P.v[t.j].N) bounds_ok = false;
+                xa.l[k].ptr = ws + P.off_T + P.v[t.j].T_off;
+            }
+            const DevClassTab &t1 = P.ctabs[vp.jtab[0]], &t2 = P.ctabs[vp.jtab[1]];
+            xa.perm1 = (const uint16_t *)(ws + t1.perm_off);
+            xa.first1 = (const uint16_t *)(ws + t1.first_off);
+            xa.first2 = (const uint16_t *)(ws + t2.first_off);
+            xa.zr1 = (const uint32_t *)(ws + t1.zr_off);
+            xa.zr2 = (const uint32_t *)(ws + t2.zr_off);
+            xa.half = blocks;
+            boff = exch_half_elems(xa.Ki, xa.Kj, xa.Kyp, xa.Kz);
+            xa.T = ws + P.off_T + vp.T_off;
+            xa.A = (uint16_t *)(ws + P.off_A + vp.A_off);
+            xa.nblk = xa.Kyp / kExchCols * ((xa.Kz + 63) / 64);
+            xa.lds = (uint32_t)exch_lds(xa.Ki);
+            L.joint = true;
+        } else if (lazy) {
+            // not filled: its terms, for one evaluation
+            ClassArgs &ca = L.ca;
+            std::memset(&ca, 0, sizeof ca);
+            ca.Lk = (const KeyT *)(ws + P.off_Lk) + koff[vp.vi];
+            ca.K = vp.K;
+            ca.Kz = 1;
+            ca.bits = vp.bits;
+            ca.rows = 1;
+            ca.nR = (uint32_t)vp.layout.size();
+            for (size_t k = 0; k < vp.layout.size(); k++) ca.rad[k] = g->K[vp.layout[k]];
+            if (!vp.edges.empty() || vp.terms.size() > (size_t)kMaxClassTerms)
+                return fail(g, PASE_ERR_INTERNAL, "a vertex without a table");
+            for (const auto &t : vp.terms) {
+                ClassTerm &ct = ca.t[ca.nt++];
+                lookup_strides(P, i, t.j, ct.sc, ct.sd);
+                if (max_index(vp.K, ct.sc, ct.sd, rad, m) >= P.v[t.j].N) bounds_ok = false;
+                ct.ptr = ws + P.off_T + P.v[t.j].T_off;
+            }
+        } else if (vp.joint >= 0) {
             if constexpr (sizeof(KeyT) != 8) {
                 return fail(g, PASE_ERR_INTERNAL, "joint fill with 128-bit keys");
             } else {
@@ -704,6 +776,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         put(i, kDescDirect, &L.da, sizeof L.da);
         put(i, kDescClass, &L.ca, sizeof L.ca);
         put(i, kDescJoint, &L.ja, sizeof L.ja);
+        put(i, kDescExch, &L.xa, sizeof L.xa);
     }
     RowsArgs *hr = (RowsArgs *)(img + P.off_desc[kDescRows]);
     if (!P.ctabs.empty()) {
@@ -737,11 +810,12 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         if (members.empty()) return;
         Batch b{kind, cur_lane, cur_group, variant, nbe, 0, 0};
         static const DescKind kind_of[] = {kDescPrep, kDescRows, kDescGeneric, kDescReduce,
-                                           kDescDirect, kDescClass, kDescJoint, kDescJoint};
+                                           kDescDirect, kDescClass, kDescJoint, kDescJoint, kDescExch, kDescExch};
         b.idx0 = P.v[members[0]].desc[kind_of[kind]];
         for (int i : members) {
             if (kind == Batch::kJoint) b.lds = std::max(b.lds, launches[i].ja.lds);
             if (kind == Batch::kHalf) b.lds = std::max(b.lds, launches[i].ja.hlds);
+            if (kind == Batch::kExchHalf) b.lds = std::max(b.lds, launches[i].xa.lds);
             if (kind == Batch::kClass) b.lds = std::max(b.lds, launches[i].ca.lds);
             if (nbe >= be_cap) { be_overflow = true; return; }
             hbe[nbe].pos = (uint32_t)i;
@@ -757,7 +831,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         si.batches.push_back(b);
     };
     // per-group scratch, reused across groups (cleared, capacity kept)
-    std::vector<int> prepped, direct, cls, joint, half, grp;
+    std::vector<int> prepped, direct, cls, joint, half, exch, exch_half, grp;
     std::vector<std::pair<uint32_t, int>> rows, gens, reds;
     std::map<uint32_t, int> shape_dom;   // TZ * 4 + TM -> largest vertex of the group
     constexpr bool kF64 = std::is_same<KeyT, double>::value;
@@ -794,18 +868,21 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         cls.clear();
         joint.clear();
         half.clear();
+        exch.clear();
+        exch_half.clear();
         // a fused minimum's blocks are built with its producer's, before the
         // producer's fill reads them; its own fill is a reduction (below)
         std::vector<int> fills;   // members with a prep here or hoisted: rows / generic fills
         for (int i : mem) {
             // (the half fill of a joint fill carries that fill's position)
             if (P.v[i].absorbed >= 0) {
-                if (P.v[P.v[i].absorbed].jearly) half.push_back(P.v[i].absorbed);
+                const VPlan &by = P.v[P.v[i].absorbed];
+                if (by.jearly) (by.exch ? exch_half : half).push_back(P.v[i].absorbed);
                 if (!g->keep_tables) continue;   // no table of its own
             }
             if (launches[i].joint) {
-                joint.push_back(i);
-                if (!P.v[i].jearly) half.push_back(i);
+                (P.v[i].exch ? exch : joint).push_back(i);
+                if (!P.v[i].jearly) (P.v[i].exch ? exch_half : half).push_back(i);
                 continue;
             }
             if (launches[i].cls) cls.push_back(i);
@@ -830,6 +907,8 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         uint32_t half_threads = 64;
         for (int i : half) half_threads = std::max(half_threads, launches[i].ja.threads);
         add_batch(Batch::kHalf, half_threads, half, [](const Launch<KeyT> &L) { return L.ja.hblk; });
+        add_batch(Batch::kExchHalf, 0, exch_half, [](const Launch<KeyT> &L) { return L.xa.Kj; });
+        add_batch(Batch::kExch, 0, exch, [](const Launch<KeyT> &L) { return L.xa.nblk; });
         // joint fills: one launch for one configuration per thread, one for two
         for (uint32_t two = 0; two < 2; two++) {
             uint32_t threads = 64;
@@ -981,13 +1060,13 @@ pase_status plan_check(pase_graph_t g, uint64_t *image_bytes) {
             if (pos >= fills.size()) return fail(g, PASE_ERR_INTERNAL, "batch entry out of range");
             const bool fused = g->plan.v[pos].fused_from >= 0;
             if (b.kind == Batch::kRows || b.kind == Batch::kGeneric || b.kind == Batch::kDirect ||
-                b.kind == Batch::kClass || b.kind == Batch::kJoint ||
+                b.kind == Batch::kClass || b.kind == Batch::kJoint || b.kind == Batch::kExch ||
                 (b.kind == Batch::kReduce && fused)) {
                 fills[pos]++;
                 fill_batch[pos] = (int)bi;
             }
             if (b.kind == Batch::kPrep) prep_batch[pos] = (int)bi;
-            if (b.kind == Batch::kHalf) half_batch[pos] = (int)bi;
+            if (b.kind == Batch::kHalf || b.kind == Batch::kExchHalf) half_batch[pos] = (int)bi;
         }
     }
     // every vertex with blocks has them built before its fill; a hoisted
@@ -995,7 +1074,7 @@ pase_status plan_check(pase_graph_t g, uint64_t *image_bytes) {
     // waited for by the vertex's group
     for (size_t i = 0; i < g->plan.v.size(); i++) {
         const VPlan &vp = g->plan.v[i];
-        if (vp.kernel == kDirect || vp.classes || vp.joint >= 0 || vp.fused_from >= 0) continue;
+        if (vp.kernel == kDirect || vp.classes || vp.joint >= 0 || vp.fused_from >= 0 || fill_batch[i] < 0) continue;
         if (prep_batch[i] < 0 || prep_batch[i] > fill_batch[i])
             return fail(g, PASE_ERR_INTERNAL, "a prep does not precede its fill");
         if (si.hoist && vp.prep_after >= -1) {
