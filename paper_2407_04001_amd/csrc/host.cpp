@@ -1025,8 +1025,8 @@ static pase_status build_plan(pase_graph_t g) {
     // table over all of D(i) = {y, z}, whose vertex j has no edges and only
     // one-digit lookups.  Both of i's edges tight, so that classes are small.
     // Costs ten operations per (c_j, y, z) and two launches, against two per
-    // (c_j, c_i, y, z) and three: 660 -> 52 us at K = 84, 462, 462, 462 and
-    // 5158 + 1156 -> 197 us at 203, 731, 731, 731; from 24 configurations
+    // (c_j, c_i, y, z) and three: 660 -> 35 us at K = 84, 462, 462, 462 and
+    // 5158 + 1156 -> 115 us at 203, 731, 731, 731; from 24 configurations
     // up, like the joint fill.  Not with kept tables (j's is then wanted).
     auto plan_exchange = [&](int i) {
         VPlan &vp = P.v[i];

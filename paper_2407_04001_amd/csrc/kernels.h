@@ -1808,11 +1808,11 @@ struct ExchLds {
 // Exchange fill: a workgroup takes kExchCols y's and 64 z's, one z per lane;
 // its four waves take every fourth c (so that even a table of 462 x 462 entries
 // has four waves per SIMD) and meet in LDS.  What depends on y is uniform over
-// a wave and comes through scalar loads; few (y, z) have an x in both classes,
-// so a wave reads that case only for y's where one of its lanes does.  Bound by
-// the latency of the loads per c.  K = 84, 462, 462, 462: 42 us after a half
+// a wave and comes through scalar loads.  All loads of two c's are in flight
+// together (branches around the few (y, z) with an x in both classes kept them
+// apart: 42 us).  K = 84, 462, 462, 462: 25 us after a half
 // fill of 9.5 us, against 652 us for the dense fill with the reader's minimum
-// in its epilogue and its prep; K = 203, 731, 731, 731: 184 + 13 us against
+// in its epilogue and its prep; K = 203, 731, 731, 731: 102 + 13 us against
 // 5158 us and a generic fill of 1156 us that reads the 3.1 GB table back.
 template <typename KeyT>
 __device__ __forceinline__ void exch_item(const ExchArgs &a, uint32_t b, ExchLds &lds) {
@@ -1837,39 +1837,44 @@ __device__ __forceinline__ void exch_item(const ExchArgs &a, uint32_t b, ExchLds
         lds.rep[wave][lane] = rep;
     }
     __syncthreads();
-    uint32_t rep[Y];
-    bool any[Y], some = false;
+    uint32_t rep[Y], at[Y];
 #pragma unroll
     for (int k = 0; k < Y; k++) {
         rep[k] = lds.rep[k][lane];
-        any[k] = __ballot(rep[k] != kNoClass) != 0;
-        some |= any[k];
+        at[k] = min(rep[k], a.Ki - 1);
     }
     KeyT t1[Y], t2[Y], t3[Y], t5[Y];
 #pragma unroll
     for (int k = 0; k < Y; k++) t1[k] = t2[k] = t3[k] = t5[k] = Ops::sentinel();
     const uint64_t pitch = 3 * (uint64_t)a.Kyp + 3 * (uint64_t)a.Kz + a.Ki;
     const KeyT *const half = (const KeyT *)a.half;
-#pragma unroll 2
-    for (uint32_t c = wave; c < a.Kj; c += Y) {
-        const KeyT *const __restrict__ hy = half + c * pitch + y0;   // (uniform)
-        const Glb<const KeyT> hz = glb<KeyT>(half + c * pitch + 3 * (uint64_t)a.Kyp);
-        const KeyT C = hz[zc], g = hz[a.Kz + zc], d = hz[2 * (uint64_t)a.Kz + zc];
+    constexpr int U = 2;   // c's in flight
+    for (uint32_t c = wave; c < a.Kj; c += U * Y) {
+        KeyT C[U], g[U], d[U], x[U][Y], h[U][3][Y];
 #pragma unroll
-        for (int k = 0; k < Y; k++) {
-            const KeyT a1 = hy[k], b1 = hy[a.Kyp + k], B = hy[2 * (uint64_t)a.Kyp + k];
-            t1[k] = Ops::min(t1[k], Ops::add(a1, C));
-            t2[k] = Ops::min(t2[k], Ops::min(Ops::add(b1, C), Ops::add(B, d)));
-            t3[k] = Ops::min(t3[k], Ops::add(B, g));
-        }
-        if (some) {
+        for (int u = 0; u < U; u++) {   // (past the end: the wave's first again)
+            const uint64_t cu = c + u * Y < a.Kj ? c + u * Y : c;
+            const Glb<const KeyT> hz = glb<KeyT>(half + cu * pitch + 3 * (uint64_t)a.Kyp);
+            C[u] = hz[zc];
+            g[u] = hz[a.Kz + zc];
+            d[u] = hz[2 * (uint64_t)a.Kz + zc];
 #pragma unroll
-            for (int k = 0; k < Y; k++)
-                if (any[k]) {
-                    const KeyT x = hz[3 * (uint64_t)a.Kz + min(rep[k], a.Ki - 1)];
-                    t5[k] = Ops::min(t5[k], Ops::add(Ops::add(hy[2 * (uint64_t)a.Kyp + k], C), x));
-                }
+            for (int k = 0; k < Y; k++) x[u][k] = hz[3 * (uint64_t)a.Kz + at[k]];
+            const auto hy = (const __attribute__((address_space(4))) KeyT *)(uintptr_t)(half + cu * pitch + y0);
+#pragma unroll
+            for (int q = 0; q < 3; q++)
+#pragma unroll
+                for (int k = 0; k < Y; k++) h[u][q][k] = hy[(uint64_t)q * a.Kyp + k];
         }
+#pragma unroll
+        for (int u = 0; u < U; u++)
+#pragma unroll
+            for (int k = 0; k < Y; k++) {
+                t1[k] = Ops::min(t1[k], Ops::add(h[u][0][k], C[u]));
+                t2[k] = Ops::min(t2[k], Ops::min(Ops::add(h[u][1][k], C[u]), Ops::add(h[u][2][k], d[u])));
+                t3[k] = Ops::min(t3[k], Ops::add(h[u][2][k], g[u]));
+                t5[k] = Ops::min(t5[k], Ops::add(Ops::add(h[u][2][k], C[u]), x[u][k]));
+            }
     }
     const KeyT fz = glb<KeyT>(a.f2z)[zc];
 #pragma unroll
