@@ -354,10 +354,12 @@ __global__ __launch_bounds__(512, MANY ? 3 : 6) void k_fill_class(const ClassArg
 #undef PASE_CLASS
 }
 
-// U: configurations per thread (2 when one of the three counts is past the
-// workgroup's 512 threads; its registers would halve the waves of the others).
-template <typename KeyT, int U>
-__global__ __launch_bounds__(512, U == 1 ? 6 : 4) void k_fill_joint(const JointArgs *__restrict__ descs,
+// U: configurations per thread.  MAX: threads per workgroup: 512, or 768 when
+// one of the three counts is past that, so that one configuration per thread
+// still does (148 393 rows at K = 731: 2864 us, 3016 us with 512 threads of
+// two); two per thread (past 768) need registers for half the waves.
+template <typename KeyT, int U, int MAX>
+__global__ __launch_bounds__(MAX, U == 1 ? 6 : 4) void k_fill_joint(const JointArgs *__restrict__ descs,
                                                                     const BatchEntry *__restrict__ be, uint32_t nbe,
                                                                     uint32_t one, uint32_t prio) {
     extern __shared__ __align__(16) char lds[];
@@ -971,11 +973,14 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
             } else if (b.kind == Batch::kJoint) {
                 const uint32_t one = b.nentries == 1 ? b.idx0 : ~0u, prio = si.lanes && b.lane == 0;
                 const dim3 threads(b.variant & ~1u);
-                if (b.variant & 1u)
-                    hipExtLaunchKernelGGL((k_fill_joint<KeyT, 2>), dim3(b.blocks), threads, b.lds, bs, e0, e1, 0, dj, e,
+                if (!(b.variant & 1u) && threads.x > 512)
+                    hipExtLaunchKernelGGL((k_fill_joint<KeyT, 1, 768>), dim3(b.blocks), threads, b.lds, bs, e0, e1, 0, dj,
+                                          e, b.nentries, one, prio);
+                else if (b.variant & 1u)
+                    hipExtLaunchKernelGGL((k_fill_joint<KeyT, 2, 512>), dim3(b.blocks), threads, b.lds, bs, e0, e1, 0, dj, e,
                                           b.nentries, one, prio);
                 else
-                    hipExtLaunchKernelGGL((k_fill_joint<KeyT, 1>), dim3(b.blocks), threads, b.lds, bs, e0, e1, 0, dj, e,
+                    hipExtLaunchKernelGGL((k_fill_joint<KeyT, 1, 512>), dim3(b.blocks), threads, b.lds, bs, e0, e1, 0, dj, e,
                                           b.nentries, one, prio);
             } else if (b.kind == Batch::kExchHalf) {
                 hipExtLaunchKernelGGL((k_exch_half<KeyT>), dim3(b.blocks), dim3(256), b.lds, bs, e0, e1, 0, dxc, e,

@@ -329,7 +329,7 @@ struct JointArgs {
     uint32_t nblk, hblk, threads, lds, hlds;   // h: of the half fill
 };
 
-constexpr uint32_t kJointMaxK = 1024;         // two configurations per thread of a 512-thread workgroup
+constexpr uint32_t kJointMaxK = 1024;         // past 768: two configurations per thread of a 512-thread workgroup
 constexpr uint32_t kJointTerms = 2;           // rest edges, and lookups, per side
 constexpr uint32_t kJointMaxLds = 80 << 10;   // two workgroups per CU
 inline uint64_t joint_half_elems(uint64_t Ki, uint64_t Kj, uint64_t Ky) { return 2 * Ki + Kj + 3 * Ky; }

@@ -1522,7 +1522,9 @@ __device__ __forceinline__ void half_item(const JointArgs &a, uint32_t b, char *
 // dense fill and its prep; the fourth decoder's key/value projection (38808
 // rows) 311 us against 613 + 162 us -- and the five tables these two kinds read,
 // 180 MB each, are not formed at all (level 0: 244 -> 21 us).  140 registers
-// instead of 80 (one workgroup per CU instead of three) took 131 and 654 us.
+// instead of 80 (one workgroup per CU instead of three) took 131 and 654 us;
+// class members read four at a time, the last one repeated, 80 and 364 us (the
+// reads and minima issued count, not their latency).
 template <typename KeyT, int U, bool HASE>
 __device__ __forceinline__ void joint_item(const JointArgs &a, uint32_t b, char *lds) {
     using Ops = KeyOps<KeyT>;

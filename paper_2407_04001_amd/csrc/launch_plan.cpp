@@ -304,7 +304,8 @@ pase_status build_launches(pase_graph_t g, char *ws, std::vector<Launch<KeyT>> &
                 ja.T = ws + P.off_T + vp.T_off;
                 ja.A = (uint16_t *)(ws + P.off_A + vp.A_off);
                 const uint32_t most = std::max(std::max(vp.K, vj.K), ja.Ky);
-                ja.threads = std::min<uint32_t>(512, (most + 63) / 64 * 64);
+                // (one configuration per thread up to 768; past that 512 threads with two)
+                ja.threads = most <= 768 ? (most + 63) / 64 * 64 : 512;
                 if (most > kJointMaxK || (uint64_t)ja.threads * 2 < most) return fail(g, PASE_ERR_INTERNAL, "joint size");
                 ja.lds = (uint32_t)joint_lds(vp.K, vj.K, ja.oi, ja.yi, ja.yj, ja.has_e);
                 ja.hlds = (uint32_t)half_lds(vj.K, ja.oj, ja.yj);
@@ -905,7 +906,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
         }
         add_batch(Batch::kPrep, 0, prepped, [](const Launch<KeyT> &L) { return L.prep.nwg; });
         uint32_t half_threads = 64;
-        for (int i : half) half_threads = std::max(half_threads, launches[i].ja.threads);
+        for (int i : half) half_threads = std::max(half_threads, std::min<uint32_t>(512, launches[i].ja.threads));
         add_batch(Batch::kHalf, half_threads, half, [](const Launch<KeyT> &L) { return L.ja.hblk; });
         add_batch(Batch::kExchHalf, 0, exch_half, [](const Launch<KeyT> &L) { return L.xa.Kj; });
         add_batch(Batch::kExch, 0, exch, [](const Launch<KeyT> &L) { return L.xa.nblk; });

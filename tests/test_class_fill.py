@@ -192,7 +192,7 @@ def triangle(di, dj, dy, has_e, looks, perm=False, r=1, upper=2):
 
 
 # (dims of v_i, v_j, y; edge from v_i to y; v_j looks a table up; permuted maps; p, every integer): K 35 to
-# 252 on one configuration per thread, 700 and more on two; classes of one and of several configurations
+# 252 on one configuration per thread, 738 on one of 768 threads, 796 on two; classes of one and of several configurations
 TRIANGLES = [(4, 4, 4, True, False, False, 8, False), (4, 4, 4, True, True, True, 16, False),
              (5, 4, 4, True, False, True, 16, False), (4, 5, 4, True, True, False, 16, False),
              (4, 4, 3, False, False, True, 16, False), (4, 4, 3, False, True, False, 32, False),
