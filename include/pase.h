@@ -406,7 +406,8 @@ typedef struct {
     int32_t prep_after;   /* its prep blocks read only tables of slots up to this one (-1: none) and are
                              built right after it, beside the launches of the slots in between -- on a
                              side stream (level layout) or at the end of that slot's launches on lane
-                             prep_lane (schedules 4 and 5); -2 = built in its own slot */
+                             prep_lane (schedules 4 and 5); -2 = built in its own slot.  A joint
+                             fill: the slot of its half fill, when that reads tables */
     uint32_t prep_lane;   /* schedules 4 and 5, prep_after >= 0: the lane its prep runs on (that of the
                              tables it reads) */
 } pase_vertex_info;
