@@ -874,6 +874,16 @@ static pase_status build_plan(pase_graph_t g) {
         vp.est_us = 6.0 + (double)vp.MR * (1.2e-3 + 1.5e-5 * vp.K);
         return true;
     };
+    // A column-less vertex without edges (its lookups alone) takes the class
+    // kernel's plain minimum while its lookups fit the 32 MB of L2: no prep
+    // launch (26 -> 17 us at 3.3e6 cells).  Past that the row kernel's stream
+    // is the faster one (80 + 5 against 93 us at 1.8e7 cells, 145 + 5 against
+    // 175 at 3.0e7).
+    auto stream_small = [&](const VPlan &vp) {
+        uint64_t looked = 0;
+        for (const auto &t : vp.terms) looked += P.v[t.j].N * 8;
+        return vp.edges.empty() && looked <= (32ull << 20);
+    };
     auto plan_one = [&](int i, uint32_t ftz, uint32_t ftm, bool no_split) {
         VPlan &vp = P.v[i];
         vp.classes = vp.exch = false;
@@ -987,6 +997,8 @@ static pase_status build_plan(pase_graph_t g) {
         }
         if (joint && (!best.ok || jointp.est_us <= std::max(best.cost, 8.0) + 8.0)) {
             vp = jointp;
+            vp.kernel = kRows;
+        } else if (best.ok && best.z < 0 && !ftz && kernel_mode == 0 && stream_small(vp) && plan_class(i, true)) {
             vp.kernel = kRows;
         } else if (best.ok) {
             vp.kernel = kRows;

@@ -152,6 +152,38 @@ def test_volume_minimum(shape, key):
             assert pg.fingerprint(v) == o.fingerprint(i), (v, cells, pg.vertex_info(v))
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("p,every", [(16, False), (7, True)])
+@pytest.mark.parametrize("key", [0, 1])
+def test_lookups_alone(p, every, key):
+    """A vertex without edges past the direct size (the decoder's context GEMM:
+    no column digit fits, its lookups are small) on the plain minimum: every
+    table against the oracle, and the strategy without kept tables."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_04001_amd import pase as P
+    from oracle.oracle import Oracle
+    from workloads import transformer
+    g = transformer(p=p, enc_layers=1, dec_layers=2)
+    print(f"lookups alone p={p} every={every} key={key}", flush=True)
+    o = Oracle(g)
+    o.configs(p, all_integers=every)
+    o.solve(threads=os.cpu_count() or 1)
+    pg = P.Graph(g)
+    pg.set_option(P.OPT_DIRECT_CELLS, 1)
+    pg.enumerate_configs(p, all_integers=every)
+    pg.set_option(P.OPT_KEY_TYPE, key)
+    info = [pg.vertex_info(v) for v in range(pg.nv)]
+    assert any(x["kernel"] == 1 and x["column"] == -1 and x["tile_cols"] == 0 for x in info)
+    for keep in (1, 0):
+        pg.set_option(P.OPT_KEEP_TABLES, keep)
+        assert pg.find_best_strategy() == o.result()
+        if keep:
+            for i, v in enumerate(o.sequence()):
+                assert pg.fingerprint(v) == o.fingerprint(i), (v, pg.vertex_info(v))
+
+
 # ------------------------------------------------------------------ joint fill
 def triangle(di, dj, dy, has_e, looks, perm=False, r=1, upper=2):
     """v_j (1) joined to v_i (2), y (3) and an upper digit (4); v_i joined to y
