@@ -1287,9 +1287,6 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
     off = align_up(off + n * sizeof(BacktrackDesc), A);
     // launch descriptors: only those that some launch reads (all kinds for all
     // vertices were 4 KB a vertex, half of the upload)
-    static const uint64_t kDescBytes[kDescKinds] = {sizeof(PrepArgs), sizeof(RowsArgs), sizeof(GenericArgs),
-                                                    sizeof(ReduceArgs), sizeof(DirectArgs), sizeof(ClassArgs),
-                                                    sizeof(JointArgs), sizeof(ExchArgs)};
     std::fill(std::begin(P.ndesc), std::end(P.ndesc), 0u);
     for (auto &vp : P.v) {
         const bool lazy = vp.absorbed >= 0 && !g->keep_tables;   // (evaluated with the terms of a class fill)

@@ -434,6 +434,10 @@ struct TermRef {
 // Kinds of launch descriptors: a vertex has those its launches need.
 enum DescKind { kDescPrep, kDescRows, kDescGeneric, kDescReduce, kDescDirect, kDescClass, kDescJoint, kDescExch, kDescKinds };
 
+// bytes of one descriptor of each kind
+constexpr uint64_t kDescBytes[kDescKinds] = {sizeof(PrepArgs), sizeof(RowsArgs), sizeof(GenericArgs), sizeof(ReduceArgs),
+                                             sizeof(DirectArgs), sizeof(ClassArgs), sizeof(JointArgs), sizeof(ExchArgs)};
+
 enum KernelKind { kGeneric = 0, kRows = 1, kDirect = 2 };
 
 struct VPlan {

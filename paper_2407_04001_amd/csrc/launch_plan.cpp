@@ -760,25 +760,33 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
     std::memcpy(img + P.off_bt, bt.data(), n * sizeof(BacktrackDesc));
 
     // ---- kernel descriptors, by kind
-    auto put = [&](int i, DescKind k, const void *src, size_t bytes) {
-        const uint32_t at = P.v[i].desc[k];
-        if (at == ~0u) return;
-        std::memcpy(img + P.off_desc[k] + (uint64_t)at * bytes, src, bytes);
-    };
     for (int k = 0; k < kDescKinds; k++)
-        if ((st = region(P.off_desc[k], 0, k + 1 < kDescKinds ? P.off_desc[k + 1] : P.off_batch, "descriptors")) != PASE_OK)
+        if ((st = region(P.off_desc[k], P.ndesc[k] * kDescBytes[k], k + 1 < kDescKinds ? P.off_desc[k + 1] : P.off_batch,
+                         "descriptors")) != PASE_OK)
             return st;
+    bool no_desc = false;   // a descriptor index past those of its kind
+    auto has_desc = [&](int i, DescKind k) {
+        no_desc |= P.v[i].desc[k] >= P.ndesc[k];
+        return P.v[i].desc[k] < P.ndesc[k];
+    };
+    auto put = [&](int i, DescKind k, const auto &src) {
+        if (P.v[i].desc[k] == ~0u) return;   // the vertex has none of this kind
+        no_desc |= sizeof src != kDescBytes[k];
+        if (has_desc(i, k)) std::memcpy(img + P.off_desc[k] + P.v[i].desc[k] * kDescBytes[k], &src, kDescBytes[k]);
+    };
     for (int i = 0; i < n; i++) {
         const Launch<KeyT> &L = launches[i];
-        put(i, kDescPrep, &L.prep, sizeof L.prep);
-        put(i, kDescRows, &L.ra, sizeof L.ra);
-        put(i, kDescGeneric, &L.ga, sizeof L.ga);
-        put(i, kDescReduce, &L.red, sizeof L.red);
-        put(i, kDescDirect, &L.da, sizeof L.da);
-        put(i, kDescClass, &L.ca, sizeof L.ca);
-        put(i, kDescJoint, &L.ja, sizeof L.ja);
-        put(i, kDescExch, &L.xa, sizeof L.xa);
+        put(i, kDescPrep, L.prep);
+        put(i, kDescRows, L.ra);
+        put(i, kDescGeneric, L.ga);
+        put(i, kDescReduce, L.red);
+        put(i, kDescDirect, L.da);
+        put(i, kDescClass, L.ca);
+        put(i, kDescJoint, L.ja);
+        put(i, kDescExch, L.xa);
+        if (P.v[i].absorbed >= 0 && !g->keep_tables) has_desc(i, kDescClass);   // (read by the back-substitution)
     }
+    if (no_desc) return fail(g, PASE_ERR_INTERNAL, "a descriptor past those of its kind");
     RowsArgs *hr = (RowsArgs *)(img + P.off_desc[kDescRows]);
     if (!P.ctabs.empty()) {
         if ((st = region(P.off_ctdesc, P.ctabs.size() * sizeof(DevClassTab), P.off_jtdesc, "class tables")) != PASE_OK) return st;
@@ -805,7 +813,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
     for (int i = 0; i < n; i++) si.groups[(size_t)P.v[i].slot * nl + (si.lanes ? P.v[i].lane : 0)].push_back(i);
     for (size_t k = 0; k < si.groups.size(); k++) si.group_lane[k] = (int)(k % nl);
     int cur_lane = 0, cur_group = 0;
-    bool be_overflow = false, no_desc = false;
+    bool be_overflow = false;
     auto add_batch = [&](Batch::Kind kind, uint32_t variant, const std::vector<int> &members,
                          uint32_t (*nblk)(const Launch<KeyT> &)) {
         if (members.empty()) return;
@@ -821,7 +829,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
             if (nbe >= be_cap) { be_overflow = true; return; }
             hbe[nbe].pos = (uint32_t)i;
             hbe[nbe].idx = P.v[i].desc[kind_of[kind]];
-            if (hbe[nbe].idx == ~0u) { no_desc = true; return; }
+            if (!has_desc(i, kind_of[kind])) return;
             hbe[nbe].first = b.blocks;
             hbe[nbe].prio = si.lanes && P.v[i].lane == 0 ? 1u : 0u;
             hbe[nbe].kind = 0;
@@ -947,7 +955,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
                 if (kF64) {
                     const int d = shape_dom[P.v[i].TZ * 4 + P.v[i].TM];
                     const uint32_t nd = std::min<uint32_t>(launches[d].ra.na, 4);
-                    if (d != i && na < nd && P.v[i].est_us <= 0.5 * P.v[d].est_us) {
+                    if (d != i && na < nd && P.v[i].est_us <= 0.5 * P.v[d].est_us && has_desc(i, kDescRows)) {
                         RowsArgs &ra = hr[P.v[i].desc[kDescRows]];
                         for (uint32_t t = na; t < nd; t++) {
                             std::memset(&ra.a[t], 0, sizeof ra.a[t]);
@@ -1002,6 +1010,7 @@ pase_status build_image(pase_graph_t g, char *ws, char *img, SearchImage &si, bo
                     if (nbe >= be_cap) { be_overflow = true; break; }
                     hbe[nbe].pos = (uint32_t)i;
                     hbe[nbe].idx = P.v[i].desc[kDescGeneric];
+                    if (!has_desc(i, kDescGeneric)) break;
                     hbe[nbe].first = b.blocks;
                     hbe[nbe].prio = si.lanes && P.v[i].lane == 0 ? 1u : 0u;
                     hbe[nbe].kind = kEntryGeneric2;

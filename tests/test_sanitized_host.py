@@ -12,12 +12,17 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-def test_host_suite_under_address_and_undefined_behaviour_sanitizers():
-    cxx = shutil.which(os.environ.get("CXX", "g++"))
-    if not cxx:
+@pytest.fixture(scope="module")
+def san_lib():
+    if not shutil.which(os.environ.get("CXX", "g++")):
         pytest.skip("no host C++ compiler")
     from paper_2407_04001_amd import build
-    lib = build.build_host_sanitized()
+    return build.build_host_sanitized()
+
+
+def test_host_suite_under_address_and_undefined_behaviour_sanitizers(san_lib):
+    cxx = shutil.which(os.environ.get("CXX", "g++"))
+    lib = san_lib
     asan = subprocess.run([cxx, "-print-file-name=libasan.so"], capture_output=True, text=True).stdout.strip()
     assert os.path.isabs(asan) and os.path.exists(asan), asan
     env = dict(os.environ, LD_PRELOAD=asan,
@@ -29,3 +34,71 @@ def test_host_suite_under_address_and_undefined_behaviour_sanitizers():
     tail = (r.stdout + r.stderr)[-4000:]
     assert r.returncode == 0, tail
     assert " passed" in r.stdout, tail
+
+
+# A chain whose middle vertices take the class fill (or, in the generic kernel
+# mode, prep + generic fills); then one vertex's descriptor index, or the number
+# of descriptors the memory layout made room for, is put out of step with the
+# other, as a planner mistake would.
+DESCRIPTORS = r"""
+#include <cstdio>
+#include <cstring>
+#include "internal.h"
+using namespace pase;
+int main() {
+    for (int mode = 0; mode < 2; mode++) {
+        pase_vertex_desc v[5];
+        pase_edge_desc e[4];
+        std::memset(v, 0, sizeof v);
+        std::memset(e, 0, sizeof e);
+        for (auto &x : v) { x.ndims = 2; x.size[0] = x.size[1] = 64; x.flops_per_point = 2; }
+        for (uint32_t k = 0; k < 4; k++) {
+            e[k].src = k; e[k].dst = k + 1; e[k].rank = 1; e[k].elems = 64;
+        }
+        pase_cost_params par{8, 0};
+        pase_graph_t g;
+        if (pase_graph_create(v, 5, e, 4, &par, &g) != PASE_OK) return 1;
+        pase_set_option(g, PASE_OPT_KERNEL, mode);
+        if (pase_enumerate_configs(g, 16) != PASE_OK) return 2;
+        uint64_t bytes;
+        if (pase_plan_check(g, &bytes) != PASE_OK) return 3;
+        int kinds = 0;
+        for (int k = 0; k < kDescKinds; k++) {
+            Plan &P = g->plan;
+            if (!P.ndesc[k]) continue;
+            kinds++;
+            uint32_t *at = nullptr;
+            for (auto &vp : P.v)
+                if (vp.desc[k] != ~0u) at = &vp.desc[k];
+            const uint32_t was = *at, n = P.ndesc[k];
+            *at = n;            // one past the last
+            if (pase_plan_check(g, &bytes) != PASE_ERR_INTERNAL) return 10 + k;
+            *at = was;
+            P.ndesc[k] = n - 1; // room for one fewer
+            if (pase_plan_check(g, &bytes) != PASE_ERR_INTERNAL) return 20 + k;
+            P.ndesc[k] = n + (uint32_t)((P.off_zero - P.off_desc[k]) / kDescBytes[k]) + 1;   // past its region
+            if (pase_plan_check(g, &bytes) != PASE_ERR_INTERNAL) return 30 + k;
+            P.ndesc[k] = n;
+            if (pase_plan_check(g, &bytes) != PASE_OK) return 4;
+        }
+        if (!kinds) return 5;
+        pase_graph_destroy(g);
+    }
+    std::puts("descriptors ok");
+}
+"""
+
+
+def test_descriptors_stay_in_their_region(san_lib, tmp_path):
+    """A launch descriptor outside the region that the memory layout made for
+    its kind is refused before it is written, not put over the next region."""
+    src = tmp_path / "descriptors.cpp"
+    src.write_text(DESCRIPTORS)
+    exe = str(tmp_path / "descriptors")
+    cxx = os.environ.get("CXX", "g++")
+    subprocess.run([cxx, "-std=c++17", "-g", "-fsanitize=address,undefined", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(ROOT, "paper_2407_04001_amd", "csrc"), str(src), san_lib,
+                    "-Wl,-rpath," + os.path.dirname(san_lib), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120,
+                       env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=1"))
+    assert r.returncode == 0 and "descriptors ok" in r.stdout, (r.returncode, (r.stdout + r.stderr)[-3000:])
