@@ -649,11 +649,11 @@ static pase_status build_plan(pase_graph_t g) {
     const int kernel_mode = g->plan_wide ? 1 : g->kernel_mode;
     // Class fill: with the split match model and no tile knob set, a digit z
     // that meets v_i in one edge and in no lookup.  The digit with the most
-    // configurations leaves the fewest rows.  Always better than the dense
-    // fills where it applies (K * rest instead of K * rest * Kz cells, no prep
-    // launch: 2.05 -> 0.24 ms on the Transformer's largest level at p = 64, 17
-    // -> 6 us on its small chain vertices); a direct vertex without such a
-    // digit takes the same kernel's plain minimum (8.2 -> 5.5 us per launch on
+    // configurations leaves the fewest rows.  K * rest instead of K * rest * Kz
+    // cells and no prep launch (2.05 -> 0.24 ms on the Transformer's largest
+    // level at p = 64, 17 -> 6 us on its small chain vertices), at more work
+    // per cell: not where that digit is small (dense_faster below).  A direct
+    // vertex without such a digit takes the same kernel's plain minimum (8.2 -> 5.5 us per launch on
     // the residual CNN at p = 8).  The tile knobs and a hoisting threshold below its default
     // ask for the dense fills and their preps, which they then get.  With the
     // volume model a direct vertex takes the plain minimum as well, each edge's
@@ -730,6 +730,38 @@ static pase_status build_plan(pase_graph_t g) {
         vp.est_us = 5.0 + std::max((double)vp.N * 10 / 3.5e6,
                                    (double)rows * vp.K * (4.0 + 6.0 * (double)(vp.edges.size() + vp.terms.size())) / 1e7);
         return true;
+    };
+    // Whether the dense fill of a vertex just planned as a class fill takes less
+    // time.  Both sides are fits to 548 measured vertices (K 7 to 924, Kz 5 to
+    // 84, up to 2e5 rows, four edges, a lookup or not): the class fill is its
+    // launch, the evaluations of X (twice without X in LDS; unstaged, every
+    // configuration's data comes from global memory per row), the stores and,
+    // staged, a part per row; the dense one its launch and its prep's, the
+    // cells, the row terms and the stores.  At K = 924 and 2e5 rows the class fill takes 519 us and the dense one 115 at
+    // Kz = 7, 494 and 986 at Kz = 84.  A table that is read whole by a vertex
+    // without a column is read more slowly from the class layout, or not formed
+    // at all by the dense one (fused minimum): 2.7 us per 1e6 entries.  A vertex
+    // that its reader may take into a joint fill stays a class fill.
+    auto dense_faster = [&](int i) {
+        const VPlan &vp = P.v[i];
+        if (vp.z < 0 || vp.consumer < 0) return false;
+        const VPlan &b = P.v[vp.consumer];
+        uint32_t to_reader = 0;
+        for (int e : vp.edges) to_reader += (int)g->E[e].src == b.vi || (int)g->E[e].dst == b.vi;
+        bool joinable = to_reader == 1 && b.K >= 24 && g->K[vp.z] >= 24;
+        for (const auto &t : vp.terms) joinable &= !std::count(t.dig.begin(), t.dig.end(), b.vi);
+        if (joinable) return false;
+        bool whole = b.N * b.K > g->direct_cells;
+        for (int w : b.D) {
+            bool in = false;
+            for (const auto &t : b.terms) in |= t.dig.size() >= 2 && std::count(t.dig.begin(), t.dig.end(), w) > 0;
+            whole &= in;
+        }
+        const double cells = 1e-6 * (double)vp.N * vp.K, entries = 1e-6 * (double)vp.N, rows = 1e-6 * (double)vp.MR;
+        const double ne = (double)vp.edges.size() - 1, nt = (double)vp.terms.size(), evals = rows * vp.K * (vp.keep ? 1 : 2);
+        const double cls = vp.lr >= kClassStagedRows ? 9.0 + 60 * rows + evals * (0.05 + 0.36 * ne + 0.6 * nt) + 1.75 * entries
+                                                     : 7.5 + evals * (4.5 + 0.18 * ne + 0.25 * nt) + 1.9 * entries;
+        return 26.5 + 0.069 * cells + 0.13 * rows * vp.K + 1.07 * entries < cls + (whole ? 2.7 * entries : 0.0);
     };
     // Joint fill: a vertex without a class digit that can take one of its
     // lookups' vertices in (the structure is described at JointSide).  The
@@ -906,9 +938,10 @@ static pase_status build_plan(pase_graph_t g) {
         // (a small vertex of a level that is not all small: the class kernel
         // still needs no prep launch)
         const bool small = g->direct_cells && vp.N * vp.K <= g->direct_cells;
-        if (!ftz && kernel_mode == 0 && plan_class(i, small)) {
+        const bool cls = !ftz && kernel_mode == 0 && plan_class(i, small);
+        if (cls) {
             vp.kernel = small ? kDirect : kRows;
-            return;
+            if (small || !dense_faster(i)) return;
         }
         // the joint fill, unless the dense one below is estimated faster: its
         // rows cost 1.3 ns each at K = 35 (86 us against 27 + 6 us of prep on the
@@ -916,7 +949,7 @@ static pase_status build_plan(pase_graph_t g) {
         // a dense fill takes at least 8 us, and its prep as much
         const VPlan plain = vp;
         VPlan jointp;
-        const bool joint = !ftz && kernel_mode == 0 && plan_joint(i);
+        const bool joint = !cls && !ftz && kernel_mode == 0 && plan_joint(i);
         if (joint) {
             jointp = vp;
             vp = plain;
@@ -995,6 +1028,8 @@ static pase_status build_plan(pase_graph_t g) {
                 if (rc.ok && (!best.ok || rc.cost < best.cost)) best = rc;
             }
         }
+        if (cls && !(best.ok && best.z >= 0)) return;   // (no column: nothing dense to compare with)
+        vp.classes = false;
         if (joint && (!best.ok || jointp.est_us <= std::max(best.cost, 8.0) + 8.0)) {
             vp = jointp;
             vp.kernel = kRows;

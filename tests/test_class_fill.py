@@ -10,16 +10,19 @@ from workloads import random_graph
 from workloads.gen import _Builder
 
 
-def star(dims, elems=(48, 48, 7), sizes=16, r=1):
+def star(dims, elems=(48, 48, 7), sizes=16, r=1, twice=()):
     """v0 with dims[0] loop dims joined to neighbours with dims[1:] loop dims,
     all joined to each other (so v0, the lowest id, comes first and its table
-    has one digit per neighbour); small extents, so that ties are dense."""
+    has one digit per neighbour); small extents, so that ties are dense.
+    twice: neighbours joined to v0 by a second edge (no class digit)."""
     b = _Builder("star", 4, comm_weight=r)
     for k, d in enumerate(dims):
         b.vertex(f"v{k}", [sizes + k] * d, [f"x{i}" for i in range(d)], [d - 1] if d > 1 else [], 1)
     for k in range(1, len(dims)):
         rank = max(1, min(dims[0], dims[k]) - (k == 1))
         b.edge(0, k, list(range(rank)), list(range(rank))[::-1], elems=elems[(k - 1) % 3])
+        if k in twice:
+            b.edge(0, k, list(range(rank)), list(range(rank)), elems=elems[k % 3])
     for k in range(1, len(dims)):
         for m in range(k + 1, len(dims)):
             b.edge(k, m, [0], [0], elems=elems[(k + m) % 3])
@@ -113,6 +116,54 @@ def test_shapes_every_entry(shape, key):
     pg = P.Graph(g)
     pg.enumerate_configs(p, all_integers=every)
     pg.set_option(P.OPT_KEY_TYPE, key)
+    for keep in (1, 0):
+        pg.set_option(P.OPT_KEEP_TABLES, keep)
+        assert pg.find_best_strategy() == o.result()
+        if keep:
+            for i, v in enumerate(o.sequence()):
+                assert pg.fingerprint(v) == o.fingerprint(i), (v, pg.vertex_info(v))
+
+
+# a class digit of few configurations beside large rest digits: (loop dims, neighbours joined twice, p, every
+# integer, whether v0 takes the class fill); K 84 to 731, Kz 6 to 56
+SMALL_DIGITS = [((5, 5, 5, 1), (1, 2), 32, False, False), ((5, 5, 5, 3), (1, 2), 32, False, True),
+                ((4, 5, 5, 3), (1, 2), 32, False, True), ((5, 4, 4, 1), (1, 2), 64, False, False),
+                ((3, 4, 4, 2), (1, 2), 64, False, True), ((5, 3, 3, 1), (1, 2), 24, True, False)]
+
+
+@pytest.mark.parametrize("case", range(len(SMALL_DIGITS)))
+def test_small_digit_plan(case):
+    """The class fill only where its digit saves more than its own cost per
+    cell; otherwise the dense fill."""
+    from paper_2407_04001_amd import pase as P
+    P.load()
+    dims, twice, p, every, classes = SMALL_DIGITS[case]
+    pg = P.Graph(star(dims, twice=twice))
+    pg.enumerate_configs(p, all_integers=every)
+    x = pg.vertex_info(0)
+    assert x["kernel"] == 1 and (x["tile_cols"] == 0) == classes, x
+    assert classes is False or x["column"] == len(dims) - 1
+    for sched in (0, 1, 4, 5):
+        pg.set_option(P.OPT_SCHEDULE, sched)
+        assert pg.plan_check() > 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(SMALL_DIGITS)))
+def test_small_digit_every_entry(case):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_04001_amd import pase as P
+    from oracle.oracle import Oracle
+    dims, twice, p, every, _ = SMALL_DIGITS[case]
+    print(f"small class digit {SMALL_DIGITS[case]}", flush=True)
+    g = star(dims, twice=twice)
+    o = Oracle(g)
+    o.configs(p, all_integers=every)
+    o.solve(threads=os.cpu_count() or 1)
+    pg = P.Graph(g)
+    pg.enumerate_configs(p, all_integers=every)
     for keep in (1, 0):
         pg.set_option(P.OPT_KEEP_TABLES, keep)
         assert pg.find_best_strategy() == o.result()
