@@ -63,8 +63,11 @@ __global__ __launch_bounds__(256) void k_cost_tables(const DevVertex *__restrict
     __shared__ uint64_t buf[kClassTabTile];
     if (blockIdx.x >= nbase) {
         const uint32_t b = blockIdx.x - nbase;
-        uint32_t lo = 0;
-        while (lo + 1 < ct.ntabs && ct.tabs[lo + 1].blk0 <= b) lo++;
+        uint32_t lo = 0, hi = ct.ntabs;   // last table with blk0 <= b (a graph may have as many as edges)
+        while (lo + 1 < hi) {
+            const uint32_t mid = (lo + hi) / 2;
+            if (ct.tabs[mid].blk0 <= b) lo = mid; else hi = mid;
+        }
         class_table_item(ct.tabs[lo], b - ct.tabs[lo].blk0, ex, ct.ws, buf);
         return;
     }
