@@ -870,8 +870,9 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
         for (size_t gi = 0; gi < si.groups.size(); gi++) {
             const int ln = si.group_lane[gi];
             for (int i : si.groups[gi])
-                for (int j : P.v[i].reads)
+                for_reads(P, P.v[i], [&](int j) {
                     if (P.v[j].lane != ln) lane_ev_used[1 + (size_t)P.v[j].slot * kLanes + P.v[j].lane] = 1;
+                });
         }
     }
     // hoisted preps: a side batch starts after everything enqueued on s before
@@ -924,8 +925,9 @@ static pase_status run_search(pase_graph_t g, hipStream_t s, char *ws, char *img
                 int need[kLanes];
                 for (int &x : need) x = -1;
                 for (int i : si.groups[b.group])
-                    for (int j : P.v[i].reads)
+                    for_reads(P, P.v[i], [&](int j) {
                         if (P.v[j].lane != b.lane) need[P.v[j].lane] = std::max(need[P.v[j].lane], P.v[j].slot);
+                    });
                 for (int l = 0; l < kLanes; l++)
                     if (need[l] > waited[b.lane][l]) {
                         if (need[l] >= b.group / nl)   // a table is read at a later slot only

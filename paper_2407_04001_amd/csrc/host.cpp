@@ -39,12 +39,14 @@ static uint32_t bits_for(uint32_t K) {
 // and the ones that split a single dim p ways (costs evaluated exactly); with
 // caller-given costs it is the cheapest layer configuration.  These bounds
 // follow the recurrence instead of summing every cost of the graph, so deep
-// graphs keep exact fp64 keys.  false: a bound exceeds 64 bits.
-bool cost_bounds(pase_graph_t g, std::vector<uint64_t> *qmax, std::vector<uint64_t> *tmax) {
-    const Plan &P = g->plan;
+// graphs keep exact fp64 keys.  They depend on the sequence and the costs, not
+// on the fills, and are evaluated once for these (plan.qmax, plan.tmax).
+// false: a bound exceeds 64 bits.
+static bool eval_bounds(pase_graph_t g) {
+    Plan &P = g->plan;
     const size_t n = P.v.size();
-    qmax->assign(n, 0);
-    tmax->assign(n, 0);
+    P.qmax.assign(n, 0);
+    P.tmax.assign(n, 0);
     for (size_t i = 0; i < n; i++) {
         const VPlan &vp = P.v[i];
         const int v = vp.vi;
@@ -83,10 +85,15 @@ bool cost_bounds(pase_graph_t g, std::vector<uint64_t> *qmax, std::vector<uint64
             if (!add_ok(rest, m, &rest)) return false;
         }
         for (const TermRef &t : vp.terms)
-            if (!add_ok(rest, (*tmax)[t.j], &rest)) return false;
-        if (!add_ok(hi, rest, &(*qmax)[i]) || !add_ok(lo, rest, &(*tmax)[i])) return false;
+            if (!add_ok(rest, P.tmax[t.j], &rest)) return false;
+        if (!add_ok(hi, rest, &P.qmax[i]) || !add_ok(lo, rest, &P.tmax[i])) return false;
     }
     return true;
+}
+
+bool cost_bounds(pase_graph_t g) {
+    if (g->plan.bounds < 0) g->plan.bounds = eval_bounds(g) ? 1 : 0;
+    return g->plan.bounds == 1;
 }
 
 // Key type: fp64 when every key (cost * 2^bits + c) of every position stays
@@ -99,8 +106,8 @@ bool cost_bounds(pase_graph_t g, std::vector<uint64_t> *qmax, std::vector<uint64
 // the keys fit) / 128-bit keys.
 uint32_t choose_key_type(pase_graph_t g, pase_status *st) {
     *st = PASE_OK;
-    std::vector<uint64_t> qmax, tmax;
-    if (!cost_bounds(g, &qmax, &tmax)) { *st = PASE_ERR_OVERFLOW; return 0; }
+    if (!cost_bounds(g)) { *st = PASE_ERR_OVERFLOW; return 0; }
+    const std::vector<uint64_t> &qmax = g->plan.qmax;
     unsigned __int128 top = 0;
     for (size_t i = 0; i < qmax.size(); i++) {
         // largest key: qmax * 2^bits + (2^bits - 1) < (qmax + 1) * 2^bits
@@ -219,7 +226,7 @@ void generate_seq(pase_graph_t g, std::vector<int> &seq, std::vector<std::vector
     std::vector<uint64_t> d(n * W, 0);
     for (size_t v = 0; v < n; v++)
         for (int u : g->nbr[v]) d[v * W + u / 64] |= 1ull << (u % 64);
-    // |u.d| is kept per vertex and recounted only when u.d changes
+    // |u.d| is kept per vertex, counting the members that come and go
     auto count = [&](size_t u) {
         int sz = 0;
         for (size_t w = 0; w < W; w++) sz += __builtin_popcountll(d[u * W + w]);
@@ -256,10 +263,16 @@ void generate_seq(pase_graph_t g, std::vector<int> &seq, std::vector<std::vector
                 if (u != vi) Dpos[i].push_back((int)u);
             }
         for (int v : Dpos[i]) {
-            for (size_t w = 0; w < W; w++) d[(size_t)v * W + w] |= d[vi * W + w];
-            d[(size_t)v * W + vi / 64] &= ~(1ull << (vi % 64));
-            if (g->seq_rule == 0) d[(size_t)v * W + v / 64] &= ~(1ull << (v % 64));
-            size[v] = count((size_t)v);
+            uint64_t *dv = &d[(size_t)v * W];
+            for (size_t w = 0; w < W; w++) {
+                uint64_t more = d[vi * W + w] & ~dv[w];
+                if (g->seq_rule == 0 && w == (size_t)v / 64) more &= ~(1ull << (v % 64));
+                dv[w] |= more;
+                for (; more; more &= more - 1) size[v]++;
+            }
+            const uint64_t out = 1ull << (vi % 64);
+            size[v] -= (dv[vi / 64] & out) != 0;
+            dv[vi / 64] &= ~out;
         }
     }
 }
@@ -351,34 +364,56 @@ TileTime tile_time(uint64_t MO, uint64_t MR, uint32_t Kz, uint32_t K, uint32_t n
     return best;
 }
 
-// Vertices of one graph often share a shape (the layers of a stack): the tile
-// model is evaluated once per distinct argument tuple.
-TileTime tile_time_cached(uint64_t MO, uint64_t MR, uint32_t Kz, uint32_t K, uint32_t na, uint32_t tz, uint32_t tm,
-                          uint32_t force_parts, uint32_t force_splits, double stream_bytes) {
+// The best tile shape of one column choice (tz, tm: forced columns and rows per
+// lane, 0 = free).  Vertices of one graph often share a shape (the layers of a
+// stack): the tile model is evaluated once per distinct argument tuple.
+struct TileChoice {
+    bool ok = false;
+    uint32_t TZ = 0, TM = 1;
+    TileTime t{0, 1, 1};
+};
+
+TileChoice tile_choice(uint64_t MO, uint64_t MR, int z, uint32_t Kz, uint32_t K, uint32_t na, uint32_t force_tz,
+                       uint32_t force_tm, uint32_t force_parts, uint32_t force_splits, double stream_bytes) {
     struct Key {
         uint64_t MO, MR;
-        uint32_t Kz, K, na, tz, tm, parts, splits;
+        uint32_t Kz, K, na, tz, tm, parts, splits, col;
         double sb;
         bool operator==(const Key &o) const {
             return MO == o.MO && MR == o.MR && Kz == o.Kz && K == o.K && na == o.na && tz == o.tz && tm == o.tm &&
-                   parts == o.parts && splits == o.splits && sb == o.sb;
+                   parts == o.parts && splits == o.splits && col == o.col && sb == o.sb;
         }
     };
     struct Hash {
         size_t operator()(const Key &k) const {
             uint64_t h = k.MO * 0x9E3779B97F4A7C15ull ^ (k.MR + 0x632BE59BD9B4E019ull) ^ (uint64_t)k.sb;
-            for (uint32_t x : {k.Kz, k.K, k.na, k.tz, k.tm, k.parts, k.splits}) h = (h ^ x) * 0x100000001B3ull;
+            for (uint32_t x : {k.Kz, k.K, k.na, k.tz, k.tm, k.parts, k.splits, k.col}) h = (h ^ x) * 0x100000001B3ull;
             return (size_t)h;
         }
     };
-    thread_local std::unordered_map<Key, TileTime, Hash> memo;
-    const Key key{MO, MR, Kz, K, na, tz, tm, force_parts, force_splits, stream_bytes};
+    thread_local std::unordered_map<Key, TileChoice, Hash> memo;
+    const Key key{MO, MR, Kz, K, na, force_tz, force_tm, force_parts, force_splits, z >= 0 ? 1u : 0u, stream_bytes};
     auto it = memo.find(key);
     if (it != memo.end()) return it->second;
-    if (memo.size() > 65536) memo.clear();
-    const TileTime t = tile_time(MO, MR, Kz, K, na, tz, tm, force_parts, force_splits, stream_bytes);
-    memo.emplace(key, t);
-    return t;
+    if (memo.size() > 8192) memo.clear();
+    TileChoice c;
+    auto consider = [&](uint32_t tz) {
+        const uint64_t nch = (Kz + tz - 1) / tz;
+        if (MO * K * nch * tz > kMaxTableEntries) return;
+        for (uint32_t tm = 1; tm <= 2; tm++) {
+            if (force_tm && tm != force_tm) continue;
+            // more than 32 accumulators per lane cost waves (VGPRs)
+            if (!force_tm && !force_tz && tz * tm > 32) continue;
+            const TileTime t = tile_time(MO, MR, Kz, K, na, tz, tm, force_parts, force_splits, stream_bytes);
+            if (!c.ok || t.us < c.t.us) c = {true, tz, tm, t};
+        }
+    };
+    if (z < 0) consider(1);
+    else
+        for (uint32_t tz : kTZ)
+            if (!force_tz || tz == force_tz) consider(tz);
+    memo.emplace(key, c);
+    return c;
 }
 
 }  // namespace
@@ -496,7 +531,7 @@ static bool bulk_fill(const VPlan &vp, double bulk_us) {
 static void assign_bulk_lanes(Plan &P, double bulk_us) {
     for (auto &vp : P.v) {
         bool bulk = bulk_fill(vp, bulk_us);
-        for (int j : vp.reads) bulk |= P.v[j].lane == 1;
+        for_reads(P, vp, [&](int j) { bulk |= P.v[j].lane == 1; });
         vp.lane = bulk ? 1 : 0;
     }
 }
@@ -513,7 +548,7 @@ static void assign_bulk_lanes(Plan &P, double bulk_us) {
 static void assign_split_lanes(Plan &P, double bulk_us) {
     for (auto &vp : P.v) {
         bool one = vp.level < kSplitBatchedLevels || bulk_fill(vp, bulk_us);
-        for (int j : vp.reads) one |= P.v[j].lane == 1 && P.v[j].level >= kSplitBatchedLevels;
+        for_reads(P, vp, [&](int j) { one |= P.v[j].lane == 1 && P.v[j].level >= kSplitBatchedLevels; });
         vp.lane = one ? 1 : 0;
     }
 }
@@ -522,7 +557,9 @@ static double ms_since(std::chrono::steady_clock::time_point t0) {
     return std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
 }
 
-static pase_status build_plan(pase_graph_t g) {
+// What the plan takes from the graph alone: the sequence, the dependent sets,
+// lookups, edges and table sizes of every position, and the dependency levels.
+static pase_status build_structure(pase_graph_t g) {
     const auto t0 = std::chrono::steady_clock::now();
     const int n = (int)g->V.size();
     Plan &P = g->plan;
@@ -608,14 +645,48 @@ static pase_status build_plan(pase_graph_t g) {
         if (P.v[i].consumer < 0) return fail(g, PASE_ERR_INTERNAL, "table never read");
         P.v[i].out_shift = P.v[P.v[i].consumer].bits;
     }
-    g->stats.seq_ms = ms_since(t0);
-    const auto t1 = std::chrono::steady_clock::now();
     // dependency level: vertices of one level read no table of each other
     for (int i = 0; i < n; i++) {
         P.v[i].level = 0;
         for (const auto &t : P.v[i].terms) P.v[i].level = std::max(P.v[i].level, P.v[t.j].level + 1);
     }
+    g->stats.seq_ms = ms_since(t0);
+    return PASE_OK;
+}
 
+// The plan's structure alone, for other fills of the same graph.
+static void reset_fills(Plan &P) {
+    Plan q;
+    q.seq.swap(P.seq);
+    q.pos.swap(P.pos);
+    q.cells = P.cells;
+    q.entries = P.entries;
+    q.max_dep = P.max_dep;
+    q.bounds = P.bounds;
+    q.qmax.swap(P.qmax);
+    q.tmax.swap(P.tmax);
+    q.v.resize(P.v.size());
+    for (size_t i = 0; i < P.v.size(); i++) {
+        VPlan &a = q.v[i], &b = P.v[i];
+        a.vi = b.vi;
+        a.K = b.K;
+        a.bits = b.bits;
+        a.D.swap(b.D);
+        a.N = b.N;
+        a.edges.swap(b.edges);
+        a.terms.swap(b.terms);
+        a.consumer = b.consumer;
+        a.out_shift = b.out_shift;
+        a.level = b.level;
+    }
+    P = std::move(q);
+}
+
+// The fill, layout and lane of every position.
+static pase_status plan_fills(pase_graph_t g) {
+    const auto t1 = std::chrono::steady_clock::now();
+    Plan &P = g->plan;
+    const int n = (int)P.v.size();
     // ---- kernel choice and T_i layout
     // threads of the generic and direct fills walk the table in layout order:
     // follow the memory order of the largest lookup that spans several digits
@@ -678,12 +749,7 @@ static pase_status build_plan(pase_graph_t g) {
         }
         const size_t edges = (g->volume ? 0 : vp.edges.size()) - (z >= 0);
         if ((z < 0 && !direct) || edges > (size_t)kMaxClassEdges) return false;
-        const std::vector<int> order = gather_layout(vp);
-        std::vector<int> R;
-        for (int u : order)
-            if (u != z) R.push_back(u);
-        uint64_t rows = 1;
-        for (int u : R) rows *= g->K[u];
+        const uint64_t rows = vp.N / (z >= 0 ? g->K[z] : 1);
         const uint32_t Kz = z >= 0 ? g->K[z] : 1;
         const uint32_t ne = (uint32_t)edges, nt = (uint32_t)lookups;
         auto fits = [&](uint32_t lr, bool keep) {
@@ -713,7 +779,12 @@ static pase_status build_plan(pase_graph_t g) {
         vp.lr = lr;
         vp.z = z;
         vp.O.clear();
-        vp.R = R;
+        vp.layout = gather_layout(vp);   // (z first: its entries are rows apart)
+        if (z >= 0) {
+            vp.layout.erase(std::find(vp.layout.begin(), vp.layout.end(), z));
+            vp.layout.insert(vp.layout.begin(), z);
+        }
+        vp.R.assign(vp.layout.begin() + (z >= 0), vp.layout.end());
         vp.MO = 1;
         vp.MR = rows;
         vp.TZ = 0;
@@ -721,9 +792,6 @@ static pase_status build_plan(pase_graph_t g) {
         vp.nsplit = 1;
         vp.cper = vp.K;
         vp.parts = 0;
-        vp.layout.clear();
-        if (z >= 0) vp.layout.push_back(z);
-        vp.layout.insert(vp.layout.end(), R.begin(), R.end());
         vp.stride.assign(vp.layout.size(), 1);
         for (int k = (int)vp.layout.size() - 2; k >= 0; k--) vp.stride[k] = vp.stride[k + 1] * g->K[vp.layout[k + 1]];
         // the table's stores, or the X evaluations
@@ -772,13 +840,20 @@ static pase_status build_plan(pase_graph_t g) {
     // configuration and row, so K_i and Ky from 24 up.  uint64 keys: the sums of both
     // vertices' terms must not wrap (fp64 sums past 2^53 round, but never below
     // a key that is exact).
-    std::vector<uint64_t> qmax, tmax;
-    uint32_t joint_kt = 2;
-    if (class_ok && n <= (int)kMaxBacktrackThreads) {
-        pase_status kst;
-        joint_kt = choose_key_type(g, &kst);
-        if (kst != PASE_OK || !cost_bounds(g, &qmax, &tmax)) joint_kt = 2;
-    }
+    const bool joint_ok = class_ok && n <= (int)kMaxBacktrackThreads;
+    uint32_t joint_key = 3;          // key type of the search (3: not evaluated; 2: none of these fills)
+    auto joint_kt = [&] {
+        if (joint_key == 3) {
+            pase_status kst;
+            joint_key = choose_key_type(g, &kst);
+            if (kst != PASE_OK) joint_key = 2;
+        }
+        return joint_key;
+    };
+    // largest sum of two vertices' terms as keys
+    auto joint_top = [&](int i, int j) {
+        return ((unsigned __int128)P.qmax[i] + P.qmax[j] + 2) << std::max(P.v[i].bits, P.v[j].bits);
+    };
     auto mapped = [&](int e, int u) {   // loop dims of vertex u that edge e's tensor maps
         const auto &d = g->E[e];
         uint32_t m = 0;
@@ -825,9 +900,10 @@ static pase_status build_plan(pase_graph_t g) {
         }
         return true;
     };
-    auto plan_joint = [&](int i) {
+    // (the plan in `out`, whose allocations the next vertex reuses)
+    auto plan_joint = [&](int i, VPlan &out) {
         VPlan &vp = P.v[i];
-        if (joint_kt == 2 || vp.K > kJointMaxK || vp.K < 24 || vp.D.size() < 2) return false;
+        if (!joint_ok || vp.K > kJointMaxK || vp.K < 24 || vp.D.size() < 2) return false;
         auto edge_to = [&](const VPlan &v, int w) {   // the one edge of v to w: its id, -1 none, -2 several
             int at = -1;
             for (int e : v.edges)
@@ -843,8 +919,7 @@ static pase_status build_plan(pase_graph_t g) {
             const int eo = edge_to(vj, vp.vi);
             bool looked = eo < 0 || !tight(eo);
             for (const auto &t : vj.terms) looked |= in(t, vp.vi);
-            const unsigned __int128 top = ((unsigned __int128)qmax[i] + qmax[tj.j] + 2) << std::max(vp.bits, vj.bits);
-            if (looked || (joint_kt == 1 && top >> 64)) continue;
+            if (looked || joint_kt() == 2 || (joint_kt() == 1 && joint_top(i, tj.j) >> 64)) continue;
             for (int y : tj.dig) {
                 const int ey = edge_to(vj, y), ei = edge_to(vp, y);
                 bool bad = ey < 0 || !tight(ey) || ei == -2 || (ei >= 0 && !tight(ei)) || g->K[y] > kJointMaxK;
@@ -882,28 +957,30 @@ static pase_status build_plan(pase_graph_t g) {
             if (std::find(order.begin(), order.end(), u) == order.end()) order.push_back(u);
         const auto has = [](const std::vector<int> &v, int u) { return std::find(v.begin(), v.end(), u) != v.end(); };
         std::vector<int> R;
-        vp.jupper = 1;
+        uint64_t jupper = 1;
         for (int u : order)
-            if (u != by && has(vj.D, u)) { R.push_back(u); vp.jupper *= g->K[u]; }
+            if (u != by && has(vj.D, u)) { R.push_back(u); jupper *= g->K[u]; }
         for (int u : order)
             if (u != by && !has(vj.D, u)) R.push_back(u);
-        vp.R = R;
-        vp.joint = bj;
-        std::copy(bcls, bcls + 4, vp.jcls);
-        vp.z = by;
-        vp.O.clear();
-        vp.MO = 1;
-        vp.MR = vp.N / g->K[by];
-        vp.TZ = 0;
-        vp.TM = 1;
-        vp.nsplit = 1;
-        vp.cper = vp.K;
-        vp.parts = 0;
-        vp.layout = vp.R;
-        vp.layout.push_back(by);
-        vp.stride.assign(vp.layout.size(), 1);
-        for (int k = (int)vp.layout.size() - 2; k >= 0; k--) vp.stride[k] = vp.stride[k + 1] * g->K[vp.layout[k + 1]];
-        vp.est_us = 6.0 + (double)vp.MR * (1.2e-3 + 1.5e-5 * vp.K);
+        out = vp;
+        out.jupper = jupper;
+        out.R = R;
+        out.joint = bj;
+        std::copy(bcls, bcls + 4, out.jcls);
+        out.z = by;
+        out.O.clear();
+        out.MO = 1;
+        out.MR = vp.N / g->K[by];
+        out.TZ = 0;
+        out.TM = 1;
+        out.nsplit = 1;
+        out.cper = vp.K;
+        out.parts = 0;
+        out.layout = out.R;
+        out.layout.push_back(by);
+        out.stride.assign(out.layout.size(), 1);
+        for (int k = (int)out.layout.size() - 2; k >= 0; k--) out.stride[k] = out.stride[k + 1] * g->K[out.layout[k + 1]];
+        out.est_us = 6.0 + (double)out.MR * (1.2e-3 + 1.5e-5 * out.K);
         return true;
     };
     // A column-less vertex without edges (its lookups alone) takes the class
@@ -916,6 +993,7 @@ static pase_status build_plan(pase_graph_t g) {
         for (const auto &t : vp.terms) looked += P.v[t.j].N * 8;
         return vp.edges.empty() && looked <= (32ull << 20);
     };
+    VPlan jointp;
     auto plan_one = [&](int i, uint32_t ftz, uint32_t ftm, bool no_split) {
         VPlan &vp = P.v[i];
         vp.classes = vp.exch = false;
@@ -947,13 +1025,7 @@ static pase_status build_plan(pase_graph_t g) {
         // rows cost 1.3 ns each at K = 35 (86 us against 27 + 6 us of prep on the
         // three-layer LSTM at p = 16), 8 ns at K = 462 (69 us against 143 + 26 us);
         // a dense fill takes at least 8 us, and its prep as much
-        const VPlan plain = vp;
-        VPlan jointp;
-        const bool joint = !cls && !ftz && kernel_mode == 0 && plan_joint(i);
-        if (joint) {
-            jointp = vp;
-            vp = plain;
-        }
+        const bool joint = !cls && !ftz && kernel_mode == 0 && plan_joint(i, jointp);
         RowsChoice best;
         // candidates: every digit of D(i) as the column digit z, and -- only
         // when none of those fits -- no column at all (z = -1: every digit is
@@ -1003,35 +1075,21 @@ static pase_status build_plan(pase_graph_t g) {
                 if (na > (uint32_t)kMaxATerms || !small) continue;
                 rc.na = na;
                 const uint32_t Kz = z >= 0 ? g->K[z] : 1;
-                static const uint32_t kNoColumn[] = {1};
-                for (uint32_t tz : z >= 0 ? std::vector<uint32_t>(std::begin(kTZ), std::end(kTZ))
-                                          : std::vector<uint32_t>(std::begin(kNoColumn), std::end(kNoColumn))) {
-                    if (z >= 0 && tile_cols && tz != tile_cols) continue;
-                    uint64_t nch = (Kz + tz - 1) / tz;
-                    if (rc.MO * vp.K * nch * tz > kMaxTableEntries) continue;
-                    for (uint32_t tm = 1; tm <= 2; tm++) {
-                        if (tile_rows && tm != tile_rows) continue;
-                        // more than 32 accumulators per lane cost waves (VGPRs)
-                        if (!tile_rows && !tile_cols && tz * tm > 32) continue;
-                        const TileTime tt = tile_time_cached(rc.MO, rc.MR, Kz, vp.K, na, tz, tm, g->tile_parts,
-                                                             no_split ? 1u : g->c_splits, stream_bytes);
-                        if (!rc.ok || tt.us < rc.cost) {
-                            rc.ok = true;
-                            rc.cost = tt.us;
-                            rc.TZ = tz;
-                            rc.TM = tm;
-                            rc.parts = tt.parts;
-                            rc.nsplit = tt.nsplit;
-                        }
-                    }
-                }
+                const TileChoice tc = tile_choice(rc.MO, rc.MR, z, Kz, vp.K, na, tile_cols, tile_rows, g->tile_parts,
+                                                  no_split ? 1u : g->c_splits, stream_bytes);
+                rc.ok = tc.ok;
+                rc.cost = tc.t.us;
+                rc.TZ = tc.TZ;
+                rc.TM = tc.TM;
+                rc.parts = tc.t.parts;
+                rc.nsplit = tc.t.nsplit;
                 if (rc.ok && (!best.ok || rc.cost < best.cost)) best = rc;
             }
         }
         if (cls && !(best.ok && best.z >= 0)) return;   // (no column: nothing dense to compare with)
         vp.classes = false;
         if (joint && (!best.ok || jointp.est_us <= std::max(best.cost, 8.0) + 8.0)) {
-            vp = jointp;
+            std::swap(vp, jointp);
             vp.kernel = kRows;
         } else if (best.ok && best.z < 0 && !ftz && kernel_mode == 0 && stream_small(vp) && plan_class(i, true)) {
             vp.kernel = kRows;
@@ -1077,7 +1135,7 @@ static pase_status build_plan(pase_graph_t g) {
     // up, like the joint fill.  Not with kept tables (j's is then wanted).
     auto plan_exchange = [&](int i) {
         VPlan &vp = P.v[i];
-        if (!g->fuse_min || g->keep_tables || joint_kt == 2 || vp.classes || vp.joint >= 0 || vp.kernel == kDirect) return;
+        if (!g->fuse_min || g->keep_tables || !joint_ok || vp.classes || vp.joint >= 0 || vp.kernel == kDirect) return;
         if (vp.terms.size() != 1 || vp.D.size() != 2 || vp.terms[0].dig.size() != 2 || vp.edges.size() != 2 ||
             vp.K < 24 || vp.K > kExchMaxK)
             return;
@@ -1099,8 +1157,7 @@ static pase_status build_plan(pase_graph_t g) {
         }
         // uint64 keys: sums of a few cases' keys and of the mark of an empty
         // class (2^62) must not wrap
-        const unsigned __int128 top = ((unsigned __int128)qmax[i] + qmax[j] + 2) << std::max(vp.bits, vj.bits);
-        if (joint_kt == 1 && top >> 60) return;
+        if (joint_kt() == 2 || (joint_kt() == 1 && joint_top(i, j) >> 60)) return;
         vp.joint = j;
         vp.exch = true;
         vp.nsplit = 1;
@@ -1110,22 +1167,11 @@ static pase_status build_plan(pase_graph_t g) {
         plan_one(i, 0, 0, false);
         plan_exchange(i);
     }
-    // the tables each vertex's launches read: a joint fill's half fill runs in
-    // the other vertex's slot (its tables are that vertex's reads), or, without
-    // levels or hoisting, just before the fill
     for (int i = 0; i < n; i++) {
         VPlan &vp = P.v[i];
-        vp.jearly = vp.joint >= 0 && g->schedule != kSchedSeq && g->hoist_elems != 0;
-        for (const auto &t : vp.terms) {
-            if (t.j == vp.joint) {
-                P.v[t.j].absorbed = i;
-                if (!vp.jearly) {
-                    for (const auto &u : P.v[t.j].terms) vp.reads.push_back(u.j);
-                    continue;
-                }
-            }
-            vp.reads.push_back(t.j);
-        }
+        if (vp.joint < 0) continue;
+        vp.jearly = g->schedule != kSchedSeq && g->hoist_elems != 0;
+        P.v[vp.joint].absorbed = i;
     }
     // One launch per level and kernel variant: a small column-form row vertex
     // of a level is re-planned with the tile shape of the level's largest one
@@ -1187,11 +1233,12 @@ static pase_status build_plan(pase_graph_t g) {
     if (g->fuse_min && kernel_mode == 0) fuse_minima(g, P);
     // class tables, one per distinct edge shape (the end u, the other end)
     P.overridden = g->overridden;
+    std::vector<int> shape_of(256, -1), shape_next;   // class tables by hash of their map
     auto class_table = [&](int u, int w) {   // of the one edge joining vertices u and w, by u's classes
-        for (int e : incident[u]) {
+        for (int e : P.v[std::min(P.pos[u], P.pos[w])].edges) {
             const auto &d = g->E[e];
             const bool is_src = (int)d.src == u;
-            if ((is_src ? (int)d.dst : (int)d.src) != w) continue;
+            if ((is_src ? (int)d.dst : (int)d.src) != w || (!is_src && (int)d.dst != u)) continue;
             DevClassTab t;
             std::memset(&t, 0, sizeof t);
             t.K = g->K[u];
@@ -1200,20 +1247,24 @@ static pase_status build_plan(pase_graph_t g) {
             t.ndz = g->V[w].ndims;
             t.rank = d.rank;
             t.factors = g->factors ? 1 : 0;
+            uint64_t hash = (t.ndu * 64 + t.ndz) * 64 + t.rank;
             for (uint32_t k = 0; k < kMaxDims; k++) {
                 t.udim[k] = (int8_t)(k < d.rank ? (is_src ? d.src_dim[k] : d.dst_dim[k]) : -1);
                 t.zdim[k] = (int8_t)(k < d.rank ? (is_src ? d.dst_dim[k] : d.src_dim[k]) : -1);
+                hash = hash * 0x9E3779B97F4A7C15ull + (uint64_t)((t.udim[k] + 1) * 16 + t.zdim[k] + 1);
             }
-            for (size_t k = 0; k < P.ctabs.size(); k++) {
+            int &first = shape_of[hash >> 56];
+            for (int k = first; k >= 0; k = shape_next[k]) {
                 const DevClassTab &o = P.ctabs[k];
                 if (o.ndu == t.ndu && o.ndz == t.ndz && o.rank == t.rank &&
                     !std::memcmp(o.udim, t.udim, sizeof t.udim) && !std::memcmp(o.zdim, t.zdim, sizeof t.zdim))
-                    return (int)k;
+                    return k;
             }
             t.blk0 = P.ctab_blocks;
             P.ctab_blocks += (t.K + t.Kz + 256 / kClassTabLanes - 1) / (256 / kClassTabLanes);
             P.ctabs.push_back(t);
-            return (int)P.ctabs.size() - 1;
+            shape_next.push_back(first);
+            return first = (int)P.ctabs.size() - 1;
         }
         return -1;
     };
@@ -1411,11 +1462,17 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
     std::iota(order.begin(), order.end(), 0);
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return iv[a].size > iv[b].size; });
     // placed tables in ascending offset order: the first gap that fits among
-    // those whose lifetimes overlap is found in one pass
+    // those whose lifetimes overlap is found in one pass.  (All of them overlap
+    // when every table stays: one after the other.)
     std::vector<int> placed;
     placed.reserve(n);
     uint64_t tbytes = 0;
     for (int k : order) {
+        if (resident || g->keep_tables) {
+            P.v[iv[k].i].T_off = tbytes;
+            tbytes += iv[k].size;
+            continue;
+        }
         uint64_t cand = 0;
         for (int q : placed) {
             if (!(iv[q].s <= iv[k].e && iv[k].s <= iv[q].e)) continue;
@@ -1507,14 +1564,20 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
 // passes 64 bits.
 static pase_status plan_search(pase_graph_t g, bool replan) {
     pase_status st;
+    if (replan && (st = build_structure(g)) != PASE_OK) return st;
+    if (!replan) g->plan.bounds = -1;   // (other costs)
     // (a plan with class fills reads the model's own costs: caller-given ones
     // need the dense fills, and the other way round)
-    if ((replan || g->plan.overridden != g->overridden) && (st = build_plan(g)) != PASE_OK) return st;
+    if (replan || g->plan.overridden != g->overridden) {
+        if (!replan) reset_fills(g->plan);
+        if ((st = plan_fills(g)) != PASE_OK) return st;
+    }
     const uint32_t kt = choose_key_type(g, &st);
     if (st != PASE_OK) return fail(g, st, "a cost bound of the recurrence exceeds 64 bits");
     if ((kt == 2) != g->plan_wide) {
         g->plan_wide = kt == 2;
-        if ((st = build_plan(g)) != PASE_OK) return st;
+        reset_fills(g->plan);
+        if ((st = plan_fills(g)) != PASE_OK) return st;
     }
     g->plan_key_type = kt;
     return layout_memory(g);
@@ -1965,10 +2028,9 @@ extern "C" pase_status pase_vertex_info_get(pase_graph_t g, uint32_t v, pase_ver
     x.fill_ms = vp.fill_ms;
     x.level = (uint32_t)vp.level;
     x.lane = (uint32_t)vp.lane;
-    std::vector<uint64_t> qmax, tmax;
-    if (cost_bounds(g, &qmax, &tmax)) {
-        x.key_bound = qmax[x.position];
-        x.table_bound = tmax[x.position];
+    if (cost_bounds(g)) {
+        x.key_bound = g->plan.qmax[x.position];
+        x.table_bound = g->plan.tmax[x.position];
     } else {
         x.key_bound = x.table_bound = ~0ull;
     }

@@ -473,7 +473,6 @@ struct VPlan {
     uint64_t jupper = 1;            // product of the upper digits (the first of R)
     bool jearly = false;            // the half fill runs in the other vertex's slot, else just before the fill
     int absorbed = -1;              // the vertex whose joint fill does without this one's table
-    std::vector<int> reads;         // positions whose tables its launches read
     uint32_t desc[kDescKinds] = {}; // index of its descriptor of each kind
     std::vector<int> O, R;          // outer / row digits (vertex ids), slowest first
     uint32_t TZ = 0, TM = 1, ldz = 0, nchunks = 0, nsplit = 1, cper = 0, parts = 1;
@@ -509,6 +508,9 @@ struct Plan {
     std::vector<VPlan> v;           // by position
     uint64_t cells = 0, entries = 0, rows_cells = 0, stream_cells = 0;
     uint32_t max_dep = 0, rows_vertices = 0;
+    // upper bounds per position (cost_bounds), of the current costs; bounds: -1 not evaluated, 0 past 64 bits, 1 valid
+    int bounds = -1;
+    std::vector<uint64_t> qmax, tmax;
     // workspace layout, byte offsets from the workspace base
     uint64_t off_ex = 0, off_vert = 0, off_edge = 0, off_L = 0, off_lsum = 0, off_sig = 0,
              off_ovedge = 0, off_contrib = 0,
@@ -532,6 +534,17 @@ struct Plan {
     uint64_t off_ctdesc = 0, off_jtdesc = 0, off_ctab = 0, off_Lk = 0, off_fk = 0;
     bool overridden = false;        // planned for caller-given costs
 };
+
+// Positions whose tables the launches of a vertex read: a joint fill's half
+// fill runs in the other vertex's slot (its tables are that vertex's reads),
+// or, without levels or hoisting, just before the fill.
+template <typename F> void for_reads(const Plan &P, const VPlan &vp, F f) {
+    for (const auto &t : vp.terms) {
+        if (t.j == vp.joint && !vp.jearly) {
+            for (const auto &u : P.v[t.j].terms) f(u.j);
+        } else f(t.j);
+    }
+}
 
 struct DeviceState;   // defined by the device runtime
 

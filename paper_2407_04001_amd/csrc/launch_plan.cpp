@@ -1110,12 +1110,13 @@ pase_status plan_check(pase_graph_t g, uint64_t *image_bytes) {
             if (b.lane != lane || b.group != vp.prep_after * nl + lane)
                 return fail(g, PASE_ERR_INTERNAL, "a hoisted prep is not on its lane");
             bool waited = !si.lanes || vp.prep_lane == vp.lane;
-            for (int j : vp.reads) {
+            bool early = false;
+            for_reads(g->plan, vp, [&](int j) {
                 const VPlan &pj = g->plan.v[j];
-                if (pj.slot <= vp.prep_after && pj.lane == vp.prep_lane && fill_batch[j] > prep_batch[i])
-                    return fail(g, PASE_ERR_INTERNAL, "a hoisted prep runs before the tables it reads");
+                early |= pj.slot <= vp.prep_after && pj.lane == vp.prep_lane && fill_batch[j] > prep_batch[i];
                 waited |= pj.lane == vp.prep_lane && pj.slot >= vp.prep_after;
-            }
+            });
+            if (early) return fail(g, PASE_ERR_INTERNAL, "a hoisted prep runs before the tables it reads");
             if (!waited) return fail(g, PASE_ERR_INTERNAL, "a hoisted prep on another lane is not waited for");
         }
     }
@@ -1126,9 +1127,11 @@ pase_status plan_check(pase_graph_t g, uint64_t *image_bytes) {
         if (fill_batch[i] < 0) continue;
         if (vp.joint >= 0 && (half_batch[i] < 0 || half_batch[i] >= fill_batch[i]))
             return fail(g, PASE_ERR_INTERNAL, "a half fill does not precede its joint fill");
-        for (int j : vp.reads)
-            if (j != vp.joint && (fill_batch[j] < 0 || fill_batch[j] >= fill_batch[i] || g->plan.v[j].slot >= vp.slot))
-                return fail(g, PASE_ERR_INTERNAL, "a table is read before it is filled");
+        bool early = false;
+        for_reads(g->plan, vp, [&](int j) {
+            early |= j != vp.joint && (fill_batch[j] < 0 || fill_batch[j] >= fill_batch[i] || g->plan.v[j].slot >= vp.slot);
+        });
+        if (early) return fail(g, PASE_ERR_INTERNAL, "a table is read before it is filled");
         if (vp.joint >= 0)
             for (const auto &t : g->plan.v[vp.joint].terms)
                 if (fill_batch[t.j] < 0 || fill_batch[t.j] >= half_batch[i])

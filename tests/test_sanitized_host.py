@@ -89,16 +89,67 @@ int main() {
 """
 
 
+# Caller-given costs on a graph planned for the model's own, and back: the
+# fills are planned again, the sequence and the dependent sets are not.
+OVERRIDE = r"""
+#include <cstdio>
+#include <cstring>
+#include "internal.h"
+using namespace pase;
+int main() {
+    pase_vertex_desc v[6];
+    pase_edge_desc e[6];
+    std::memset(v, 0, sizeof v);
+    std::memset(e, 0, sizeof e);
+    for (auto &x : v) { x.ndims = 2; x.size[0] = x.size[1] = 64; x.flops_per_point = 2; }
+    for (uint32_t k = 0; k < 6; k++) {
+        e[k].src = k < 5 ? k : 0; e[k].dst = k < 5 ? k + 1 : 3; e[k].rank = 1; e[k].elems = 64;
+    }
+    pase_cost_params par{8, 0};
+    pase_graph_t g;
+    if (pase_graph_create(v, 6, e, 6, &par, &g) != PASE_OK) return 1;
+    if (pase_enumerate_configs(g, 16) != PASE_OK) return 2;
+    const auto seq = g->plan.seq;
+    const auto D = g->plan.v[1].D;
+    const uint32_t fills = g->plan.class_fills;
+    std::vector<uint64_t> layer, edge;
+    for (uint32_t k : g->K) layer.resize(layer.size() + k, 3);
+    for (auto &x : g->E) edge.resize(edge.size() + (size_t)g->K[x.src] * g->K[x.dst], 5);
+    g->stats.seq_ms = -7;   // (set whenever the sequence is formed)
+    uint64_t bytes;
+    for (int turn = 0; turn < 2; turn++) {
+        if (pase_override_costs(g, layer.data(), edge.data()) != PASE_OK) return 3;
+        if (g->stats.seq_ms != -7) return 4;
+        if (g->plan.seq != seq || g->plan.v[1].D != D || g->plan.class_fills) return 5;
+        if (pase_plan_check(g, &bytes) != PASE_OK) return 6;
+        // the bounds are those of the new costs: one layer cost and up to two edges per vertex, and its lookups
+        if (g->plan.qmax[0] != (turn ? 1000u : 3u) + 5 * g->plan.v[0].edges.size()) return 7;
+        for (auto &x : layer) x = 1000;
+    }
+    if (pase_enumerate_configs(g, 16) != PASE_OK || g->plan.class_fills != fills || !fills) return 8;
+    pase_graph_destroy(g);
+    std::puts("override ok");
+}
+"""
+
+
+def host_program(source, lib, tmp_path, expect):
+    src = tmp_path / "program.cpp"
+    src.write_text(source)
+    exe = str(tmp_path / "program")
+    subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-g", "-fsanitize=address,undefined",
+                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2407_04001_amd", "csrc"),
+                    str(src), lib, "-Wl,-rpath," + os.path.dirname(lib), "-o", exe], check=True)
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120,
+                       env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=1"))
+    assert r.returncode == 0 and expect in r.stdout, (r.returncode, (r.stdout + r.stderr)[-3000:])
+
+
 def test_descriptors_stay_in_their_region(san_lib, tmp_path):
     """A launch descriptor outside the region that the memory layout made for
     its kind is refused before it is written, not put over the next region."""
-    src = tmp_path / "descriptors.cpp"
-    src.write_text(DESCRIPTORS)
-    exe = str(tmp_path / "descriptors")
-    cxx = os.environ.get("CXX", "g++")
-    subprocess.run([cxx, "-std=c++17", "-g", "-fsanitize=address,undefined", "-I", os.path.join(ROOT, "include"),
-                    "-I", os.path.join(ROOT, "paper_2407_04001_amd", "csrc"), str(src), san_lib,
-                    "-Wl,-rpath," + os.path.dirname(san_lib), "-o", exe], check=True)
-    r = subprocess.run([exe], capture_output=True, text=True, timeout=120,
-                       env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0:abort_on_error=1"))
-    assert r.returncode == 0 and "descriptors ok" in r.stdout, (r.returncode, (r.stdout + r.stderr)[-3000:])
+    host_program(DESCRIPTORS, san_lib, tmp_path, "descriptors ok")
+
+
+def test_caller_given_costs_keep_the_structure(san_lib, tmp_path):
+    host_program(OVERRIDE, san_lib, tmp_path, "override ok")
