@@ -344,7 +344,8 @@ pase_status pase_find_best_strategy(pase_graph_t g, void *stream, uint64_t *min_
  * region is staged through a static host buffer of the same size.  Same
  * arguments, results and errors as pase_find_best_strategy, plus TOO_LARGE
  * when pase_workspace_size() exceeds PASE_NOALLOC_WORKSPACE_BYTES (checked on
- * the host before any device work).  Profiling (PASE_OPT_PROFILE) is ignored
+ * the host before any device work; a plan that exceeds it only because of the
+ * class, joint and exchange fills is made again without them).  Profiling (PASE_OPT_PROFILE) is ignored
  * and a two-stream plan (PASE_OPT_SCHEDULE 4 or 5) runs level by level on `stream`.
  * The array keeps the last call's contents and every call on one GPU shares
  * it: calls in one process are serialized by a lock, calls from different

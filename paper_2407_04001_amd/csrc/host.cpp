@@ -729,7 +729,7 @@ static pase_status plan_fills(pase_graph_t g) {
     // ask for the dense fills and their preps, which they then get.  With the
     // volume model a direct vertex takes the plain minimum as well, each edge's
     // matrix read as a lookup.
-    const bool min_ok = kernel_mode == 0 && !g->overridden && !g->tile_cols && !g->tile_rows &&
+    const bool min_ok = kernel_mode == 0 && !g->dense_only && !g->overridden && !g->tile_cols && !g->tile_rows &&
                         !g->tile_parts && !g->c_splits && (!g->hoist_elems || g->hoist_elems >= kHoistElems);
     const bool class_ok = min_ok && !g->volume;
     auto plan_class = [&](int i, bool direct) {
@@ -1562,6 +1562,8 @@ static pase_status layout_memory_mode(pase_graph_t g, LayoutMode mode) {
 // layout.  A change to or from 128-bit keys re-plans every vertex (such plans
 // run on the generic kernel).  OVERFLOW when a cost bound of the recurrence
 // passes 64 bits.
+static pase_status lay_out(pase_graph_t g);
+
 static pase_status plan_search(pase_graph_t g, bool replan) {
     pase_status st;
     if (replan && (st = build_structure(g)) != PASE_OK) return st;
@@ -1570,6 +1572,7 @@ static pase_status plan_search(pase_graph_t g, bool replan) {
     // need the dense fills, and the other way round)
     if (replan || g->plan.overridden != g->overridden) {
         if (!replan) reset_fills(g->plan);
+        g->dense_only = false;
         if ((st = plan_fills(g)) != PASE_OK) return st;
     }
     const uint32_t kt = choose_key_type(g, &st);
@@ -1580,7 +1583,43 @@ static pase_status plan_search(pase_graph_t g, bool replan) {
         if ((st = plan_fills(g)) != PASE_OK) return st;
     }
     g->plan_key_type = kt;
-    return layout_memory(g);
+    return lay_out(g);
+}
+
+// The plan again with the dense fills alone (dense), or with all of them.
+static pase_status refill(pase_graph_t g, bool dense) {
+    if (dense) g->structured_total = g->plan.total;
+    g->dense_only = dense;
+    reset_fills(g->plan);
+    const pase_status st = plan_fills(g);
+    return st == PASE_OK ? layout_memory(g) : st;
+}
+
+// The memory layout; past the memory budget, that of the dense fills: the
+// class, joint and exchange fills keep key-space costs and class tables beside
+// the layer costs and signatures, and so need up to half as much again on a
+// chain of small vertices (12 kB more per vertex of 462 configurations).
+static pase_status lay_out(pase_graph_t g) {
+    const pase_status st = layout_memory(g);
+    if (st != PASE_ERR_TOO_LARGE || !(g->plan.class_fills + g->plan.joint_fills)) return st;
+    return refill(g, true);
+}
+
+// Fit the plan to `limit` bytes of workspace where the dense fills do and the
+// others do not (a lent workspace, the static one); back to all fills when
+// there is room again.
+static pase_status fit_plan(pase_graph_t g, uint64_t limit) {
+    pase_status st = PASE_OK;
+    if (g->dense_only && g->structured_total <= std::min(limit, g->mem_budget)) {
+        g->searched = false;
+        st = refill(g, false);
+    } else if (g->plan.total > limit && g->plan.class_fills + g->plan.joint_fills) {
+        g->searched = false;
+        st = refill(g, true);
+        if (st != PASE_OK || g->plan.total > limit) st = refill(g, false);
+    }
+    if (st != PASE_OK) g->planned = false;
+    return st;
 }
 
 extern "C" pase_status pase_enumerate_configs(pase_graph_t g, uint32_t p) {
@@ -1922,6 +1961,8 @@ extern "C" pase_status pase_find_best_strategy(pase_graph_t g, void *stream, uin
                                                uint32_t *config_idx) {
     if (!g || !min_cost || !config_idx) return PASE_ERR_INVALID_ARGUMENT;
     if (!g->planned) return fail(g, PASE_ERR_BAD_STATE, "configurations not enumerated");
+    const pase_status st = fit_plan(g, g->lent_ws ? g->lent_bytes : g->mem_budget);
+    if (st != PASE_OK) return st;
     if (g->lent_ws && g->lent_bytes < g->plan.total)
         return fail(g, PASE_ERR_OUT_OF_MEMORY, "lent workspace smaller than pase_workspace_size");
     return device_search(g, stream, min_cost, config_idx);
@@ -1937,6 +1978,8 @@ extern "C" pase_status pase_find_best_strategy_noalloc(pase_graph_t g, void *str
                                                        uint32_t *config_idx) {
     if (!g || !min_cost || !config_idx) return PASE_ERR_INVALID_ARGUMENT;
     if (!g->planned) return fail(g, PASE_ERR_BAD_STATE, "configurations not enumerated");
+    const pase_status st = fit_plan(g, PASE_NOALLOC_WORKSPACE_BYTES);
+    if (st != PASE_OK) return st;
     return device_search_noalloc(g, stream, min_cost, config_idx);
 }
 

@@ -559,6 +559,8 @@ struct pase_graph_s {
     std::string err;
     // options
     bool keep_tables = false;
+    bool dense_only = false;        // no class, joint or exchange fills: they do not fit the memory at hand
+    uint64_t structured_total = 0;  // dense_only: the workspace with them
     int profile = 0;                // pase_option PASE_OPT_PROFILE: 0 off, 1 every fill launch, 2 the
                                     // column-form row-kernel launches only
     uint64_t mem_budget = 64ull << 30;

@@ -475,3 +475,33 @@ def test_exchange_strategies(case, key):
             assert pg.find_best_strategy() == o.result(), (elems, sched, hoist)
         if pg.workspace_size() <= P.NOALLOC_WORKSPACE_BYTES:
             assert P.pase_find_best_strategy_noalloc(pg.h, pg.nv) == o.result()
+
+
+@pytest.mark.gpu
+def test_memory_limits():
+    """A chain of small vertices in a lent workspace, a memory budget and the
+    static workspace that only the dense fills fit: the same strategy."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_04001_amd import pase as P
+    from workloads import chain_graph
+    pg = P.Graph(chain_graph(1, 600, p=64, max_dims=5))
+    pg.enumerate_configs(64)
+    want, need = pg.find_best_strategy(), pg.workspace_size()
+    pg.set_option(P.OPT_C_SPLITS, 1)   # (a tile knob: the dense fills)
+    dense = pg.workspace_size()
+    assert dense < need and pg.find_best_strategy() == want
+    pg.set_option(P.OPT_C_SPLITS, 0)
+    ws = torch.empty(dense + 256, dtype=torch.uint8, device="cuda")
+    at = -ws.data_ptr() % 256
+    P.pase_set_workspace(pg.h, ws.data_ptr() + at, dense)
+    assert P.pase_find_best_strategy(pg.h, pg.nv) == want and pg.workspace_size() == dense
+    P.pase_set_workspace(pg.h, 0, 0)
+    assert P.pase_find_best_strategy(pg.h, pg.nv) == want and pg.workspace_size() == need
+    pg.set_option(P.OPT_MEMORY_BUDGET, dense)
+    assert P.pase_find_best_strategy(pg.h, pg.nv) == want and pg.workspace_size() <= dense
+    big = P.Graph(chain_graph(1, 6100, p=64, max_dims=5))
+    big.enumerate_configs(64)
+    assert big.workspace_size() > P.NOALLOC_WORKSPACE_BYTES
+    assert P.pase_find_best_strategy_noalloc(big.h, big.nv) == P.pase_find_best_strategy(big.h, big.nv)

@@ -133,6 +133,71 @@ int main() {
 """
 
 
+# Chains of small vertices of 462 configurations, whose class fills need more
+# memory than the dense ones: at a memory budget, a lent workspace and the
+# static workspace that only the dense fills fit, the search is not refused.
+LIMITS = r"""
+#include <cstdio>
+#include <cstring>
+#include "internal.h"
+using namespace pase;
+static pase_graph_t chain(uint32_t n) {
+    std::vector<pase_vertex_desc> v(n);
+    std::vector<pase_edge_desc> e(n - 1);
+    std::memset(v.data(), 0, n * sizeof v[0]);
+    std::memset(e.data(), 0, (n - 1) * sizeof e[0]);
+    for (auto &x : v) { x.ndims = 5; for (int k = 0; k < 5; k++) x.size[k] = 64; x.flops_per_point = 2; }
+    for (uint32_t k = 0; k + 1 < n; k++) { e[k].src = k; e[k].dst = k + 1; e[k].rank = 1; e[k].elems = 64; }
+    pase_cost_params par{8, 0};
+    pase_graph_t g = nullptr;
+    if (pase_graph_create(v.data(), n, e.data(), n - 1, &par, &g) != PASE_OK) return nullptr;
+    return pase_enumerate_configs(g, 64) == PASE_OK ? g : nullptr;
+}
+static void sizes(uint32_t n, uint64_t &all, uint64_t &dense) {
+    pase_graph_t g = chain(n);
+    pase_workspace_size(g, &all);
+    pase_set_option(g, PASE_OPT_C_SPLITS, 1);   // (a tile knob: the dense fills)
+    pase_workspace_size(g, &dense);
+    pase_graph_destroy(g);
+}
+int main() {
+    uint64_t all = 0, dense = 0, mc = 0, now = 0, bytes = 0;
+    std::vector<uint32_t> cfg(20000);
+    sizes(40, all, dense);
+    if (all <= dense + 131072) return 1;
+    // a memory budget that the structured fills pass
+    pase_graph_t g = chain(40);
+    if (pase_set_option(g, PASE_OPT_MEMORY_BUDGET, dense + 65536) != PASE_OK) return 2;
+    if (pase_workspace_size(g, &now) != PASE_OK || now > dense + 65536 || !g->dense_only || g->plan.class_fills) return 3;
+    if (pase_plan_check(g, &bytes) != PASE_OK) return 4;
+    if (pase_set_option(g, PASE_OPT_MEMORY_BUDGET, 64ull << 30) != PASE_OK || g->dense_only || !g->plan.class_fills) return 5;
+    // a lent workspace (the host-only build stops where the device work would begin)
+    void *lent = (void *)(uintptr_t)4096;
+    for (int turn = 0; turn < 2; turn++) {
+        pase_set_workspace(g, lent, dense + 65536);
+        if (pase_find_best_strategy(g, nullptr, &mc, cfg.data()) != PASE_ERR_HIP || !g->dense_only) return 6;
+        pase_set_workspace(g, lent, all);
+        if (pase_find_best_strategy(g, nullptr, &mc, cfg.data()) != PASE_ERR_HIP || g->dense_only) return 7;
+    }
+    pase_set_workspace(g, lent, 100000);   // neither fits: refused, and planned as before
+    if (pase_find_best_strategy(g, nullptr, &mc, cfg.data()) != PASE_ERR_OUT_OF_MEMORY) return 8;
+    if (g->dense_only || pase_workspace_size(g, &now) != PASE_OK || now != all) return 9;
+    pase_graph_destroy(g);
+    // the static workspace
+    uint64_t all2, dense2;
+    sizes(80, all2, dense2);
+    const uint32_t n = (uint32_t)(40 + (PASE_NOALLOC_WORKSPACE_BYTES - (1u << 20) - dense) / ((dense2 - dense) / 40));
+    g = chain(n);
+    if (pase_workspace_size(g, &now) != PASE_OK || now <= PASE_NOALLOC_WORKSPACE_BYTES) return 10;
+    if (pase_find_best_strategy_noalloc(g, nullptr, &mc, cfg.data()) != PASE_ERR_HIP) return 11;
+    if (!g->dense_only || g->plan.total > PASE_NOALLOC_WORKSPACE_BYTES) return 12;
+    if (pase_find_best_strategy(g, nullptr, &mc, cfg.data()) != PASE_ERR_HIP || g->dense_only) return 13;
+    pase_graph_destroy(g);
+    std::puts("limits ok");
+}
+"""
+
+
 def host_program(source, lib, tmp_path, expect):
     src = tmp_path / "program.cpp"
     src.write_text(source)
@@ -153,3 +218,7 @@ def test_descriptors_stay_in_their_region(san_lib, tmp_path):
 
 def test_caller_given_costs_keep_the_structure(san_lib, tmp_path):
     host_program(OVERRIDE, san_lib, tmp_path, "override ok")
+
+
+def test_memory_limits_that_the_dense_fills_meet(san_lib, tmp_path):
+    host_program(LIMITS, san_lib, tmp_path, "limits ok")
