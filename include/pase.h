@@ -199,10 +199,11 @@ typedef enum {
                                    workgroups with 64-bit atomic minima of the packed keys (the
                                    strict "<" tie-break is unchanged: keys are distinct per c),
                                    so the predecessor's table is never written to HBM and read
-                                   back; with the split match model and no kept tables, a pair
-                                   whose predecessor has one-digit lookups only and whose reader
-                                   has one edge to each of two digits is evaluated with the two
-                                   minima exchanged (the exchange fill) instead; 0: every vertex fills on its own.  Re-plans */
+                                   back; with the split match model and no kept tables, a pair whose
+                                   predecessor has one-digit lookups only and whose reader has one
+                                   edge to each of two digits is evaluated with the two minima
+                                   exchanged (the exchange fill) instead; 0: every vertex fills on
+                                   its own.  Re-plans */
     PASE_OPT_HOIST_ELEMS = 21,  /* one-stream level layout (the level schedule, or the bulk lane
                                    schedule over its memory budget): a vertex whose prep blocks
                                    hold at least this many elements (default 2^20) and read only
@@ -383,16 +384,22 @@ pase_status pase_stats(pase_graph_t g, pase_run_stats *out);
  * PASE_OPT_PROFILE=1, its fill time. */
 typedef struct {
     uint32_t position;   /* index in the GenerateSeq order */
-    uint32_t kernel;     /* 0 = generic fill, 1 = row/column-chunk fill (tile_cols 0: its class form, which
-                            evaluates the column digit's transfer cost per split class), 2 = direct fill */
+    uint32_t kernel;     /* 0 = generic fill, 1 = row/column-chunk fill, 2 = direct fill.  1 or 2 with
+                            tile_cols 0 is a structured form: the class fill (parts 0; kernel 2 without
+                            a column: the direct fill, or the class fill's plain minimum), the joint fill
+                            (parts 2, with a column) or the exchange fill (parts 2, without one);
+                            splits 0: a vertex whose table such a fill does without, so that nothing is
+                            filled for it (the half fill runs in its slot) */
     uint32_t num_configs, dep_count;
     uint64_t entries;    /* |table| = product of K over D(v) */
     uint64_t cells;      /* K_v * entries */
     int32_t column;      /* row kernel: column digit (vertex id), -1 for none or the generic kernel */
     uint32_t outer, rows, tile_cols;
-    uint32_t tile_rows;  /* rows per lane (1 or 2); class form: rows per workgroup */
+    uint32_t tile_rows;  /* rows per lane (1 or 2); class fill: rows per workgroup; exchange fill: columns
+                            per workgroup */
     uint32_t splits, row_terms, lookups;
-    uint32_t parts;      /* row kernel: waves sharing one tile's c range (1, 2 or 4) */
+    uint32_t parts;      /* row kernel: waves sharing one tile's c range (1, 2 or 4); joint and exchange
+                            fills: 2, the vertices filled together; class fill: 0 */
     double fill_ms;      /* PASE_OPT_PROFILE: event time of this vertex's fill kernel */
     uint32_t level;      /* dependency level: 1 + the largest level of the tables it reads */
     uint32_t lane;       /* schedules 4 and 5: the lane it runs on: 0 = small vertices (highest wave
@@ -401,9 +408,10 @@ typedef struct {
                             below (key_bound + 1) * 2^ceil(log2 K_v)); ~0 if it exceeds 64 bits */
     uint64_t table_bound; /* upper bound of every entry of its DP table; ~0 likewise */
     uint32_t key_type;    /* key type of the plan (the same for every vertex): 0 fp64, 1 uint64, 2 128-bit */
-    uint32_t fused;       /* PASE_OPT_FUSED_MIN: 1 = its fill also forms the minimum of its table's reader,
-                             2 = that reader (its fill is then a one-split reduction of those keys, or
-                             an exchange fill that does without the other's table), 0 = neither */
+    uint32_t fused;       /* PASE_OPT_FUSED_MIN: 1 = its fill also forms the minimum of its table's reader
+                             (row kernel), or that reader's exchange fill does without its table; 2 = the
+                             reader (its fill is a one-split reduction of those keys, or the exchange
+                             fill: tile_cols 0); 0 = neither */
     int32_t prep_after;   /* its prep blocks read only tables of slots up to this one (-1: none) and are
                              built right after it, beside the launches of the slots in between -- on a
                              side stream (level layout) or at the end of that slot's launches on lane

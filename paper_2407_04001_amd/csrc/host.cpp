@@ -524,13 +524,15 @@ static void hoist_preps(pase_graph_t g, Plan &P, bool lanes) {
 // the sequence, so one pass suffices.
 // (A class fill counts from a quarter of the threshold: it is bound by the
 // stores of its table, which hold up the other lane's loads as well.)
-static bool bulk_fill(const VPlan &vp, double bulk_us) {
-    return vp.kernel == kRows && vp.est_us * (vp.classes || vp.joint >= 0 ? 4.0 : 1.0) >= bulk_us;
+// A vertex without a table of its own is where its half fill's reader is.
+static bool bulk_fill(const Plan &P, const VPlan &vp, double bulk_us) {
+    return (vp.kernel == kRows && vp.est_us * (vp.classes || vp.joint >= 0 ? 4.0 : 1.0) >= bulk_us) ||
+           (vp.absorbed >= 0 && bulk_fill(P, P.v[vp.absorbed], bulk_us));
 }
 
 static void assign_bulk_lanes(Plan &P, double bulk_us) {
     for (auto &vp : P.v) {
-        bool bulk = bulk_fill(vp, bulk_us);
+        bool bulk = bulk_fill(P, vp, bulk_us);
         for_reads(P, vp, [&](int j) { bulk |= P.v[j].lane == 1; });
         vp.lane = bulk ? 1 : 0;
     }
@@ -547,7 +549,7 @@ static void assign_bulk_lanes(Plan &P, double bulk_us) {
 // for each other level by level.
 static void assign_split_lanes(Plan &P, double bulk_us) {
     for (auto &vp : P.v) {
-        bool one = vp.level < kSplitBatchedLevels || bulk_fill(vp, bulk_us);
+        bool one = vp.level < kSplitBatchedLevels || bulk_fill(P, vp, bulk_us);
         for_reads(P, vp, [&](int j) { one |= P.v[j].lane == 1 && P.v[j].level >= kSplitBatchedLevels; });
         vp.lane = one ? 1 : 0;
     }
@@ -975,7 +977,7 @@ static pase_status plan_fills(pase_graph_t g) {
         out.TM = 1;
         out.nsplit = 1;
         out.cper = vp.K;
-        out.parts = 0;
+        out.parts = 2;
         out.layout = out.R;
         out.layout.push_back(by);
         out.stride.assign(out.layout.size(), 1);
@@ -1160,8 +1162,21 @@ static pase_status plan_fills(pase_graph_t g) {
         if (joint_kt() == 2 || (joint_kt() == 1 && joint_top(i, j) >> 60)) return;
         vp.joint = j;
         vp.exch = true;
+        // (layout and strides stay those of the dense plan)
+        vp.kernel = kRows;
+        vp.z = -1;
+        vp.O.clear();
+        vp.R = vp.layout;
+        vp.MO = 1;
+        vp.MR = vp.N;
+        vp.TZ = 0;
+        vp.TM = kExchCols;
+        vp.na = 0;
         vp.nsplit = 1;
         vp.cper = vp.K;
+        vp.parts = 2;
+        // 24 us at 1.8e7 (c, y, z), 102 at 1.1e8
+        vp.est_us = 8.0 + 0.9e-6 * (double)vj.K * (double)vp.N;
     };
     for (int i = 0; i < n; i++) {
         plan_one(i, 0, 0, false);
@@ -1171,7 +1186,25 @@ static pase_status plan_fills(pase_graph_t g) {
         VPlan &vp = P.v[i];
         if (vp.joint < 0) continue;
         vp.jearly = g->schedule != kSchedSeq && g->hoist_elems != 0;
-        P.v[vp.joint].absorbed = i;
+        VPlan &vj = P.v[vp.joint];
+        vj.absorbed = i;
+        if (g->keep_tables) continue;
+        // no fill of its own: what runs in its slot is the half fill (9 us for 84
+        // c's of 462 configurations each, 13 for 203 of 731; 9 us for 343 upper
+        // indices of 462, 23 for 819 of 731)
+        if (vp.exch) {
+            vj.kernel = kRows;
+            vj.z = vp.vi;
+            vj.O.clear();
+            vj.MO = 1;
+            vj.MR = vp.N;
+            vj.TZ = vj.na = vj.parts = 0;
+            vj.TM = vj.nsplit = 1;
+            vj.cper = vj.K;
+            vj.est_us = 8.0 + 4.5e-6 * (double)exch_half_elems(vp.K, vj.K, g->K[vp.layout[0]], g->K[vp.layout[1]]);
+        } else {
+            vj.est_us = 7.0 + 2e-5 * (double)vp.jupper * vj.K;
+        }
     }
     // One launch per level and kernel variant: a small column-form row vertex
     // of a level is re-planned with the tile shape of the level's largest one
@@ -1195,6 +1228,7 @@ static pase_status plan_fills(pase_graph_t g) {
         for (int i = 0; i < n; i++) {
             const int d = dom[P.v[i].level];
             if (d < 0 || d == i || P.v[i].kernel != kRows || P.v[i].z < 0 || P.v[i].joint >= 0) continue;
+            if (P.v[i].absorbed >= 0 && !P.v[i].classes && !g->keep_tables) continue;
             // (split chains: only the batched levels share launches level-wide)
             if (g->schedule == kSchedSplit && P.v[i].level >= kSplitBatchedLevels) continue;
             const VPlan &dv = P.v[d];
@@ -2065,7 +2099,7 @@ extern "C" pase_status pase_vertex_info_get(pase_graph_t g, uint32_t v, pase_ver
     x.tile_cols = vp.TZ;
     x.tile_rows = vp.TM;
     x.parts = vp.kernel == kRows ? vp.parts : 0;
-    x.splits = vp.nsplit;
+    x.splits = vp.absorbed >= 0 && !g->keep_tables ? 0 : vp.nsplit;
     x.row_terms = vp.na;
     x.lookups = (uint32_t)vp.terms.size();
     x.fill_ms = vp.fill_ms;

@@ -10,6 +10,19 @@ from workloads import random_graph
 from workloads.gen import _Builder
 
 
+def form(x):
+    """The fill a vertex's plan reports (pase_vertex_info)."""
+    if x["splits"] == 0:
+        return "none"
+    if x["tile_cols"]:
+        return "rows"
+    if x["kernel"] == 0:
+        return "generic"
+    if x["parts"] == 2:
+        return "joint" if x["column"] >= 0 else "exchange"
+    return "class" if x["column"] >= 0 else "minimum"
+
+
 def star(dims, elems=(48, 48, 7), sizes=16, r=1, twice=()):
     """v0 with dims[0] loop dims joined to neighbours with dims[1:] loop dims,
     all joined to each other (so v0, the lowest id, comes first and its table
@@ -298,13 +311,14 @@ def test_joint_plan(case):
     pg.enumerate_configs(p, all_integers=every)
     x = pg.vertex_info(2)
     assert (x["kernel"], x["column"], x["tile_cols"]) == (1, 3, 0) and x["lookups"] >= 1, x
+    assert form(x) == "joint" and form(pg.vertex_info(1)) == "none"
     assert 2 in pg.dependent_set(1) and 3 in pg.dependent_set(1) and 3 in pg.dependent_set(2)
     for sched in (0, 1, 4, 5):
         for hoist in (0, 1 << 20):
             pg.set_option(P.OPT_SCHEDULE, sched)
             pg.set_option(P.OPT_HOIST_ELEMS, hoist)
             pg.set_option(P.OPT_KEEP_TABLES, 1)
-            assert pg.plan_check() > 0
+            assert pg.plan_check() > 0 and form(pg.vertex_info(1)) == "class" and form(pg.vertex_info(2)) == "joint"
             kept = pg.workspace_size()
             pg.set_option(P.OPT_KEEP_TABLES, 0)
             assert pg.plan_check() > 0 and pg.workspace_size() <= kept
@@ -338,6 +352,7 @@ def test_joint_every_table(case, key):
         pg.set_option(P.OPT_HOIST_ELEMS, hoist)
         for keep in (1, 0):
             pg.set_option(P.OPT_KEEP_TABLES, keep)
+            assert form(pg.vertex_info(2)) == "joint"
             assert pg.find_best_strategy() == o.result(), (sched, hoist, keep)
             if keep:
                 for i, v in enumerate(o.sequence()):
@@ -439,9 +454,23 @@ def test_exchange_plan(case):
             kept = pg.workspace_size()
             pg.set_option(P.OPT_KEEP_TABLES, 0)
             assert pg.plan_check() > 0 and pg.workspace_size() <= kept
+            assert (form(pg.vertex_info(3)), form(pg.vertex_info(4))) == ("none", "exchange")
             assert (pg.vertex_info(3)["fused"], pg.vertex_info(4)["fused"]) == (1, 2)
     pg.set_option(P.OPT_FUSED_MIN, 0)
     assert not any(pg.vertex_info(v)["fused"] for v in range(7))
+    assert "exchange" not in [form(pg.vertex_info(v)) for v in range(7)]
+
+
+def test_exchange_lanes():
+    """The lanes follow the fills that run: a pair whose dense fill would take
+    past the bulk threshold (84 x 462 x 210 x 210 cells), whose exchange fill
+    takes 12 us, is on the lane of the small vertices."""
+    from paper_2407_04001_amd import pase as P
+    P.load()
+    pg = P.Graph(exchange(3, 5, 4, 4))
+    pg.enumerate_configs(64)
+    assert form(pg.vertex_info(4)) == "exchange"
+    assert [pg.vertex_info(v)["lane"] for v in (3, 4, 5, 6)] == [0, 0, 0, 0]
 
 
 @pytest.mark.gpu
@@ -471,7 +500,7 @@ def test_exchange_strategies(case, key):
         for sched, hoist in ((5, 1 << 20), (0, 1 << 20), (1, 1 << 20), (5, 0)):
             pg.set_option(P.OPT_SCHEDULE, sched)
             pg.set_option(P.OPT_HOIST_ELEMS, hoist)
-            assert pg.vertex_info(4)["fused"] == 2
+            assert form(pg.vertex_info(4)) == "exchange"
             assert pg.find_best_strategy() == o.result(), (elems, sched, hoist)
         if pg.workspace_size() <= P.NOALLOC_WORKSPACE_BYTES:
             assert P.pase_find_best_strategy_noalloc(pg.h, pg.nv) == o.result()

@@ -70,7 +70,7 @@ def _compare_all_entries(pg, o, g, max_entries=2048):
 
 def _run(P, g, p=None, keep=True, kernel=0, key=0, costs=None, rule=0, schedule=0, tile=(0, 0),
          parts=0, splits=0, all_integers=False, bf=False, volume=False, grad=False,
-         direct=0, bulk_us=None, halo=False, fuse=None):
+         direct=0, bulk_us=None, halo=False, fuse=None, hoist=None):
     """direct: PASE_OPT_DIRECT_CELLS (0 = off, so the tests aimed at the row and
     generic kernels keep them; None = the library's default)."""
     pg = P.Graph(g, seq_rule=rule)
@@ -93,6 +93,8 @@ def _run(P, g, p=None, keep=True, kernel=0, key=0, costs=None, rule=0, schedule=
         pg.set_option(P.OPT_BULK_US, bulk_us)
     if fuse is not None:
         pg.set_option(P.OPT_FUSED_MIN, int(fuse))
+    if hoist is not None:
+        pg.set_option(P.OPT_HOIST_ELEMS, hoist)
     if costs is not None:
         pg.override_costs(*costs)
     mc, strat = pg.find_best_strategy()
@@ -725,6 +727,7 @@ def test_fused_minimum_every_entry(P, schedule, key):
     pg, mc, strat = _run(P, g, schedule=schedule, key=key, direct=None, bulk_us=5)
     fused = [v for v in range(pg.nv) if pg.vertex_info(v)["fused"]]
     assert len(fused) == 2, fused
+    assert all(pg.vertex_info(v)["tile_cols"] for v in fused)
     assert (mc, strat) == o.result()
     _compare_all_entries(pg, o, g, max_entries=4096)
     pg2, mc2, strat2 = _run(P, g, schedule=schedule, key=key, direct=None, bulk_us=5, fuse=False)

@@ -652,11 +652,14 @@ def test_fused_minimum_plan(pase):
     minimum of the last cross-attention key/value projection into its
     predecessor's fill (producer flagged 1, reader 2, adjacent in the order,
     the producer's column digit being the reader); the option validates,
-    turns it off and on, and the launch plan checks in every schedule."""
+    turns it off and on, and the launch plan checks in every schedule.  The
+    dense fills form that minimum in the row kernel's epilogue; by default the
+    same pair is an exchange fill."""
     P = pase
     g = workload("w4_transformer")
     pg = P.Graph(g)
     assert _status(lambda: pg.set_option(P.OPT_FUSED_MIN, 2)) == P.INVALID_ARGUMENT
+    pg.set_option(P.OPT_HOIST_ELEMS, (1 << 20) - 1)   # (a threshold below its default: the dense fills)
     pg.enumerate_configs(g["p"])
     info = {v: pg.vertex_info(v) for v in range(pg.nv)}
     prod = [v for v in info if info[v]["fused"] == 1]
@@ -665,6 +668,11 @@ def test_fused_minimum_plan(pase):
     a, b = info[prod[0]], info[read[0]]
     assert b["position"] == a["position"] + 1 and a["column"] == read[0] and b["column"] == -1
     assert a["splits"] == 1 and b["splits"] == 1 and a["outer"] == 1 and a["rows"] == b["rows"]
+    assert a["tile_cols"] > 1 and b["tile_cols"] == 1
+    pg.set_option(P.OPT_HOIST_ELEMS, 1 << 20)
+    a, b = pg.vertex_info(prod[0]), pg.vertex_info(read[0])
+    assert (a["fused"], b["fused"], a["tile_cols"], b["tile_cols"], a["splits"], b["parts"]) == (1, 2, 0, 0, 0, 2)
+    assert a["column"] == read[0] and b["column"] == -1 and a["rows"] == b["rows"]
     for sched in (0, 1, 4, 5):
         for keep in (0, 1):
             pg.set_option(P.OPT_SCHEDULE, sched)
