@@ -199,7 +199,7 @@ typedef enum {
                                    workgroups with 64-bit atomic minima of the packed keys (the
                                    strict "<" tie-break is unchanged: keys are distinct per c),
                                    so the predecessor's table is never written to HBM and read
-                                   back; with the split match model and no kept tables, a pair whose
+                                   back; with the split match model, a pair whose
                                    predecessor has one-digit lookups only and whose reader has one
                                    edge to each of two digits is evaluated with the two minima
                                    exchanged (the exchange fill) instead; 0: every vertex fills on

@@ -1134,10 +1134,10 @@ static pase_status plan_fills(pase_graph_t g) {
     // Costs ten operations per (c_j, y, z) and two launches, against two per
     // (c_j, c_i, y, z) and three: 660 -> 35 us at K = 84, 462, 462, 462 and
     // 5158 + 1156 -> 115 us at 203, 731, 731, 731; from 24 configurations
-    // up, like the joint fill.  Not with kept tables (j's is then wanted).
+    // up, like the joint fill.  With kept tables j's is filled by itself as well.
     auto plan_exchange = [&](int i) {
         VPlan &vp = P.v[i];
-        if (!g->fuse_min || g->keep_tables || !joint_ok || vp.classes || vp.joint >= 0 || vp.kernel == kDirect) return;
+        if (!g->fuse_min || !joint_ok || vp.classes || vp.joint >= 0 || vp.kernel == kDirect) return;
         if (vp.terms.size() != 1 || vp.D.size() != 2 || vp.terms[0].dig.size() != 2 || vp.edges.size() != 2 ||
             vp.K < 24 || vp.K > kExchMaxK)
             return;

@@ -436,9 +436,9 @@ def test_exchange_identity(seed):
 
 @pytest.mark.parametrize("case", range(len(EXCHANGES)))
 def test_exchange_plan(case):
-    """The pair is flagged as a fused minimum without v_j's table: the launch
-    plan checks under every schedule; not with kept tables (whose workspace is
-    larger) or the option off."""
+    """The pair is an exchange fill without v_j's table (with it, filled by
+    itself, when tables are kept): the launch plan checks under every schedule;
+    not with the option off."""
     from paper_2407_04001_amd import pase as P
     P.load()
     dj, di, dy, dz, perm, p, every = EXCHANGES[case]
@@ -451,6 +451,7 @@ def test_exchange_plan(case):
             pg.set_option(P.OPT_HOIST_ELEMS, hoist)
             pg.set_option(P.OPT_KEEP_TABLES, 1)
             assert pg.plan_check() > 0
+            assert form(pg.vertex_info(3)) in ("rows", "generic") and form(pg.vertex_info(4)) == "exchange"
             kept = pg.workspace_size()
             pg.set_option(P.OPT_KEEP_TABLES, 0)
             assert pg.plan_check() > 0 and pg.workspace_size() <= kept
@@ -478,30 +479,37 @@ def test_exchange_lanes():
 @pytest.mark.parametrize("case", range(len(EXCHANGES)))
 def test_exchange_strategies(case, key):
     """Against the oracle under each schedule, with the half fill in v_j's slot
-    or just before the fill, for several tensor sizes (v_j's argmin is
-    evaluated afterwards, so a wrong entry shows as another strategy or cost)."""
+    or just before the fill, for several tensor sizes: every table with tables
+    kept, and the strategy with v_j's left out (its argmin evaluated
+    afterwards)."""
     import torch
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2407_04001_amd import pase as P
     from oracle.oracle import Oracle
     dj, di, dy, dz, perm, p, every = EXCHANGES[case]
-    for elems in ((40, 24, 33, 17, 11, 9), (5, 90, 700, 300, 2, 60), (900, 4, 4, 3000, 2000, 1), (1, 1, 1, 1, 1, 1)):
+    sizes = ((40, 24, 33, 17, 11, 9), (5, 90, 700, 300, 2, 60), (900, 4, 4, 3000, 2000, 1), (1, 1, 1, 1, 1, 1))
+    for elems in sizes[:1] if p == 23 else sizes:
         g = exchange(dj, di, dy, dz, perm, elems=elems)
         print(f"exchange fill {EXCHANGES[case]} key={key} elems={elems}", flush=True)
         o = Oracle(g)
         o.configs(p, all_integers=every)
         o.solve(threads=os.cpu_count() or 1)
+        want = [o.fingerprint(i) for i in range(7)]
         pg = P.Graph(g)
         pg.set_option(P.OPT_DIRECT_CELLS, 1)
         pg.enumerate_configs(p, all_integers=every)
         pg.set_option(P.OPT_KEY_TYPE, key)
-        pg.set_option(P.OPT_KEEP_TABLES, 0)
         for sched, hoist in ((5, 1 << 20), (0, 1 << 20), (1, 1 << 20), (5, 0)):
             pg.set_option(P.OPT_SCHEDULE, sched)
             pg.set_option(P.OPT_HOIST_ELEMS, hoist)
-            assert form(pg.vertex_info(4)) == "exchange"
-            assert pg.find_best_strategy() == o.result(), (elems, sched, hoist)
+            for keep in (1, 0):
+                pg.set_option(P.OPT_KEEP_TABLES, keep)
+                assert form(pg.vertex_info(4)) == "exchange"
+                assert pg.find_best_strategy() == o.result(), (elems, sched, hoist, keep)
+                if keep:
+                    for i, v in enumerate(o.sequence()):
+                        assert pg.fingerprint(v) == want[i], (v, elems, sched, hoist)
         if pg.workspace_size() <= P.NOALLOC_WORKSPACE_BYTES:
             assert P.pase_find_best_strategy_noalloc(pg.h, pg.nv) == o.result()
 

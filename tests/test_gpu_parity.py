@@ -720,16 +720,18 @@ def _fused_graph():
 def test_fused_minimum_every_entry(P, schedule, key):
     """The fused producer/reader pair against the oracle entry by entry (every
     table, with tables kept so the producer also writes its own), under each
-    schedule and both 64-bit key types; and the same search with fusion off."""
+    schedule and both 64-bit key types, in the row kernel's epilogue (the
+    dense fills) and as an exchange fill; and the same search with fusion off."""
     g = _fused_graph()
     say(f"fused minimum schedule={schedule} key={key}")
     o = _oracle(g)
-    pg, mc, strat = _run(P, g, schedule=schedule, key=key, direct=None, bulk_us=5)
-    fused = [v for v in range(pg.nv) if pg.vertex_info(v)["fused"]]
-    assert len(fused) == 2, fused
-    assert all(pg.vertex_info(v)["tile_cols"] for v in fused)
-    assert (mc, strat) == o.result()
-    _compare_all_entries(pg, o, g, max_entries=4096)
+    for hoist, rows in (((1 << 20) - 1, True), (1 << 20, False)):
+        pg, mc, strat = _run(P, g, schedule=schedule, key=key, direct=None, bulk_us=5, hoist=hoist)
+        fused = [v for v in range(pg.nv) if pg.vertex_info(v)["fused"]]
+        assert len(fused) == 2, fused
+        assert all((pg.vertex_info(v)["tile_cols"] > 0) == rows for v in fused if pg.vertex_info(v)["fused"] == 2)
+        assert (mc, strat) == o.result()
+        _compare_all_entries(pg, o, g, max_entries=4096)
     pg2, mc2, strat2 = _run(P, g, schedule=schedule, key=key, direct=None, bulk_us=5, fuse=False)
     assert not any(pg2.vertex_info(v)["fused"] for v in range(pg2.nv))
     assert (mc2, strat2) == (mc, strat)
