@@ -264,9 +264,8 @@ def triangle(di, dj, dy, has_e, looks, perm=False, r=1, upper=2):
             continue
         b.vertex(f"v{k}", [12 + k] * d, [f"x{i}" for i in range(d)], [d - 1] if d > 2 else [], 1)
 
-    def edge(u, v, elems, free=0):
-        rank = min(dims[u] if u or looks else 1, dims[v]) - free
-        d = list(range(max(1, rank)))
+    def edge(u, v, elems):
+        d = list(range(max(1, min(dims[u] if u or looks else 1, dims[v]))))
         b.edge(u, v, d, d[::-1] if perm else d, elems=elems)
     edge(1, 2, 40)
     edge(1, 3, 24)
@@ -288,13 +287,119 @@ def triangle(di, dj, dy, has_e, looks, perm=False, r=1, upper=2):
 
 
 # (dims of v_i, v_j, y; edge from v_i to y; v_j looks a table up; permuted maps; p, every integer): K 35 to
-# 252 on one configuration per thread, 738 on one of 768 threads, 796 on two; classes of one and of several configurations
+# 252 on one configuration per thread, 738 on one of 768 threads, 796 on two; classes of one and of several
+# configurations, of five on both sides of an entry in the last two (y of three dims, its neighbours of four)
 TRIANGLES = [(4, 4, 4, True, False, False, 8, False), (4, 4, 4, True, True, True, 16, False),
              (5, 4, 4, True, False, True, 16, False), (4, 5, 4, True, True, False, 16, False),
              (4, 4, 3, False, False, True, 16, False), (4, 4, 3, False, True, False, 32, False),
              (3, 4, 4, True, False, False, 12, True), (4, 4, 3, False, True, True, 10, True),
              (5, 4, 5, True, True, True, 32, False), (3, 2, 2, False, False, True, 64, True),
-          (3, 2, 2, True, False, False, 60, True)]
+             (3, 2, 2, True, False, False, 60, True), (4, 4, 3, True, False, True, 16, False),
+             (4, 4, 3, True, True, True, 16, False)]
+
+
+def maps(rng, nu, nv):
+    """A tensor whose dims map at least all but one loop dim of either end:
+    permuted, some dims unmapped at one end, some loop dims mapped twice."""
+    for _ in range(1000):
+        rank = int(rng.integers(max(1, max(nu, nv) - 1), max(nu, nv) + 3))
+        if rank > 8:
+            continue
+        su, sv = rng.integers(-1, nu, rank), rng.integers(-1, nv, rank)
+        if len(set(su) - {-1}) >= nu - 1 and len(set(sv) - {-1}) >= nv - 1:
+            return [int(k) for k in su], [int(k) for k in sv]
+    raise AssertionError("no map")
+
+
+def random_triangle(seed):
+    """triangle() with its three edges between v_i, v_j and y mapped at random."""
+    rng = np.random.default_rng(seed)
+    di, dj, dy = (int(k) for k in rng.integers(3, 5, 3))
+    g = triangle(di, dj, dy, True, False)
+    dims = {1: dj, 2: di, 3: dy}
+    for e in g["edges"]:
+        if {e["src"], e["dst"]} <= {1, 2, 3}:
+            e["src_dim"], e["dst_dim"] = maps(rng, dims[e["src"]], dims[e["dst"]])
+    return g
+
+
+# (in the last three an entry's pair of combined classes has several configurations on both sides)
+RANDOM_TRIANGLES = list(range(12)) + [30, 77, 106]
+
+
+@pytest.mark.parametrize("every,p", [(False, 16), (True, 8)])
+@pytest.mark.parametrize("case", range(len(RANDOM_TRIANGLES) + len(TRIANGLES)))
+def test_joint_identity(case, every, p):
+    """The minima over classes, with at most one pair of combined classes per
+    entry, against the dense minimum over both configurations: value and the
+    lowest v_i, at every y, for the edges of joint plans; costs with ties."""
+    from oracle.oracle import Oracle
+    from paper_2407_04001_amd import pase as P
+    P.load()
+    if case < len(RANDOM_TRIANGLES):
+        g = random_triangle(RANDOM_TRIANGLES[case])
+    else:
+        di, dj, dy, has_e, looks, perm = TRIANGLES[case - len(RANDOM_TRIANGLES)][:6]
+        g = triangle(di, dj, dy, has_e, looks, perm)
+    pg = P.Graph(g)
+    pg.set_option(P.OPT_DIRECT_CELLS, 1)
+    pg.enumerate_configs(p, all_integers=every)
+    if form(pg.vertex_info(2)) != "joint":
+        pytest.skip("not a joint fill")
+    o = Oracle(g)
+    o.configs(p, all_integers=every)
+    K = {v: len(o.splits(v)) for v in (1, 2, 3)}
+    rng = np.random.default_rng(case)
+    big = np.int64(1) << 60
+
+    def edge(u, v):
+        """t (K_u x K_v), f of either end, same class; None without an edge."""
+        at = [k for k, e in enumerate(g["edges"]) if {e["src"], e["dst"]} == {u, v}]
+        if not at:
+            return None
+        e, k = g["edges"][at[0]], at[0]
+        t = o.edge_costs(k).astype(np.int64)
+        sig = {}
+        for x, dims in ((e["src"], e["src_dim"]), (e["dst"], e["dst_dim"])):
+            sp = o.splits(x).astype(np.int64)
+            sig[x] = np.stack([sp[:, d] if d >= 0 else np.ones(len(sp), np.int64) for d in dims], 1)
+        f = [g["comm_weight"] * -(-e["elems"] // o.splits(x).astype(np.int64).prod(1)) for x in (u, v)]
+        return t if e["src"] == u else t.T, f[0], f[1], (sig[u][:, None, :] == sig[v][None, :, :]).all(2)
+    to, fio, fjo, so = edge(2, 1)
+    tj, fjy, fyj, sj = edge(1, 3)
+    has_e = edge(2, 3) is not None
+    ti, fiy, fyi, si = edge(2, 3) or (np.zeros((K[2], K[3]), np.int64), None, None, None)
+    hi = int(max(to.max(), tj.max(), ti.max())) // 4 + 1
+    XI = rng.integers(0, 5, K[2]) * hi * K[2] + np.arange(K[2])    # keys of v_i
+    XJ = rng.integers(0, 5, K[1]) * hi * K[2]
+    to, tj, ti, fio, fjo, fjy, fyj = (x * K[2] for x in (to, tj, ti, fio, fjo, fjy, fyj))
+    if has_e:
+        fiy, fyi = fiy * K[2], fyi * K[2]
+    pair = XI[:, None] + XJ[None, :] + to                           # c, c'
+    J0, J1 = (XJ[None, :] + to).min(1), (XJ[None, :] + fjy[None, :] + to).min(1)
+    I0 = (XI[:, None] + to).min(0)
+    I1 = (XI[:, None] + fiy[:, None] + to).min(0) if has_e else None
+    several = 0
+    for y in range(K[3]):
+        dense = (pair + ti[:, y][:, None] + tj[:, y][None, :]).min()
+        best = (ti[:, y] + XI + np.minimum(J0 + fyj[y], J1)).min()
+        cj = np.flatnonzero(sj[:, y])
+        ci = np.flatnonzero(si[:, y]) if has_e else np.arange(0)
+        if len(cj):
+            both = np.minimum(I0[cj] + fyi[y], I1[cj]) if has_e else I0[cj]
+            best = min(best, (XJ[cj] + both).min())
+        if len(cj) and len(ci):
+            # t(c', c) as one of the f, and as 0 in the one pair of combined classes
+            best = min(best, XI[ci].min() + (XJ + fjo)[cj].min(), (XI + fio)[ci].min() + XJ[cj].min())
+            at = so[np.ix_(ci, cj)]
+            if at.any():
+                a, b = np.flatnonzero(at.any(1)), np.flatnonzero(at.any(0))
+                assert at[np.ix_(a, b)].all(), (y, "more than one pair of combined classes")
+                best = min(best, XI[ci[a]].min() + XJ[cj[b]].min())
+                several += len(a) > 1 and len(b) > 1
+        assert best == dense < big, y
+    if case < len(RANDOM_TRIANGLES) and RANDOM_TRIANGLES[case] >= 30:
+        assert several
 
 
 @pytest.mark.parametrize("case", range(len(TRIANGLES)))
@@ -322,6 +427,35 @@ def test_joint_plan(case):
             kept = pg.workspace_size()
             pg.set_option(P.OPT_KEEP_TABLES, 0)
             assert pg.plan_check() > 0 and pg.workspace_size() <= kept
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("key", [0, 1])
+@pytest.mark.parametrize("seed", RANDOM_TRIANGLES)
+def test_random_maps_every_table(seed, key):
+    """Unmapped and repeated tensor dims on the three edges of a joint fill (or
+    of the fill the plan takes in its place): every table, then the strategy
+    without v_j's."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_04001_amd import pase as P
+    from oracle.oracle import Oracle
+    g = random_triangle(seed)
+    print(f"random maps seed={seed} key={key}", flush=True)
+    o = Oracle(g)
+    o.configs(16)
+    o.solve(threads=os.cpu_count() or 1)
+    pg = P.Graph(g)
+    pg.set_option(P.OPT_DIRECT_CELLS, 1)
+    pg.set_option(P.OPT_KEY_TYPE, key)
+    pg.enumerate_configs(16)
+    for keep in (1, 0):
+        pg.set_option(P.OPT_KEEP_TABLES, keep)
+        assert pg.find_best_strategy() == o.result()
+        if keep:
+            for i, v in enumerate(o.sequence()):
+                assert pg.fingerprint(v) == o.fingerprint(i), (v, pg.vertex_info(v))
 
 
 @pytest.mark.gpu
@@ -383,11 +517,12 @@ def exchange(dj, di, dy, dz, perm=False, r=1, elems=(40, 24, 33, 17, 11, 9)):
     return b.done()
 
 
-# (dims of v_j, v_i, y, z; permuted maps; p, every integer): K_i 35 to past 512, K_y and K_z odd, below and
-# past a wave, K_j below the four waves of the fill
+# (dims of v_j, v_i, y, z; permuted maps; p, every integer): K_i 28 to 556, K_y and K_z odd, below and past a
+# wave, K_j 3 (a wave of the fill without a c) to 43
 EXCHANGES = [(2, 4, 4, 4, False, 8, False), (4, 4, 3, 4, True, 8, False), (1, 4, 4, 3, True, 8, False),
              (4, 3, 3, 2, False, 7, True), (2, 5, 4, 5, True, 16, False), (1, 4, 5, 4, False, 32, False),
-             (2, 3, 4, 3, True, 7, True), (1, 4, 3, 3, True, 24, True)]
+             (2, 3, 4, 3, True, 7, True), (1, 4, 3, 3, True, 24, True), (1, 6, 5, 5, False, 4, False),
+             (1, 5, 4, 4, True, 23, True)]
 
 
 @pytest.mark.parametrize("seed", range(8))
@@ -542,3 +677,105 @@ def test_memory_limits():
     big.enumerate_configs(64)
     assert big.workspace_size() > P.NOALLOC_WORKSPACE_BYTES
     assert P.pase_find_best_strategy_noalloc(big.h, big.nv) == P.pase_find_best_strategy(big.h, big.nv)
+
+
+# -------------------------------------------------------------- key edges
+def scaled(g, m):
+    """The graph with every cost about m times as large (and no multiple of it:
+    the splits round up)."""
+    return dict(g, vertices=[dict(v, flops_per_point=v["flops_per_point"] * m) for v in g["vertices"]],
+                edges=[dict(e, elems=e["elems"] * m + k % 3) for k, e in enumerate(g["edges"])])
+
+
+# graph, p, every integer, the vertex whose fill is looked at and its form
+EDGE_GRAPHS = [(lambda: star((3, 3, 3, 2)), 16, False, 0, "class"),
+               (lambda: triangle(4, 4, 3, True, True, True), 16, False, 2, "joint"),
+               (lambda: triangle(4, 4, 3, False, False, True), 16, False, 2, "joint"),
+               (lambda: exchange(2, 5, 4, 5, True), 16, False, 4, "exchange"),
+               (lambda: exchange(4, 3, 3, 2), 7, True, 4, "exchange")]
+
+
+def edge_plan(P, graph, p, every, m):
+    """A handle planned at m; None past 64-bit costs."""
+    pg = P.Graph(scaled(graph, m))
+    pg.set_option(P.OPT_DIRECT_CELLS, 1)
+    pg.set_option(P.OPT_KEEP_TABLES, 1)
+    try:
+        pg.enumerate_configs(p, all_integers=every)
+    except P.PaseError as e:
+        assert e.status == P.OVERFLOW, e
+        return None
+    return pg
+
+
+def edge_scales(P, case):
+    """The largest m with fp64 keys, with the structured form in uint64 keys,
+    and with 64-bit keys (bisection on the host), in that order."""
+    build, p, every, v, kind = EDGE_GRAPHS[case]
+    g = build()
+
+    def largest(accept):
+        lo, hi = 1, 1 << 56
+        while hi - lo > 1:
+            mid = (lo + hi) // 2
+            pg = edge_plan(P, g, p, every, mid)
+            if pg is not None and accept(pg.vertex_info(v)):
+                lo = mid
+            else:
+                hi = mid
+        return lo
+    return g, [largest(lambda x: x["key_type"] == 0), largest(lambda x: x["key_type"] < 2 and form(x) == kind),
+               largest(lambda x: x["key_type"] < 2)]
+
+
+@pytest.mark.parametrize("case", range(len(EDGE_GRAPHS)))
+def test_key_edge_plan(case):
+    """The key types meet at 2^53 and 2^64; in uint64 keys the joint and the
+    exchange fill stop where the sums they form could wrap (2^64, and 2^60 for
+    the mark of an empty class), the class fill, whose sums are those of the
+    dense fill, nowhere before."""
+    from paper_2407_04001_amd import pase as P
+    P.load()
+    g, (a, b, c) = edge_scales(P, case)
+    _, p, every, v, kind = EDGE_GRAPHS[case]
+
+    def top(m):
+        pg = edge_plan(P, g, p, every, m)
+        return max((int(x["key_bound"]) + 1) << max(0, (int(k) - 1).bit_length())
+                   for x, k in ((pg.vertex_info(u), pg.K[u]) for u in range(pg.nv)))
+    assert top(a) <= 1 << 53 < top(a + 1) and top(c) <= 1 << 64
+    assert a < b <= c
+    below, past = edge_plan(P, g, p, every, b), edge_plan(P, g, p, every, b + 1)
+    assert form(below.vertex_info(v)) == kind and below.plan_check() > 0
+    if kind == "class":
+        assert b == c
+    else:
+        assert past.vertex_info(v)["key_type"] == 1 and form(past.vertex_info(v)) != kind and past.plan_check() > 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", range(len(EDGE_GRAPHS)))
+def test_key_edge_every_table(case):
+    """Every table on both sides of each edge (fp64 and uint64 keys with the
+    structured fill; uint64 keys with and without it; uint64 and 128-bit keys)."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2407_04001_amd import pase as P
+    from oracle.oracle import Oracle
+    g, scales = edge_scales(P, case)
+    _, p, every, v, kind = EDGE_GRAPHS[case]
+    for m in sorted({x for s in scales for x in (s, s + 1)}):
+        pg = edge_plan(P, g, p, every, m)
+        if pg is None:
+            continue
+        x = pg.vertex_info(v)
+        print(f"key edge {kind} m={m} key type {x['key_type']} {form(x)}", flush=True)
+        o = Oracle(scaled(g, m))
+        o.configs(p, all_integers=every)
+        o.solve(threads=os.cpu_count() or 1)
+        assert pg.find_best_strategy() == o.result(), m
+        for i, u in enumerate(o.sequence()):
+            assert pg.fingerprint(u) == o.fingerprint(i), (u, m, pg.vertex_info(u))
+        pg.set_option(P.OPT_KEEP_TABLES, 0)
+        assert pg.find_best_strategy() == o.result(), m
