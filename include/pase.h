@@ -117,19 +117,19 @@ typedef enum {
                                    the keys need 128 bits; 2 = force 128-bit keys.  Re-plans */
     PASE_OPT_PROFILE = 5,       /* 1: time every fill launch with HIP events (pase_stats);
                                    2: only the row kernel's launches with a column chunk per lane
-                                   (the dominant kernel; fewer events, so less overhead) */
+                                   (the largest of the dense fills; fewer events, so less overhead) */
     PASE_OPT_SCHEDULE = 6,      /* 5 (default): split chains -- the leaves (dependency level 0)
                                    share their kernel launches on the caller's stream; after
-                                   them every row-kernel vertex whose planned fill takes at least
-                                   PASE_OPT_BULK_US, with every vertex reading its table, runs on
-                                   that stream level by level (lane 1), and all other vertices
-                                   level by level on a side stream at the highest wave priority
-                                   (lane 0); events only where a table is read across the two, so
-                                   the chain of small vertices and the chain of large fills never
-                                   wait for each other level by level.  Without such a fill after
-                                   the leaves everything runs on the caller's stream.  0: vertices of one dependency level
-                                   (whose tables do not read each other) share their kernel
-                                   launches, one stream, table memory packed by lifetimes.  1: one
+                                   them every large fill (PASE_OPT_BULK_US), with every vertex
+                                   reading its table, runs on that stream level by level (lane 1),
+                                   and all other vertices level by level on a side stream at the
+                                   highest wave priority (lane 0); events only where a table is
+                                   read across the two, so the chain of small vertices and the
+                                   chain of large fills never wait for each other level by level.
+                                   Without such a fill after the leaves everything runs on the
+                                   caller's stream.  0: vertices of one dependency level (whose
+                                   tables do not read each other) share their kernel launches, one
+                                   stream, table memory packed by lifetimes.  1: one
                                    vertex at a time in sequence order (same packing).  4: bulk
                                    lane -- as 5, without the batched leaves (the large fills and
                                    their readers from level 0 on one stream).  4 and 5 keep every
@@ -143,9 +143,9 @@ typedef enum {
                                    (default), 1, 2 or 4 */
     PASE_OPT_C_SPLITS = 10,     /* same kernel: workgroups sharing one tile's c range (partial
                                    keys reduced by a second launch), 0 = chosen (default), else
-                                   min(value, K_v) for every vertex.  Any of these four knobs set,
-                                   or PASE_OPT_HOIST_ELEMS below its default, also keeps every
-                                   vertex off the class form (which has no tiles and no prep) */
+                                   min(value, K_v) for every vertex.  Any of these four knobs set
+                                   also keeps every vertex off the class, joint and exchange fills
+                                   (which have no such tiles) */
     PASE_OPT_CONFIG_SET = 12,   /* configuration set of the next pase_enumerate_configs: 0
                                    (default) power-of-two split factors, p = 2^L <= 65536; 1
                                    every tuple of positive integer factors (Sec. II's C(v)),
@@ -190,7 +190,9 @@ typedef enum {
                                    saves launches; any vertex under the sequential schedule).
                                    Default 2^18; 0 = never.  Not used with PASE_OPT_KERNEL = 1 */
     PASE_OPT_BULK_US = 17,      /* schedules 4 and 5: planned fill time (microseconds) from which a
-                                   row-kernel vertex runs on the bulk stream (default 100) */
+                                   row-kernel vertex runs on lane 1 (default 100); a class, joint
+                                   or exchange fill from a quarter of it (its table's stores hold
+                                   up the other lane's loads as well) */
     PASE_OPT_FUSED_MIN = 20,    /* 1 (default): a row-kernel vertex without a column digit whose one
                                    lookup is the whole table of its predecessor in the recurrence
                                    (that table's column digit being this vertex, the same row
@@ -210,7 +212,10 @@ typedef enum {
                                    tables filled two or more slots before its own has its prep
                                    built on a second stream right after the last of them, while
                                    the slots in between run; its blocks get memory of their own.
-                                   0: never.  The allocation-free entry point builds every prep
+                                   0: never.  A value from 1 to below the default asks for preps
+                                   and so also keeps every vertex off the class, joint and
+                                   exchange fills (which have none); 0 and values from the default
+                                   up do not.  The allocation-free entry point builds every prep
                                    in its own slot.  Re-plans */
     PASE_OPT_HALO = 19          /* 1: the next pase_enumerate_configs adds the halo exchange of
                                    convolutions to every layer cost (an assumed form; the paper

@@ -727,10 +727,10 @@ static pase_status plan_fills(pase_graph_t g) {
     // level at p = 64, 17 -> 6 us on its small chain vertices), at more work
     // per cell: not where that digit is small (dense_faster below).  A direct
     // vertex without such a digit takes the same kernel's plain minimum (8.2 -> 5.5 us per launch on
-    // the residual CNN at p = 8).  The tile knobs and a hoisting threshold below its default
-    // ask for the dense fills and their preps, which they then get.  With the
-    // volume model a direct vertex takes the plain minimum as well, each edge's
-    // matrix read as a lookup.
+    // the residual CNN at p = 8).  The tile knobs and a hoisting threshold
+    // below its default (0, no hoisting, is none) ask for the dense fills and
+    // their preps, which they then get.  With the volume model a direct vertex
+    // takes the plain minimum as well, each edge's matrix read as a lookup.
     const bool min_ok = kernel_mode == 0 && !g->dense_only && !g->overridden && !g->tile_cols && !g->tile_rows &&
                         !g->tile_parts && !g->c_splits && (!g->hoist_elems || g->hoist_elems >= kHoistElems);
     const bool class_ok = min_ok && !g->volume;

@@ -1047,14 +1047,19 @@ __device__ __forceinline__ void class_item_small(const ClassArgs &a, uint32_t lb
 // its class's X values and of the two minima.  When X of all K configurations
 // does not fit (keep = 0; 64 rows, one wave per group) each class's X values are
 // formed again: one more evaluation per (c, row), against Kz / K table entries.
-// Bound by the stores of its table (10 bytes per entry).
 //
-// Measured on the Transformer at p = 64: its 36 leaves, four of them 8.3e9
-// cells, 2.05 ms dense (94% of the fp64 issue rate) and 0.24 ms here (3 TB/s of
-// stores); one level of its encoder chain 20 us (prep, row fill, split
-// reduction) and 6 us.  With the data read from global memory by every group
-// instead of staged, the leaves took 0.57 ms (vector loads of data that whole
-// waves share).
+// Bound by the stores of its table (10 bytes per entry) where its lookups are
+// small: 1.8e7 entries of the Transformer at p = 64 in 47 us, 3.8 TB/s, with
+// the VALU busy for 31% of its cycles; 1.1e8 at p = 24 in 278 us, 4.0 TB/s.
+// With a lookup of the table's size its loads are waited for as well: 78 us
+// (2.3 TB/s, waves waiting for 69% of their cycles) and 569 us.
+//
+// Against the dense fill: four leaves of 8.3e9 cells and 32 small ones 2.05 ms
+// dense (94% of the fp64 issue rate) and 0.24 ms here, before the four were
+// taken into joint fills; one level of the encoder chain 20 us (prep, row fill,
+// split reduction) and 6 us.  With the data read from global memory by every
+// group instead of staged, those leaves took 0.57 ms (vector loads of data that
+// whole waves share).
 template <typename KeyT, int NE, int NT>
 __device__ __forceinline__ void class_item_staged(const ClassArgs &a, uint32_t lb, char *lds) {
     using Ops = KeyOps<KeyT>;
@@ -1514,8 +1519,16 @@ __device__ __forceinline__ void half_item(const JointArgs &a, uint32_t b, char *
 // the lower digits stays in registers and LDS.  XI goes to LDS in class order,
 // so a class's minimum is a thread's walk over a few neighbouring values;
 // three barriers per row (XI and its minima; class minima; those of XJ + I),
-// then the row's entries.  Bound by the LDS traffic, about 26 accesses per
-// configuration; on small vertices by the latency of the steps.
+// then the row's entries.
+//
+// Bound by none of the units: by the chain of steps in a row and their
+// barriers.  38 808 rows of 462 configurations (316 us under the counters):
+// 2430 VALU and 456 LDS wave instructions per row, VALU busy for 52% of its
+// cycles, LDS for 36% (a third of these bank conflicts), waves waiting for 64%
+// of theirs with 20 of them per CU.  148 393 rows of 731: 5140 and 1150, 45%,
+// 34%, 74% with 22 per CU; stores 0.38 TB/s.  The walks over classes of 1 to 24
+// members leave most lanes of their waves idle.  On small vertices by the
+// latency of the steps alone.
 //
 // Measured on the Transformer at p = 64: a cross-attention score vertex (7056
 // rows, 3.3e6 entries of 462 configurations) 68 us against 167 + 26 us for the
@@ -1523,8 +1536,7 @@ __device__ __forceinline__ void half_item(const JointArgs &a, uint32_t b, char *
 // rows) 311 us against 613 + 162 us -- and the five tables these two kinds read,
 // 180 MB each, are not formed at all (level 0: 244 -> 21 us).  140 registers
 // instead of 80 (one workgroup per CU instead of three) took 131 and 654 us;
-// class members read four at a time, the last one repeated, 80 and 364 us (the
-// reads and minima issued count, not their latency).
+// class members read four at a time, the last one repeated, 80 and 364 us.
 template <typename KeyT, int U, bool HASE>
 __device__ __forceinline__ void joint_item(const JointArgs &a, uint32_t b, char *lds) {
     using Ops = KeyOps<KeyT>;
