@@ -5,12 +5,13 @@ enumeration, GenerateSeq, plans) + pase_find_best_strategy (cost tables,
 per-vertex DP fill, back-substitution).  Default workload: the Transformer
 encoder-decoder graph at p = 64 modeled devices (6.99e10 DP cell updates).
 
-Prints one JSON line: DP cell-updates/s of whole steps (`value`), the step
-wall time, the roofline of the dominant kernel (the row/column-chunk fill,
-fp64 add + min per cell, timed with HIP events on the search stream), the
-parity of the result with the CPU oracle's stored answer, and the oracle's
-own time for the same search on the host cores (and single-threaded on a
-prefix of the vertex sequence).
+Prints one JSON line: DP cell-updates/s of whole steps (`value`: the cells of
+the recurrence, K_v times the table's entries, over the step's time, whether
+they are evaluated one by one or by classes), the step wall time, the roofline
+of the fill kernel with the most device time (timed with HIP events on the
+search streams), the parity of the result with the CPU oracle's stored answer,
+and the oracle's own time for the same search on the host cores (and
+single-threaded on a prefix of the vertex sequence).
 """
 import argparse
 import json
@@ -118,20 +119,49 @@ def copy_calibration(mib):
     print(json.dumps({"copy_bytes": n, "copies": 3}), flush=True)
 
 
-def traffic_from_profile():
-    """HBM bytes per launch of the row kernel from the committed counter
-    summary, if it was taken on the current kernel sources; else None."""
+def counters_from_profile(kernel, workload):
+    """The committed counter record of a fill kernel (HBM bytes per launch, VALU
+    lane operations per search), if it was taken on this workload and the
+    current kernel sources; else None."""
     from paper_2407_04001_amd.profiling import kernel_source_digest
-    path = os.path.join(ROOT, "profiles", "k_fill_rows_hbm_traffic.json")
+    path = os.path.join(ROOT, "profiles", f"{kernel}_counters.json")
     try:
         with open(path) as f:
             prof = json.load(f)
         digest = kernel_source_digest(ROOT)
     except OSError:
         return None
-    if prof.get("kernel_sources_sha256") != digest:
+    return prof if prof.get("kernel_sources_sha256") == digest and prof.get("workload") == workload else None
+
+
+def fill_kernel(x):
+    """Name of the kernel that fills a vertex (pase_vertex_info), None if none does."""
+    if x["splits"] == 0:
         return None
-    return prof.get("bytes_per_launch")
+    if x["kernel"] == 0:
+        return "k_fill_generic"
+    if x["tile_cols"]:
+        return "k_fill_rows" if x["tile_cols"] > 1 else "k_fill_rows, column-less"
+    if x["parts"] == 2:
+        return "k_fill_joint" if x["column"] >= 0 else "k_fill_exch"
+    return "k_fill_class" if x["kernel"] == 1 else "k_fill_class, k_fill_direct (small vertices)"
+
+
+def fill_times(pg):
+    """{kernel: [ms, launches]} of the last search, profiled launch by launch
+    (the vertices of one launch carry the same time)."""
+    seen, out = set(), {}
+    for v in range(pg.nv):
+        x = pg.vertex_info(v)
+        k = fill_kernel(x)
+        key = (k, x["level"], x["lane"], x["fill_ms"])
+        if k is None or not x["fill_ms"] or key in seen:
+            continue
+        seen.add(key)
+        t = out.setdefault(k, [0.0, 0])
+        t[0] += x["fill_ms"]
+        t[1] += 1
+    return out
 
 
 SCHEDULES = {0: "level", 1: "sequential", 4: "bulk lane", 5: "split chains"}
@@ -224,14 +254,12 @@ def run_workload(name, seed, steps, warmup, cpu_cells, cpu_single_cells, no_cpu,
     elapsed = time.perf_counter() - t0
 
     # profiled steps, right after the timed ones: the same searches with HIP
-    # events (on the search stream) attached to every launch of the dominant
-    # kernel -- the row kernel with a column chunk per lane -- and recorded at
-    # the phase boundaries; they give the roofline and the device phases
-    rows_ms, rows_launches, prof_ms = 0.0, 0, []
-    if no_roofline:
-        prof_steps = 0
-    else:
-        prof_steps = steps
+    # events at the phase boundaries (and on the dense fills' launches), which
+    # give the device phases; then with events on every fill launch, which give
+    # the time of each fill kernel
+    prof_ms, kernels = [], {}
+    prof_steps = 0 if no_roofline else steps
+    if prof_steps:
         pg.set_option(OPT_PROFILE, 2)
         step()
         torch.cuda.synchronize()
@@ -243,18 +271,30 @@ def run_workload(name, seed, steps, warmup, cpu_cells, cpu_single_cells, no_cpu,
         prof_ms.append((time.perf_counter() - ts) * 1e3)
         assert (pmc, pstrat) == (mc, strat)
         pst = pg.stats()
-        rows_ms += pst["rows_fill_ms"]
-        rows_launches += pst["rows_launches"]
         for k in dev_keys:
             dev_phases[k] += pst[k] / prof_steps
+    if prof_steps:
+        pg.set_option(OPT_PROFILE, 1)
+        step()
+    for _ in range(prof_steps):
+        assert step() == (mc, strat)
+        for k, (ms, n) in fill_times(pg).items():
+            t = kernels.setdefault(k, [0.0, 0])
+            t[0] += ms / prof_steps
+            t[1] = n
     torch.cuda.synchronize()
     phases.update(dev_phases)
 
     cells = st["cells"]
     col_cells = st["rows_cells"] - st["stream_cells"]
     ops = OPS_PER_CELL if st["key_type"] == 0 else OPS_PER_CELL_U64
-    achieved = ops * col_cells * prof_steps / (rows_ms / 1e3) / 1e12 if rows_ms else 0.0
     t_roof_ms = ops * cells / (FP64_OPS_PEAK_T * 1e12) * 1e3
+    # the fill kernel with the most time: the row kernel's rate counts its
+    # cells, another's the VALU lane operations of the committed counter record
+    kernel, (kernel_ms, kernel_launches) = max(kernels.items(), key=lambda kv: kv[1][0], default=(None, (0.0, 0)))
+    counters = counters_from_profile(kernel, g["name"]) if headline else None
+    work = ops * col_cells if kernel == "k_fill_rows" else counters["valu_lane_ops_per_search"] if counters else None
+    achieved = work / (kernel_ms / 1e3) / 1e12 if work and kernel_ms else None
     parity = None
     # the oracle's stored answer for exactly this variant, if one was written
     gold_name = None
@@ -291,21 +331,24 @@ def run_workload(name, seed, steps, warmup, cpu_cells, cpu_single_cells, no_cpu,
         "phases_ms": {k[:-3]: round(v, 4) for k, v in phases.items()},
         "profiled_ms_per_step": sorted(prof_ms)[len(prof_ms) // 2] if prof_ms else None,
         "median_ms_per_step": sorted(step_ms)[len(step_ms) // 2],
-        # the whole search against the ALU roofline: every cell costs `ops` VALU
-        # lane-ops (t_roof), against the fill-kernel time and the step
+        # two (five) VALU lane-ops for every cell of the recurrence against the
+        # step.  The class, joint and exchange fills evaluate a small part of
+        # the cells one by one: above 1 this says how much less work they do
         "search_roofline": {"t_roof_ms": t_roof_ms, "ops_per_cell": ops,
                             "frac_of_step": t_roof_ms / (elapsed * 1e3 / steps)},
         "min_cost": mc, "parity_with_oracle": parity,
-        "roofline": {"bound": "alu", "kernel": "k_fill_rows",
+        "roofline": {"bound": "alu", "kernel": kernel,
                      "achieved": achieved, "peak": FP64_OPS_PEAK_T,
-                     "unit": "T fp64-op/s" if st["key_type"] == 0 else "T int32-op/s",
-                     "frac": achieved / FP64_OPS_PEAK_T,
-                     "traffic": traffic_from_profile() if headline else None,
-                     "launches_per_step": rows_launches // steps,
-                     "avg_launch_us": rows_ms * 1e3 / max(rows_launches, 1),
-                     "cells_per_step": col_cells,
+                     "unit": ("T VALU lane-op/s" if kernel != "k_fill_rows" else
+                              "T fp64-op/s" if st["key_type"] == 0 else "T int32-op/s"),
+                     "frac": achieved / FP64_OPS_PEAK_T if achieved else None,
+                     "traffic": counters["bytes_per_launch"] if counters else None,
+                     "launches_per_step": kernel_launches,
+                     "avg_launch_us": kernel_ms * 1e3 / max(kernel_launches, 1),
+                     "ms_per_step": kernel_ms,
+                     "fill_kernels_ms": {k: round(v[0], 4) for k, v in sorted(kernels.items(), key=lambda kv: -kv[1][0])},
                      "timed_in": f"{steps} profiled steps after the timed ones (HIP events on the search "
-                                 "stream around every launch of the kernel)"},
+                                 "streams around every fill launch)"},
     }
     if not no_cpu:
         out["cpu_baseline"] = oracle_baseline(g, p, int(cpu_cells), int(cpu_single_cells), all_integers, bf,
